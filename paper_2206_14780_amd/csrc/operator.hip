@@ -182,6 +182,32 @@ struct RowWriter {
     }
 };
 
+// RowWriter's counterpart for the windowed code: the window index of a column
+// comes from the block's ranges, which ascend with the columns of a row, so a
+// lane walks them once.
+template <typename T>
+struct WinWriter {
+    T* coef;
+    uint16_t* dcol;
+    float* lo;
+    int64_t base;
+    const WinRange* tab;  // the block's ranges
+    int32_t own;          // column code of the row itself (padding)
+    int32_t j = 0;
+    int32_t q = 0;
+    __device__ int32_t code(int32_t col) {
+        while (col >= tab[q].beg + tab[q].len) ++q;
+        return (col - tab[q].beg + tab[q].base) * kWinStep;
+    }
+    __device__ void put(int32_t col, double c) {
+        sell_put(coef, dcol, lo, slot_of<T>(base, j), code(col), c);
+        ++j;
+    }
+    __device__ void pad(int32_t width) {
+        for (; j < width; ++j) sell_put(coef, dcol, lo, slot_of<T>(base, j), own, 0.0);
+    }
+};
+
 // Slots of a row with c entries in column order: c plus one escape per step
 // outside [0, kEscape).
 struct SlotCounter {
@@ -229,7 +255,9 @@ __global__ __launch_bounds__(kBlock) void k_row_count(NbrView nv, PartView pv, O
 }
 
 // Slice size = 64 x (most slots of a row of the slice); nnz += entries.
+// Windowed columns (*wmax <= wlim) need no escapes: slots = entries.
 __global__ __launch_bounds__(kBlock) void k_slice_size(int64_t n, int64_t nslices, int32_t pack,
+                                                       const int32_t* __restrict__ wmax, int32_t wlim,
                                                        const int32_t* __restrict__ cnt,
                                                        const int32_t* __restrict__ creal,
                                                        int64_t* __restrict__ size,
@@ -244,12 +272,13 @@ __global__ __launch_bounds__(kBlock) void k_slice_size(int64_t n, int64_t nslice
     const int nw = blockDim.x / kWave;
     int64_t tot = 0;
     int32_t longest = 0;
+    const bool windowed = *wmax <= wlim;
     for (int64_t s = (int64_t)blockIdx.x * nw + wid; s < nslices; s += (int64_t)gridDim.x * nw) {
         const int64_t r = s * kWave + lane;
         int32_t w = 0;
         if (r < n) {
-            w = cnt[r];
             const int32_t c = creal[r];
+            w = windowed ? c : cnt[r];
             tot += c;
             longest = max(longest, c);
         }
@@ -275,6 +304,112 @@ __global__ __launch_bounds__(kBlock) void k_slice_size(int64_t n, int64_t nslice
             atomicMax(reinterpret_cast<int32_t*>(nnz + 1), longest);
         }
     }
+}
+
+// The windows of a block of kWinRows rows, one wave per block: the cells of
+// the rows taken x-row by x-row of the cell grid, the neighbouring runs of
+// cells of each as index ranges, sorted and merged where they touch or nearly
+// do.  A block whose window would exceed `limit` takes one per half, or one
+// per slice.  wmax receives the largest window (kWinMax + 1 when a slice's
+// does not fit either).
+__global__ __launch_bounds__(kWave) void k_windows(NbrView nv, int32_t limit, WinRange* __restrict__ win,
+                                                   int32_t* __restrict__ wmax) {
+    constexpr int kGap = 4;     // particles between two ranges that are rather staged
+    constexpr int kRuns = 256;  // runs before merging
+    const Grid& g = nv.g;
+    const int lane = threadIdx.x;
+    const int64_t bid = blockIdx.x;
+    const int32_t nx = g.nc[0], ny = g.nc[1];
+    __shared__ int32_t beg[kRuns], end[kRuns], sb[kRuns], se[kRuns];
+    // ranges of rows [r0, r1] into tab; the window's size, or kWinMax + 1
+    const auto window = [&](int64_t r0, int64_t r1, WinRange* tab, int32_t parts) -> int32_t {
+        const int32_t ca = nv.scell[r0], cb = nv.scell[r1];
+        const int32_t l0 = ca / nx, l1 = cb / nx;  // x-rows of cells
+        if (l1 - l0 >= kRuns / 9) return kWinMax + 1;
+        // tasks: x-row, z and y neighbour, part of the run (middle, wrapped low, wrapped high)
+        const int32_t ntask = (l1 - l0 + 1) * 27;
+        int32_t cnt = 0;
+        for (int32_t t0 = 0; t0 < ntask; t0 += kWave) {
+            const int32_t t = t0 + lane;
+            int32_t b = 0, e = 0;
+            if (t < ntask) {
+                const int32_t l = l0 + t / 27, part = t % 3, iy = (t / 3) % 3, iz = (t / 9) % 3;
+                int32_t zs[3], ys[3];
+                const int nzs = axis_cells(l / ny, g.nc[2], g.per[2], zs);
+                const int nys = axis_cells(l % ny, ny, g.per[1], ys);
+                const int32_t xa = l == l0 ? ca % nx : 0, xe = l == l1 ? cb % nx : nx - 1;
+                int32_t lo = xa > 0 ? xa - 1 : 0, hi = xe < nx - 1 ? xe + 1 : nx - 1;
+                if (g.per[0] && nx < 3) {
+                    lo = 0;
+                    hi = nx - 1;
+                }
+                bool on = iz < nzs && iy < nys;
+                if (part == 1) {
+                    on = on && g.per[0] && nx >= 3 && xa == 0;
+                    lo = hi = nx - 1;
+                } else if (part == 2) {
+                    on = on && g.per[0] && nx >= 3 && xe == nx - 1;
+                    lo = hi = 0;
+                }
+                if (on) {
+                    const int32_t base = (zs[iz] * ny + ys[iy]) * nx;
+                    b = nv.cell_start[base + lo];
+                    e = nv.cell_start[base + hi + 1];
+                }
+            }
+            const uint64_t m = __ballot(e > b);
+            const int32_t at =
+                cnt + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0));
+            cnt += __popcll(m);
+            if (cnt > kRuns) return kWinMax + 1;
+            if (e > b) {
+                beg[at] = b;
+                end[at] = e;
+            }
+        }
+        __syncthreads();
+        for (int32_t k = lane; k < cnt; k += kWave) {
+            int32_t rank = 0;
+            for (int32_t i = 0; i < cnt; ++i) rank += beg[i] < beg[k] || (beg[i] == beg[k] && i < k);
+            sb[rank] = beg[k];
+            se[rank] = end[k];
+        }
+        __syncthreads();
+        int32_t nr = 0, next = 1;  // window index 0 stays free for the unit before the first range
+        if (lane == 0) {
+            for (int32_t i = 0; i < cnt;) {
+                const int32_t b = sb[i];
+                int32_t e = se[i];
+                for (++i; i < cnt && sb[i] <= e + kGap; ++i) e = max(e, se[i]);
+                // base = b modulo 4; a 16-byte unit may reach one 3-vector over either end
+                const int32_t base = next + ((b - next) & 3);
+                if (nr == kWinRanges || (int64_t)base + (e - b) + 3 > kWinMax) {
+                    next = kWinMax;
+                    break;
+                }
+                tab[nr++] = WinRange{b, e - b, base, 0};
+                next = base + (e - b) + 2;
+            }
+            tab[0].head = nr | parts << 16;  // (at least the rows' own cells)
+        }
+        __syncthreads();
+        return __builtin_amdgcn_readfirstlane(next) + 1;
+    };
+    int32_t largest = kWinMax + 1, parts = 1;
+    for (; parts <= kWinParts; parts *= 2) {
+        largest = 0;
+        const int32_t rows = kWinRows / parts;
+        for (int32_t k = 0; k < parts && largest <= limit; ++k) {
+            const int64_t r0 = bid * kWinRows + k * rows;
+            WinRange* tab = win + (bid * kWinParts + k) * kWinRanges;
+            if (r0 < nv.n)
+                largest = max(largest, window(r0, min(r0 + rows, nv.n) - 1, tab, parts));
+            else if (lane == 0)
+                tab[0].head = parts << 16;
+        }
+        if (largest <= limit) break;
+    }
+    if (lane == 0) atomicMax(wmax, largest > limit ? kWinMax + 1 : largest);
 }
 
 // Pass 2: write the slots (coefficients evaluated inside the scan).
@@ -406,7 +541,7 @@ __global__ __launch_bounds__(kBlock) void k_row_scan(NbrView nv, PartView pv, Op
     creal[row] = sc.c;
 }
 
-template <typename T>
+template <typename T, bool WIN>
 __global__ __launch_bounds__(kBlock) void k_row_fill_list(NbrView nv, PartView pv, OpParams op, int64_t nslices,
                                                           const int32_t* __restrict__ creal,
                                                           const int32_t* __restrict__ list,
@@ -415,8 +550,18 @@ __global__ __launch_bounds__(kBlock) void k_row_fill_list(NbrView nv, PartView p
                                                           uint16_t* __restrict__ dcol, float* __restrict__ lo,
                                                           int32_t* __restrict__ c0, T* __restrict__ dg,
                                                           double* __restrict__ rs64, double* __restrict__ diag64,
-                                                          int32_t cap) {
-    const int64_t r = (int64_t)xcd_block(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x;
+                                                          int32_t cap, Sell<T> A) {
+    const int64_t bid = xcd_block(blockIdx.x, gridDim.x);
+    const int64_t r = bid * blockDim.x + threadIdx.x;
+    __shared__ WinRange tabs[WIN ? kWinParts * kWinRanges : 1];
+    const WinRange* tab = tabs;
+    if constexpr (WIN) {
+        static_assert(kBlock == kWinRows && kWinParts * kWinRanges <= kBlock, "one block's windows");
+        if (bid * kWinRows >= nv.n) return;
+        if (threadIdx.x < kWinParts * kWinRanges) tabs[threadIdx.x] = A.win[bid * (kWinParts * kWinRanges) + threadIdx.x];
+        __syncthreads();
+        tab += (threadIdx.x / (kWinRows / (tabs[0].head >> 16))) * kWinRanges;
+    }
     if (r >= nslices * kWave) return;
     const Grid& g = nv.g;
     const int64_t s = r / kWave;
@@ -514,7 +659,18 @@ __global__ __launch_bounds__(kBlock) void k_row_fill_list(NbrView nv, PartView p
         return w / sum;
     };
     const int32_t width = (int32_t)((sl_ptr[s + 1] - sl_ptr[s]) / kWave);
-    RowWriter<T> wr{coef, dcol, lo, lane_base<T>(sl_ptr[s], r % kWave)};
+    const int64_t lb = lane_base<T>(sl_ptr[s], r % kWave);
+    auto wr = [&] {
+        if constexpr (WIN) {
+            // a padding row beyond the last particle codes its slice's first row
+            WinWriter<T> ww{coef, dcol, lo, lb, tab, 0};
+            ww.own = ww.code((int32_t)(valid ? r : s * kWave));
+            ww.q = 0;
+            return ww;
+        } else {
+            return RowWriter<T>{coef, dcol, lo, lb};
+        }
+    }();
     int32_t first = row;
     double csum = 0.0;  // f32: FP64 sum of the stored coefficients
     if (listed) {
@@ -566,9 +722,19 @@ sph_status row_diag64(sph_ctx* ctx, const sph_nbr* nb, const PartView& pv, const
     return SPH_OK;
 }
 
+// Largest window (3-vectors) that a block stages at once: 40.1 KB in FP32,
+// four blocks (all that the registers allow) in the 160 KB of LDS; 80.2 KB in
+// FP64, two blocks.  About a fifth of the blocks then take two windows.
+// Operator launch at 33.7M particles, FP32, by limit 1760 / 2250 / 2700 /
+// 3340 / 4400 (three blocks) / 4480 (two): 4.23 / 3.79 / 3.58 / 3.44 / 3.54 /
+// 4.00 ms; FP64 at 328k by 1760 / 2250 / 2700 / 3340 / 4480 (one block): 91 /
+// 80 / 74 / 66 / 81 us.
+constexpr int32_t kWinLimit = 3340;
+static_assert(kWinLimit <= kWinMax, "window offsets fit 16 bits");
+
 template <typename T>
 sph_status build_sell(sph_ctx* ctx, const sph_nbr* nb, const PartView& pv, const OpParams& op, Sell<T>* out,
-                      const double** diag64, int64_t* nnz_out, int64_t* slots_out) {
+                      const double** diag64, bool reused, int64_t* nnz_out, int64_t* slots_out) {
     const int64_t n = nb->n;
     const int64_t nslices = ceil_div(n, kWave);
     // Test hook: the environment variable SPH_BUILD_LEGACY=1 selects the
@@ -577,6 +743,10 @@ sph_status build_sell(sph_ctx* ctx, const sph_nbr* nb, const PartView& pv, const
     if (op.f32cell && nb->g.kernel != SPH_KERNEL_WENDLAND)
         return ctx->fail(SPH_E_ARG, "SPH_OP_PAPER32 is defined for the Wendland kernel");
     const bool legacy = env_int("SPH_BUILD_LEGACY", 0) > 0 && !op.f32cell;
+    // The windows cost one latency-bound launch (21 us on 5,632 particles, 46
+    // on 187k with the Gaussian kernel) and save 5 to 30 us per operator pass:
+    // a matrix that is applied once keeps the delta code.
+    const bool windows = reused && !legacy;
     // list entries per row: room for every neighbour of the kernel's support
     // (int32 index + FP64 weight each) while that fits the budget
     const int32_t cap = nb->g.kernel == SPH_KERNEL_GAUSSIAN &&
@@ -591,10 +761,19 @@ sph_status build_sell(sph_ctx* ctx, const sph_nbr* nb, const PartView& pv, const
     SPH_TRY(ctx->ensure_t(kDiag64, n, &d));
     SPH_TRY(ctx->ensure_t(kSlSize, nslices, &size));
     SPH_TRY(ctx->ensure_t(kSlPtr, nslices + 1, &ptr));
-    unsigned long long* nnz_dev = nullptr;  // [0] nonzeros, [1] longest row
-    SPH_TRY(ctx->ensure_t(kNnzCount, 2, &nnz_dev));
-    SPH_HIP(hipMemsetAsync(nnz_dev, 0, 2 * sizeof(unsigned long long), ctx->stream));
+    unsigned long long* nnz_dev = nullptr;  // [0] nonzeros, [1] longest row, [2] largest window
+    SPH_TRY(ctx->ensure_t(kNnzCount, 3, &nnz_dev));
+    SPH_HIP(hipMemsetAsync(nnz_dev, 0, 3 * sizeof(unsigned long long), ctx->stream));
     // row kernels: whole XCD rounds of blocks (xcd_block needs a multiple of 8)
+    // windows of the operator's blocks; [2] of the counters: the largest
+    WinRange* win = nullptr;
+    const int64_t nwb = ceil_div(n, (int64_t)kWinRows);
+    if (windows) {
+        SPH_TRY(ctx->ensure_t(kWin, (size_t)nwb * kWinParts * kWinRanges, &win));
+        hipLaunchKernelGGL(k_windows, dim3((unsigned)nwb), dim3(kWave), 0, ctx->stream, nb->view(), kWinLimit, win,
+                           reinterpret_cast<int32_t*>(nnz_dev + 2));
+        SPH_LAUNCHED("k_windows");
+    }
     const dim3 rows_grid((unsigned)(ceil_div(ceil_div(n, kBlock), kNumXcd) * kNumXcd));
     const dim3 slice_grid((unsigned)(ceil_div(ceil_div(nslices * kWave, kBlock), kNumXcd) * kNumXcd));
     if (legacy) {
@@ -609,14 +788,17 @@ sph_status build_sell(sph_ctx* ctx, const sph_nbr* nb, const PartView& pv, const
     }
     hipLaunchKernelGGL(k_slice_size, dim3((unsigned)std::min<int64_t>(ceil_div(nslices * kWave, kBlock), 1024)),
                        dim3(kBlock), 0, ctx->stream,
-                       n, nslices, (int32_t)pack_of<T>(), cnt, creal, size, nnz_dev);
+                       n, nslices, (int32_t)pack_of<T>(), reinterpret_cast<const int32_t*>(nnz_dev + 2),
+                       windows ? kWinLimit : -1, cnt, creal, size, nnz_dev);
     SPH_LAUNCHED("k_row_count/k_slice_size");
     SPH_TRY(scan_i64(ctx, size, ptr, nslices));
     int64_t nnzp = 0;
-    unsigned long long hcnt[2] = {0, 0};
+    unsigned long long hcnt[3] = {0, 0, 0};
     SPH_HIP(hipMemcpyAsync(&nnzp, ptr + nslices, sizeof(int64_t), hipMemcpyDeviceToHost, ctx->stream));
     SPH_HIP(hipMemcpyAsync(hcnt, nnz_dev, sizeof(hcnt), hipMemcpyDeviceToHost, ctx->stream));
     SPH_HIP(hipStreamSynchronize(ctx->stream));
+    const int32_t wmax = (int32_t)hcnt[2];
+    const bool windowed = windows && wmax <= kWinLimit;
     if (nnz_out) *nnz_out = (int64_t)hcnt[0];
     if (slots_out) *slots_out = nnzp;
     T* coef = nullptr;
@@ -625,6 +807,8 @@ sph_status build_sell(sph_ctx* ctx, const sph_nbr* nb, const PartView& pv, const
     int32_t* c0 = nullptr;
     T* dg = nullptr;
     const size_t ns = (size_t)(nnzp > 0 ? nnzp : 1);
+    out->win = win;
+    out->wmax = windowed ? wmax : 0;
     SPH_TRY(ctx->ensure_t(kCoef, ns, &coef));
     SPH_TRY(ctx->ensure_t(kDcol, ns, &dcol));
     if constexpr (sizeof(T) == 4) SPH_TRY(ctx->ensure_t(kLo, ns, &lo));
@@ -638,8 +822,14 @@ sph_status build_sell(sph_ctx* ctx, const sph_nbr* nb, const PartView& pv, const
         // flight on an XCD then fit its L2 (with eight blocks per CU they
         // did not): 8.1 -> 5.8 ms at 4.49M particles.
         constexpr size_t kFillLdsReserve = 60 * 1024;
-        hipLaunchKernelGGL(k_row_fill_list<T>, slice_grid, dim3(kBlock), kFillLdsReserve, ctx->stream, nb->view(), pv, op,
-                           nslices, creal, list, wlist, ptr, coef, dcol, lo, c0, dg, rs64, d, cap);
+        if (windowed)
+            hipLaunchKernelGGL((k_row_fill_list<T, true>), slice_grid, dim3(kBlock), kFillLdsReserve, ctx->stream,
+                               nb->view(), pv, op, nslices, creal, list, wlist, ptr, coef, dcol, lo, c0, dg, rs64, d,
+                               cap, *out);
+        else
+            hipLaunchKernelGGL((k_row_fill_list<T, false>), slice_grid, dim3(kBlock), kFillLdsReserve, ctx->stream,
+                               nb->view(), pv, op, nslices, creal, list, wlist, ptr, coef, dcol, lo, c0, dg, rs64, d,
+                               cap, *out);
         SPH_LAUNCHED("k_row_fill_list");
     } else {
         hipLaunchKernelGGL(k_row_fill<T>, dim3((unsigned)ceil_div(nslices * kWave, kBlock)), dim3(kBlock), 0,
@@ -659,9 +849,9 @@ sph_status build_sell(sph_ctx* ctx, const sph_nbr* nb, const PartView& pv, const
 }
 
 template sph_status build_sell<float>(sph_ctx*, const sph_nbr*, const PartView&, const OpParams&, Sell<float>*,
-                                      const double**, int64_t*, int64_t*);
+                                      const double**, bool, int64_t*, int64_t*);
 template sph_status build_sell<double>(sph_ctx*, const sph_nbr*, const PartView&, const OpParams&,
-                                       Sell<double>*, const double**, int64_t*, int64_t*);
+                                       Sell<double>*, const double**, bool, int64_t*, int64_t*);
 
 
 // Launch geometry of the row kernels.
@@ -700,15 +890,11 @@ sph_status apply_plain(sph_ctx* ctx, const sph_nbr* nb, const PartView& pv, cons
     const Launch L = make_launch(nb->n);
     if (mode == SPH_OP_PAPER32) {
         if constexpr (sizeof(T) == 4)
-            hipLaunchKernelGGL((k_apply_sell<T, kDotNone, T, true>), dim3(L.grid_apply), dim3(L.block_apply), 0,
-                               ctx->stream, (const int32_t*)nullptr, nb->n, *sell, x, y, (const T*)nullptr,
-                               (const double*)nullptr, (double*)nullptr);
+            launch_apply_sell<T, kDotNone, T, true>(ctx->stream, L, nullptr, *sell, x, y, nullptr, nullptr, nullptr);
         else
             return ctx->fail(SPH_E_ARG, "apply: SPH_OP_PAPER32 is single precision");
     } else if (mode == SPH_OP_CACHED) {
-        hipLaunchKernelGGL((k_apply_sell<T, kDotNone>), dim3(L.grid_apply), dim3(L.block_apply), 0, ctx->stream,
-                           (const int32_t*)nullptr, nb->n, *sell, x, y, (const T*)nullptr, (const double*)nullptr,
-                           (double*)nullptr);
+        launch_apply_sell<T, kDotNone>(ctx->stream, L, nullptr, *sell, x, y, nullptr, nullptr, nullptr);
     } else {
         hipLaunchKernelGGL((k_apply_otf<T, kDotNone>), dim3(L.grid_apply), dim3(L.block_apply), 0, ctx->stream,
                            (const int32_t*)nullptr, nb->view(), pv, op, x, y, (const T*)nullptr,
@@ -754,12 +940,12 @@ static sph_status apply_entry(sph_ctx* ctx, const sph_nbr* nb, const sph_particl
     SPH_TRY(gather_props(ctx, nb, p, &pv));
     OpParams op{v->dt, v->wall, v->avg, v->jacobi ? 1 : 0};
     T *xin = nullptr, *yout = nullptr;
-    SPH_TRY(ctx->ensure_t(kApplyIn, (size_t)nb->n * 3, &xin));
+    SPH_TRY(ctx->ensure_t(kApplyIn, (size_t)nb->n * 3 + kVecPad, &xin));
     SPH_TRY(ctx->ensure_t(kApplyOut, (size_t)nb->n * 3, &yout));
     SPH_TRY(gather_vec3<T>(ctx, nb, x, xin));
     Sell<T> sell{};
     if (v->op_mode == SPH_OP_PAPER32) op.f32cell = 1;
-    if (v->op_mode != SPH_OP_ONTHEFLY) SPH_TRY(build_sell<T>(ctx, nb, pv, op, &sell, nullptr));
+    if (v->op_mode != SPH_OP_ONTHEFLY) SPH_TRY(build_sell<T>(ctx, nb, pv, op, &sell, nullptr, false));
     SPH_TRY(apply_plain<T>(ctx, nb, pv, op, v->op_mode, &sell, xin, yout));
     SPH_TRY(scatter_vec3<T>(ctx, nb, yout, y));
     return SPH_OK;

@@ -223,9 +223,189 @@ __device__ inline void sell_row_kahan(const Sell<float>& A, int64_t base, int32_
     y = V3<float>{s0, s1, s2};
 }
 
+// ---------------------------------------------------------------------------
+// Windowed rows.
+// ---------------------------------------------------------------------------
+template <typename XT>
+constexpr size_t win_bytes(int32_t wmax) { return (size_t)wmax * 3 * sizeof(XT); }
+
+// Copies a window of nr ranges (lane r holds range r) into LDS: 16-byte units
+// by the direct global-to-LDS load (no registers, every unit in flight at
+// once), each wave taking whole runs of 64 units.  Ends with a barrier.
+template <typename XT>
+__device__ inline void win_stage(const WinRange& mine, int32_t nr, const XT* __restrict__ x, unsigned char* lds) {
+    constexpr int U = 16 / sizeof(XT);
+    typedef const __attribute__((address_space(1))) void* gptr;
+    typedef __attribute__((address_space(3))) void* lptr;
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    for (int32_t r = 0; r < nr; ++r) {
+        const WinRange t{__builtin_amdgcn_readlane(mine.beg, r), __builtin_amdgcn_readlane(mine.len, r),
+                         __builtin_amdgcn_readlane(mine.base, r), 0};
+        const int64_t e0 = 3 * (int64_t)t.beg;
+        const int32_t pre = (int32_t)(e0 % U);
+        const int32_t nv = (pre + 3 * t.len + U - 1) / U;
+        const XT* src = x + (e0 - pre);
+        XT* dst = reinterpret_cast<XT*>(lds) + (3 * t.base - pre);
+        for (int32_t v = wid * kWave; v < nv; v += (int32_t)blockDim.x)
+            if (v + lane < nv)
+                __builtin_amdgcn_global_load_lds((gptr)(src + (int64_t)(v + lane) * U), (lptr)(dst + v * U), 16, 0, 0);
+    }
+    __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();
+}
+
+// Stages the windows of block `bid` in turn and calls f() in the waves whose
+// rows the staged window serves.  Called by the whole block.
+template <typename T, typename XT, typename F>
+__device__ __forceinline__ void win_parts(const Sell<T>& A, int64_t bid, const XT* __restrict__ x, unsigned char* lds, F&& f) {
+    if (bid * kWinRows >= A.nslices * kWave) return;
+    // one load per lane brings a window's table (a scalar load per range, one
+    // after the other, took longer than the copy)
+    const WinRange* tab = A.win + bid * kWinParts * kWinRanges + (threadIdx.x & (kWinRanges - 1));
+    WinRange r = *tab;
+    const int32_t head = __builtin_amdgcn_readfirstlane(r.head);
+    const int32_t np = head >> 16;
+    win_stage(r, head & 0xFFFF, x, lds);
+    if constexpr (sizeof(XT) == 8) {
+        // a path of its own for the one-window block: with FP64 windows the
+        // LDS, not the registers it costs (160 against 100), bounds the
+        // blocks per CU; FP32 takes the shared path and four blocks
+        if (np == 1) {
+            f();
+            return;
+        }
+    }
+    const int32_t own = threadIdx.x / (kWinRows / np);
+    for (int32_t k = 0;;) {
+        if (own == k) f();
+        if (++k == np) break;
+        r = tab[k * kWinRanges];
+        __syncthreads();
+        win_stage(r, __builtin_amdgcn_readfirstlane(r.head) & 0xFFFF, x, lds);
+    }
+}
+
+// One group of slots in registers: the coefficients, the packed column codes
+// and (residual) the coefficients' low parts.
+template <typename T, bool RES>
+struct WinGroup {
+    static constexpr int P = pack_of<T>();
+    static constexpr int N = sizeof(T) == 4 ? (RES ? 8 : 16) : 8;  // slots
+    typedef uint16_t idv __attribute__((ext_vector_type(P)));
+    typename Pack<T, P>::v c[N / P];
+    idv d[N / P];
+    typename Pack<float, P>::v l[RES && sizeof(T) == 4 ? N / P : 1];
+    // slots k0 .. k0 + N - 1 below the slice width (uniform branches)
+    __device__ __forceinline__ void load(const Sell<T>& A, int64_t base, int32_t width, int32_t k0) {
+#pragma unroll
+        for (int q = 0; q < N / P; ++q) {
+            if (k0 + q * P < width) {
+                const int64_t i = slot_of<T>(base, k0 + q * P);
+                // read once per launch: non-temporal, so that the stream does
+                // not evict x from L2
+                c[q] = __builtin_nontemporal_load(reinterpret_cast<const typename Pack<T, P>::v*>(A.coef + i));
+                d[q] = __builtin_nontemporal_load(reinterpret_cast<const idv*>(A.dcol + i));
+                if constexpr (RES && sizeof(T) == 4)
+                    l[q] = __builtin_nontemporal_load(reinterpret_cast<const typename Pack<float, P>::v*>(A.lo + i));
+            }
+        }
+    }
+};
+
+// The slots of a row as a ring of groups in registers: D groups are in flight
+// at once, the first of them from before the window is staged.
+template <typename T, bool RES, typename XT>
+struct WinStream {
+    typedef WinGroup<T, RES> G;
+    static constexpr int P = G::P;
+    static constexpr int D = 3;
+    const Sell<T>& A;
+    int64_t base;   // the lane's first slot
+    int32_t width;  // slice width, uniform across the wave
+    G g[D];
+    __device__ __forceinline__ WinStream(const Sell<T>& A_, int64_t s, int lane) : A(A_) {
+        base = lane_base<T>(A.sl_ptr[s], lane);
+        width = (int32_t)((A.sl_ptr[s + 1] - A.sl_ptr[s]) / kWave);
+#pragma unroll
+        for (int d = 0; d < D; ++d) g[d].load(A, base, width, d * G::N);
+    }
+    // term(w, lo, x) for every slot in order (lo: 0 but for the residual)
+    template <typename F>
+    __device__ __forceinline__ void run(const unsigned char* win, F&& term) {
+        for (int32_t k0 = 0; k0 < width; k0 += D * G::N) {
+#pragma unroll
+            for (int d = 0; d < D; ++d) {
+                const G& s = g[d];
+#pragma unroll
+                for (int q = 0; q < G::N / P; ++q) {
+                    if (k0 + d * G::N + q * P >= width) break;
+                    V3<XT> xv[P];
+#pragma unroll
+                    for (int e = 0; e < P; ++e) {
+                        const XT* v = reinterpret_cast<const XT*>(win + (uint32_t)s.d[q][e] * (sizeof(XT) / 4));
+                        xv[e] = V3<XT>{v[0], v[1], v[2]};
+                    }
+#pragma unroll
+                    for (int e = 0; e < P; ++e) {
+                        double lo = 0.0;
+                        if constexpr (RES && sizeof(T) == 4) lo = (double)s.l[q][e];
+                        term(s.c[q][e], lo, xv[e]);
+                    }
+                }
+                g[d].load(A, base, width, k0 + (d + D) * G::N);
+            }
+        }
+    }
+};
+
+// sell_row on the window.
+template <typename T, bool RES, typename ACC, typename XT>
+__device__ __forceinline__ void win_row(WinStream<T, RES, XT>& st, const unsigned char* win, const V3<XT>& xs, ACC& a0, ACC& a1,
+                               ACC& a2) {
+    st.run(win, [&](T c, double lo, const V3<XT>& xv) __attribute__((always_inline)) {
+        if constexpr (RES) {
+            const double w = (double)c + lo;
+            a0 += w * ((double)xv.x - (double)xs.x);
+            a1 += w * ((double)xv.y - (double)xs.y);
+            a2 += w * ((double)xv.z - (double)xs.z);
+        } else {
+            a0 = fma_t(c, xv.x - xs.x, a0);
+            a1 = fma_t(c, xv.y - xs.y, a1);
+            a2 = fma_t(c, xv.z - xs.z, a2);
+        }
+    });
+}
+
+// sell_row_kahan on the window.
+__device__ __forceinline__ void win_row_kahan(WinStream<float, false, float>& st, const unsigned char* win,
+                                     const V3<float>& xs, float d, V3<float>& y) {
+    float s0 = 0.f, s1 = 0.f, s2 = 0.f, c0 = 0.f, c1 = 0.f, c2 = 0.f;
+    kahan_add(s0, c0, d * xs.x);
+    kahan_add(s1, c1, d * xs.y);
+    kahan_add(s2, c2, d * xs.z);
+    st.run(win, [&](float c, double, const V3<float>& xv) __attribute__((always_inline)) {
+        if (c != 0.f) {
+            kahan_add(s0, c0, c * xv.x);
+            kahan_add(s1, c1, c * xv.y);
+            kahan_add(s2, c2, c * xv.z);
+        }
+    });
+    y = V3<float>{s0, s1, s2};
+}
+
+template <typename T, bool RES>
+struct AccOf {
+    typedef T t;
+};
+template <typename T>
+struct AccOf<T, true> {
+    typedef double t;
+};
+
 // Cached operator: y_r = rs_r x_r + sum_k coef[r,k] (x[col[r,k]] - x_r).
-// One wavefront per 64-row slice; each block takes a contiguous range of
-// slices (XCD-aware order) and its waves interleave over it.  With kDotResid
+// One wavefront per 64-row slice, a block of consecutive slices (XCD-aware
+// order).  With kDotResid
 // the kernel writes y = b64 - A x (FP64-accurate, rounded to T) instead, and
 // x may be held in another precision XT; with kDotCG, b64 holds the weights
 // D of the inner product.
@@ -233,7 +413,17 @@ __device__ inline void sell_row_kahan(const Sell<float>& A, int64_t base, int32_
 // KH (T = float only): the paper's single precision: the row in plain form
 // with compensated FP32 sums (sell_row_kahan, A.dg the plain diagonal) and
 // the inner products of FP32 products with compensated FP32 sums.
-template <typename T, int MODE, typename XT = T, bool KH = false>
+//
+// WIN: the windowed column code (see Sell).  The block first copies its
+// window of x into LDS (about 130 bytes a row against the matrix's 490); the
+// gathers of x, one per slot and lane, are then LDS reads, and the matrix
+// stream has the vector memory path to itself.  The wave's first three groups
+// of slots are loaded before the window.  A launch (A s with two dots):
+// 4.13 -> 3.33 ms at 33.7M particles in FP32 (5.3 TB/s of matrix, vectors and
+// windows' own share of HBM), 140 -> 115 us at 1.16M, 85 -> 61 us at 328k in
+// FP64; the delta-coded kernel waits for its gathers, this one for HBM and, a
+// sixth of its time, for the windows.
+template <typename T, int MODE, typename XT = T, bool KH = false, bool WIN = false>
 __global__ __launch_bounds__(kApplyMaxBlock) void k_apply_sell(const int32_t* __restrict__ halt, int64_t n, Sell<T> A,
                                                           const XT* __restrict__ x, T* __restrict__ y,
                                                           const T* __restrict__ w, const double* __restrict__ b64,
@@ -243,6 +433,7 @@ __global__ __launch_bounds__(kApplyMaxBlock) void k_apply_sell(const int32_t* __
     constexpr bool RES = MODE == kDotResid;
     static_assert(!KH || (sizeof(T) == 4 && !RES), "single-precision arithmetic: FP32 operator, not the residual");
     __shared__ double lds[(KH ? 2 : 1) * K * kMaxWaves];
+    extern __shared__ __align__(16) unsigned char win_lds[];
     double acc[K];
     float cmp[K];
 #pragma unroll
@@ -251,21 +442,34 @@ __global__ __launch_bounds__(kApplyMaxBlock) void k_apply_sell(const int32_t* __
         cmp[k] = 0.f;
     }
     const int lane = threadIdx.x & (kWave - 1);
-    const int wid = threadIdx.x / kWave;
-    const int nw = blockDim.x / kWave;
+    const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const int64_t bid = xcd_block(blockIdx.x, gridDim.x);
-    const int64_t spb = ceil_div(A.nslices, (int64_t)gridDim.x);
-    const int64_t s0 = bid * spb;
-    const int64_t s1 = min(s0 + spb, A.nslices);
-    for (int64_t s = s0 + wid; s < s1; s += nw) {
-        const int64_t row = s * kWave + lane;
-        if (row >= n) continue;
+    const int64_t s = bid * (kApplyMaxBlock / kWave) + wid;  // the wave's slice
+    const int64_t row = s * kWave + lane;
+    const bool on = row < n;
+    // sums: the row's three sums of c (x_col - x_row), or under KH the whole row
+    typedef typename AccOf<T, RES>::t ACC;
+    ACC a0 = 0, a1 = 0, a2 = 0;
+    V3<T> yv{};
+    V3<XT> xs{};
+    if constexpr (WIN) {
+        static_assert(kApplyMaxBlock == kWinRows, "one block's windows");
+        WinStream<T, RES, XT> st(A, min(s, A.nslices - 1), lane);
+        if (on) xs = ld3(x, row);
+        win_parts(A, bid, x, win_lds, [&]() __attribute__((always_inline)) {
+            if (!on) return;
+            if constexpr (KH) win_row_kahan(st, win_lds, xs, A.dg[row], yv);
+            else win_row<T, RES>(st, win_lds, xs, a0, a1, a2);
+        });
+    } else if (on) {
         const int64_t base = lane_base<T>(A.sl_ptr[s], lane);
         const int32_t width = (int32_t)((A.sl_ptr[s + 1] - A.sl_ptr[s]) / kWave);
-        const V3<XT> xs = ld3(x, row);
+        xs = ld3(x, row);
+        if constexpr (KH) sell_row_kahan(A, base, width, (int32_t)row, x, xs, A.dg[row], yv);
+        else sell_row<T, RES, ACC, XT>(A, base, width, (int32_t)row, x, xs, a0, a1, a2);
+    }
+    if (on) {
         if constexpr (RES) {
-            double a0 = 0.0, a1 = 0.0, a2 = 0.0;
-            sell_row<T, true, double, XT>(A, base, width, (int32_t)row, x, xs, a0, a1, a2);
             const double d = A.rs64[row];
             const V3<double> bb = ld3(b64, row);
             const double r0 = bb.x - (d * (double)xs.x + a0);
@@ -276,12 +480,7 @@ __global__ __launch_bounds__(kApplyMaxBlock) void k_apply_sell(const int32_t* __
             acc[2] += r2 * r2;
             st3(y, row, V3<T>{(T)r0, (T)r1, (T)r2});
         } else {
-            V3<T> yv;
-            if constexpr (KH) {
-                sell_row_kahan(A, base, width, (int32_t)row, x, xs, A.dg[row], yv);
-            } else {
-                T a0 = T(0), a1 = T(0), a2 = T(0);
-                sell_row<T, false>(A, base, width, (int32_t)row, x, xs, a0, a1, a2);
+            if constexpr (!KH) {
                 const T d = A.dg[row];
                 yv.x = fma_t(d, xs.x, a0);
                 yv.y = fma_t(d, xs.y, a1);
@@ -392,6 +591,19 @@ __global__ __launch_bounds__(kApplyMaxBlock) void k_apply_otf(const int32_t* __r
         }
     }
     if constexpr (MODE != kDotNone) write_partials<K>(acc, lds, part);
+}
+
+// Launch of the cached operator in the matrix's column code.
+template <typename T, int MODE, typename XT = T, bool KH = false>
+inline void launch_apply_sell(hipStream_t stream, const Launch& L, const int32_t* halt, const Sell<T>& A, const XT* x,
+                              T* y, const T* w, const double* b64, double* part) {
+    const dim3 grid(L.grid_apply), block(L.block_apply);
+    if (A.wmax > 0)
+        hipLaunchKernelGGL((k_apply_sell<T, MODE, XT, KH, true>), grid, block, win_bytes<XT>(A.wmax), stream, halt,
+                           L.n, A, x, y, w, b64, part);
+    else
+        hipLaunchKernelGGL((k_apply_sell<T, MODE, XT, KH, false>), grid, block, 0, stream, halt, L.n, A, x, y, w, b64,
+                           part);
 }
 
 }  // namespace sph

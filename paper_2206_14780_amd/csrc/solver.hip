@@ -702,8 +702,8 @@ struct Solver {
     void apply(const int32_t* halt, const XT* xin, T* yout, const T* w, double* part) {
         const double* aux = MODE == kDotCG ? dw : b64;
         if (mode == SPH_OP_CACHED)
-            hipLaunchKernelGGL((k_apply_sell<T, MODE, XT, KH && MODE != kDotResid>), ga(), ba(), 0, ctx->stream,
-                               halt, L.n, sell, xin, yout, w, aux, part);
+            launch_apply_sell<T, MODE, XT, KH && MODE != kDotResid>(ctx->stream, L, halt, sell, xin, yout, w, aux,
+                                                                   part);
         else
             hipLaunchKernelGGL((k_apply_otf<T, MODE, XT>), ga(), ba(), 0, ctx->stream, halt, nb->view(), pv, op,
                                xin, yout, w, aux, part);
@@ -803,20 +803,21 @@ sph_status solve_impl(sph_ctx* ctx, const sph_nbr* nb, const sph_particles* part
     ++S.launches;
     S.profile = std::max(o->profile, 0);
     if (S.mode == SPH_OP_CACHED) {
-        SPH_TRY(build_sell<T>(ctx, nb, S.pv, S.op, &S.sell, &S.diag64, &rep->mat_nnz, &rep->mat_slots));
-        S.launches += 6;
+        SPH_TRY(build_sell<T>(ctx, nb, S.pv, S.op, &S.sell, &S.diag64, true, &rep->mat_nnz, &rep->mat_slots));
+        S.launches += 7;
     } else {
         SPH_TRY(row_diag64(ctx, nb, S.pv, S.op, &S.diag64));
         ++S.launches;
     }
     const size_t v3 = (size_t)n * 3;
+    const size_t v3p = v3 + kVecPad;  // vectors that operators stage in 16-byte units
     SPH_TRY(ctx->ensure_t(kVecB, v3, &S.b));
-    SPH_TRY(ctx->ensure_t(kVecX, v3, &S.x));  // X
+    SPH_TRY(ctx->ensure_t(kVecX, v3p, &S.x));  // X
     SPH_TRY(ctx->ensure_t(kVecR, v3, &S.r));
     SPH_TRY(ctx->ensure_t(kVecRh0, v3, &S.rh0));
-    SPH_TRY(ctx->ensure_t(kVecP, v3, &S.p));
+    SPH_TRY(ctx->ensure_t(kVecP, v3p, &S.p));
     SPH_TRY(ctx->ensure_t(kVecAp, v3, &S.ap));
-    SPH_TRY(ctx->ensure_t(kVecS, v3, &S.s));
+    SPH_TRY(ctx->ensure_t(kVecS, v3p, &S.s));
     SPH_TRY(ctx->ensure_t(kVecAs, v3, &S.as));
     SPH_TRY(ctx->ensure_t(kVecTmp, v3, &S.tmp));
     SPH_TRY(ctx->ensure_t(kB64, v3, &S.b64));
@@ -876,7 +877,7 @@ sph_status solve_impl(sph_ctx* ctx, const sph_nbr* nb, const sph_particles* part
             const void* uu[3];
             for (int c = 0; c < 3; ++c) uu[c] = o->warm_u[c] ? o->warm_u[c] : (o->x0_given ? xout[c] : rhs[c]);
             X* ub = nullptr;
-            SPH_TRY(ctx->ensure_t(kWarmU, v3, &ub));
+            SPH_TRY(ctx->ensure_t(kWarmU, v3p, &ub));
             SPH_TRY(gather_vec3<X>(ctx, nb, uu, ub));
             ucell = ub;
         }

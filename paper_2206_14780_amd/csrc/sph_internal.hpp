@@ -81,14 +81,25 @@ struct OpParams {
 // Sliced ELLPACK matrix, one slice = 64 consecutive rows (one wavefront).
 // Entry k of row r = s*64 + l lives at slot
 //   sl_ptr[s] + (k / P) * 64 P + l P + k % P,
-// with P = pack_of<T>() (4 for FP32 coefficients, 1 for FP64): each lane's P
-// consecutive entries are adjacent (one vector load) and the 64 lanes' packs
-// of one slot group are contiguous; slice widths are multiples of P.  Columns
-// are delta coded: a row's columns ascend; the row starts at column c0[r]
-// and each slot adds its 16-bit step dcol (the first entry steps by 0).  A
-// step that does not fit takes an escape slot (dcol = kEscape) whose
-// coefficient bits hold the whole jump and which contributes nothing.  Rows
-// shorter than their slice are padded with (step 0, coef 0).  The operator is
+// with P = pack_of<T>() (4 for FP32 coefficients, 2 for FP64): each lane's P
+// consecutive entries are adjacent (one 16-byte load) and the 64 lanes' packs
+// of one slot group are contiguous; slice widths are multiples of P.  A row's
+// columns ascend.  They are coded in one of two ways:
+//   windowed (wmax > 0): each block of kWinRows rows has a window, or one for
+//     each of its nparts (2 or 4) equal parts: the union of the index ranges
+//     of the rows' neighbour cells as at most kWinRanges disjoint ranges of
+//     particles (win), each with the window index its first particle
+//     takes; dcol holds kWinStep times the window index of the
+//     column (a byte offset into the window of FP32 3-vectors that the
+//     operator stages in LDS).  Rows shorter than their slice are padded with
+//     (own row, coef 0).
+//   delta coded (wmax = 0; a matrix for one product, or a system with a
+//     window too large to stage): the row
+//     starts at column c0[r] and each slot adds its 16-bit step dcol (the
+//     first entry steps by 0).  A step that does not fit takes an escape slot
+//     (dcol = kEscape) whose coefficient bits hold the whole jump and which
+//     contributes nothing.  Padding: (step 0, coef 0).
+// The operator is
 // applied in difference form, y_r = rs_r x_r + sum_k coef[r,k] (x_col - x_r),
 // with rs_r the row sum of the matrix, which the structure of A fixes exactly
 // (1/A_rr for a Jacobi-scaled fluid row, 1 unscaled, 2 for a dummy-wall row
@@ -97,11 +108,25 @@ struct OpParams {
 // lo = coefficient - (double)coef, so coef + lo carries ~48 bits for the
 // FP64-accurate residual.
 constexpr uint16_t kEscape = 0xFFFF;
-// Slots of a lane stored together: four FP32 coefficients make one 16-byte
-// load; FP64 keeps one (four measured slower there: more registers, lower
-// occupancy).
+// Slots of a lane stored together: one 16-byte load of coefficients.
 template <typename T>
-constexpr int pack_of() { return sizeof(T) == 4 ? 4 : 1; }
+constexpr int pack_of() { return sizeof(T) == 4 ? 4 : 2; }
+
+// Windows of the operator (see Sell).
+constexpr int kWinRows = 256;     // rows of a block of the row kernels
+constexpr int kWinParts = 4;      // windows of a block at most
+constexpr int kWinRanges = 32;    // ranges of a window at most
+constexpr int kWinStep = 12;      // bytes of an FP32 3-vector
+constexpr int kWinMax = 65535 / kWinStep;  // largest window whose offsets fit 16 bits
+constexpr int kVecPad = 4;        // values past the end of a vector that the 16-byte units may read
+// One range of a window: particles [beg, beg + len) take the window indices
+// base, base + 1, ...; base = beg modulo 4, so that the 16-byte units of the
+// source array and of the staged copy coincide in FP32 and FP64.
+// The head of a window's first range: its ranges in the low half, the block's
+// windows in the high half.
+struct alignas(16) WinRange {
+    int32_t beg, len, base, head;
+};
 
 // First slot of lane l of a slice starting at slot sl, and its k-th slot.
 template <typename T>
@@ -119,7 +144,9 @@ struct Sell {
     const T* coef;          // per slot
     const uint16_t* dcol;   // per slot: column step or kEscape
     const float* lo;        // per slot, FP32 only
-    const int32_t* c0;      // per row: first column (the row itself if empty)
+    const int32_t* c0;      // per row: first column (the row itself if empty); delta coded
+    const WinRange* win;    // [blocks of kWinRows rows][kWinParts][kWinRanges]; windowed
+    int32_t wmax;           // 3-vectors of the largest window, 0: delta coded
     const T* dg;            // row sum of the (scaled) matrix, per row
     const double* rs64;     // the same row sums in FP64
 };
@@ -212,7 +239,7 @@ enum Slot : int {
     kMass, kRho, kMu, kType, kMuMr, kInvRho, kCnt, kCntReal, kDiag64, kWsum, kSlSize, kSlPtr, kCoef, kDcol, kC0, kDg, kLo, kRs64,
     kVecB, kVecX, kVecR, kVecRh0, kVecP, kVecAp, kVecS, kVecAs, kVecTmp, kB64,
     kPartA1, kPartA2, kPartK3, kPartChk, kCtl, kHist, kStallHist, kScanTmp,
-    kApplyIn, kApplyOut, kExportCnt, kNnzCount, kMlpPart, kMlpOut, kWarmS, kWarmO, kWarmInfo, kWarmPart,
+    kApplyIn, kApplyOut, kExportCnt, kNnzCount, kMlpPart, kMlpOut, kWin, kWarmS, kWarmO, kWarmInfo, kWarmPart,
     kWarmPart2, kWarmU, kList, kWList, kNbrCell, kNbrCount, kNbrFill, kViscU, kStepBuf, kNumSlots
 };
 
@@ -309,11 +336,12 @@ template <typename S, typename T>
 sph_status gather_vec3_cvt(sph_ctx* ctx, const sph_nbr* nb, const void* const src[3], T* dst);
 template <typename T>
 sph_status scatter_vec3(sph_ctx* ctx, const sph_nbr* nb, const T* src, void* const dst[3]);
-// Builds the cached matrix; *nnz / *slots (host, optional) receive the
+// Builds the cached matrix, windowed where it is applied more than once
+// (reused) and the windows fit; *nnz / *slots (host, optional) receive the
 // off-diagonal entry count and the stored slot count.
 template <typename T>
 sph_status build_sell(sph_ctx* ctx, const sph_nbr* nb, const PartView& pv, const OpParams& op,
-                      Sell<T>* out, const double** diag64, int64_t* nnz = nullptr,
+                      Sell<T>* out, const double** diag64, bool reused, int64_t* nnz = nullptr,
                       int64_t* slots = nullptr);
 template <typename T>
 sph_status apply_plain(sph_ctx* ctx, const sph_nbr* nb, const PartView& pv, const OpParams& op,

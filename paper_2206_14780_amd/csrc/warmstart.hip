@@ -126,19 +126,31 @@ __device__ inline void zero_row(float* o) {
 template <typename T, typename C>
 __global__ __launch_bounds__(kBlock) void k_warm_feat_sell(FeatArgs<T, C> a, Sell<T> A) {
     __shared__ double lds[3 * kMaxWaves];
+    extern __shared__ __align__(16) unsigned char win_lds[];
+    static_assert(kBlock == kWinRows, "one window per block of rows");
     double acc[3] = {0.0, 0.0, 0.0};
-    for (int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; r < a.n;
-         r += (int64_t)gridDim.x * blockDim.x) {
+    for (int64_t q = blockIdx.x; q * kWinRows < a.n; q += gridDim.x) {
+        const int64_t r = q * kWinRows + threadIdx.x;
+        V3<C> us{};
+        double s0 = 0.0, s1 = 0.0, s2 = 0.0;
+        if (A.wmax > 0) {
+            if (q != blockIdx.x) __syncthreads();
+            WinStream<T, true, C> st(A, min(r / kWave, A.nslices - 1), (int)(r % kWave));
+            if (r < a.n) us = ld3(a.u, r);
+            win_parts(A, q, a.u, win_lds, [&]() __attribute__((always_inline)) { win_row<T, true>(st, win_lds, us, s0, s1, s2); });
+        }
+        if (r >= a.n) continue;
         float* o = sample_row(a, r);
         const bool fluid = a.pv.type[r] == SPH_FLUID;
         if (!fluid) zero_row(o);
         if (!fluid && !a.rplain) continue;
-        const int64_t s = r / kWave;
-        const int64_t base = lane_base<T>(A.sl_ptr[s], r % kWave);
-        const int32_t width = (int32_t)((A.sl_ptr[s + 1] - A.sl_ptr[s]) / kWave);
-        const V3<C> us = ld3(a.u, r);
-        double s0 = 0.0, s1 = 0.0, s2 = 0.0;
-        sell_row<T, true, double, C>(A, base, width, (int32_t)r, a.u, us, s0, s1, s2);
+        if (A.wmax == 0) {
+            const int64_t s = r / kWave;
+            const int64_t base = lane_base<T>(A.sl_ptr[s], r % kWave);
+            const int32_t width = (int32_t)((A.sl_ptr[s + 1] - A.sl_ptr[s]) / kWave);
+            us = ld3(a.u, r);
+            sell_row<T, true, double, C>(A, base, width, (int32_t)r, a.u, us, s0, s1, s2);
+        }
         if (a.rplain) {
             const double rs = A.rs64[r];
             const V3<double> bb = ld3(a.b64, r);
@@ -210,15 +222,24 @@ __global__ __launch_bounds__(kBlock) void k_warm_x0(int64_t n, Rhs<C> rhs, const
 // wall row are its fluid neighbours' normalised kernel values; D = 1 there).
 template <typename T, typename C>
 __global__ __launch_bounds__(kBlock) void k_warm_wall_sell(int64_t n, Rhs<C> rhs, const uint8_t* __restrict__ type,
-                                                           Sell<T> A, T* __restrict__ x) {
+                                                           Sell<T> A, T* x) {
     const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (r >= n || type[r] == SPH_FLUID) return;
-    const int64_t s = r / kWave;
-    const int64_t base = lane_base<T>(A.sl_ptr[s], r % kWave);
-    const int32_t width = (int32_t)((A.sl_ptr[s + 1] - A.sl_ptr[s]) / kWave);
+    extern __shared__ __align__(16) unsigned char win_lds[];
+    const bool wall = r < n && type[r] != SPH_FLUID;
+    if (!__syncthreads_or(wall)) return;
     const V3<T> zero{T(0), T(0), T(0)};
     double s0 = 0.0, s1 = 0.0, s2 = 0.0;
-    sell_row<T, true>(A, base, width, (int32_t)r, x, zero, s0, s1, s2);
+    if (A.wmax > 0) {
+        WinStream<T, true, T> st(A, min(r / kWave, A.nslices - 1), (int)(r % kWave));
+        win_parts(A, (int64_t)blockIdx.x, x, win_lds, [&]() __attribute__((always_inline)) { win_row<T, true>(st, win_lds, zero, s0, s1, s2); });
+    }
+    if (!wall) return;
+    if (A.wmax == 0) {
+        const int64_t s = r / kWave;
+        const int64_t base = lane_base<T>(A.sl_ptr[s], r % kWave);
+        const int32_t width = (int32_t)((A.sl_ptr[s + 1] - A.sl_ptr[s]) / kWave);
+        sell_row<T, true>(A, base, width, (int32_t)r, x, zero, s0, s1, s2);
+    }
     st3(x, r, V3<T>{(T)(rhs.at(r, 0) - s0), (T)(rhs.at(r, 1) - s1), (T)(rhs.at(r, 2) - s2)});
 }
 
@@ -250,8 +271,8 @@ template <typename T, typename C>
 sph_status launch_features(sph_ctx* ctx, const WarmOp<T>& w, const FeatArgs<T, C>& a) {
     const unsigned grid = (unsigned)ceil_div(a.n, kBlock);
     if (w.mode == SPH_OP_CACHED)
-        hipLaunchKernelGGL((k_warm_feat_sell<T, C>), dim3(std::min<unsigned>(grid, kFeatBlocks)), dim3(kBlock), 0,
-                           ctx->stream, a, *w.sell);
+        hipLaunchKernelGGL((k_warm_feat_sell<T, C>), dim3(std::min<unsigned>(grid, kFeatBlocks)), dim3(kBlock),
+                           win_bytes<C>(w.sell->wmax), ctx->stream, a, *w.sell);
     else
         hipLaunchKernelGGL((k_warm_feat_otf<T, C>), dim3(grid), dim3(kBlock), 0, ctx->stream, a, w.nb->view(),
                            w.op.avg);
@@ -393,8 +414,8 @@ sph_status warm_learned(sph_ctx* ctx, const WarmOp<T>& w, const void* const rhs[
                        (const float*)O, (const double*)info, x);
     if (w.op.wall == SPH_WALL_DUMMY) {
         if (w.mode == SPH_OP_CACHED)
-            hipLaunchKernelGGL((k_warm_wall_sell<T, C>), dim3(grid), dim3(kBlock), 0, ctx->stream, n, rb, w.pv.type,
-                               *w.sell, x);
+            hipLaunchKernelGGL((k_warm_wall_sell<T, C>), dim3(grid), dim3(kBlock), win_bytes<T>(w.sell->wmax),
+                               ctx->stream, n, rb, w.pv.type, *w.sell, x);
         else
             hipLaunchKernelGGL((k_warm_wall_otf<T, C>), dim3(grid), dim3(kBlock), 0, ctx->stream, rb, w.nb->view(),
                                w.pv.type, x);
@@ -430,10 +451,10 @@ sph_status prepare(sph_ctx* ctx, const sph_nbr* nb, const sph_particles* p, cons
     w->mode = v->op_mode == SPH_OP_PAPER32 ? SPH_OP_CACHED : v->op_mode;
     w->sell = sell;
     if (w->mode == SPH_OP_CACHED)
-        SPH_TRY(build_sell<T>(ctx, nb, w->pv, w->op, sell, &w->diag64));
+        SPH_TRY(build_sell<T>(ctx, nb, w->pv, w->op, sell, &w->diag64, false));
     else
         SPH_TRY(row_diag64(ctx, nb, w->pv, w->op, &w->diag64));
-    SPH_TRY(ctx->ensure_t(kApplyIn, (size_t)nb->n * 3, ucell));
+    SPH_TRY(ctx->ensure_t(kApplyIn, (size_t)nb->n * 3 + kVecPad, ucell));
     SPH_TRY(gather_vec3<T>(ctx, nb, u, *ucell));
     SPH_TRY(ctx->ensure_t(kWarmInfo, kWiSize, info));
     return SPH_OK;
@@ -459,7 +480,7 @@ sph_status warmstart_entry(sph_ctx* ctx, const sph_nbr* nb, const sph_particles*
     double* info = nullptr;
     SPH_TRY(prepare<T>(ctx, nb, p, v, u, &w, &sell, &ucell, &info));
     T* x = nullptr;
-    SPH_TRY(ctx->ensure_t(kApplyOut, (size_t)nb->n * 3, &x));
+    SPH_TRY(ctx->ensure_t(kApplyOut, (size_t)nb->n * 3 + kVecPad, &x));
     SPH_TRY((warm_learned<T, T>(ctx, w, rhs, ucell, params, x, info, nullptr)));
     SPH_TRY(scatter_vec3<T>(ctx, nb, x, x0));
     if (U) {
