@@ -48,14 +48,8 @@ constexpr int kWaves = 4;             // waves per block
 constexpr int kThreads = kWaves * kWave;
 constexpr int kPad = 65;              // padded row of the per-wave transpose tile
 
-// Orders a wave's own LDS writes before its later LDS reads by other lanes
-// (every tile and output staging area belongs to one wave, so waves of a
-// block never wait for each other after the parameters are loaded).
-__device__ inline void wave_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
+// Every tile and output staging area belongs to one wave (wave_sync), so the
+// waves of a block never wait for each other after the parameters are loaded.
 
 __device__ inline uint16_t f2bf(float f) {  // nearest, ties to even (finite inputs)
     uint32_t u = __float_as_uint(f);

@@ -3,6 +3,7 @@
 // kernels used by sph_visc_apply and the solver.
 #include <algorithm>
 #include <cstdlib>
+#include <type_traits>
 
 #include "operator_kernels.hpp"
 
@@ -255,8 +256,50 @@ __global__ __launch_bounds__(kBlock) void k_row_count(NbrView nv, PartView pv, O
 }
 
 // Slice size = 64 x (most slots of a row of the slice); nnz += entries.
-// Windowed columns (*wmax <= wlim) need no escapes: slots = entries.
+constexpr int kChunk = 16;                    // indices per segment
+constexpr int kListCap = 96;                  // listed neighbours per row, Wendland kernel
+constexpr int kListCapGauss = 288;            // the same, truncated Gaussian
+constexpr size_t kListBudget = size_t(24) << 30;  // bytes of lists and weights at most
+constexpr int kBufStride = kChunk + 1;        // LDS words per lane (odd: no bank conflicts)
+constexpr int kFillGroup = 8;                 // list entries whose gathers are issued together
+static_assert(kListCap % kChunk == 0 && kListCapGauss % kChunk == 0, "whole segments");
+
+__device__ inline int64_t list_base(int64_t r, int32_t cap) {
+    return ((r / kWave) * (cap / kChunk) * kWave + (r % kWave)) * kChunk;
+}
+__device__ inline uint32_t list_off(uint32_t k) {
+    return k / kChunk * (kWave * kChunk) + k % kChunk;
+}
+
+// Row kinds: fluid rows take every neighbour, dummy-wall rows their fluid
+// neighbours, other wall rows none (identity rows).
+enum { kRowNone = 0, kRowFluid = 1, kRowDummy = 2 };
+__device__ inline int row_kind(const PartView& pv, const OpParams& op, int32_t row) {
+    if (pv.type[row] == SPH_FLUID) return kRowFluid;
+    return op.wall == SPH_WALL_DUMMY ? kRowDummy : kRowNone;
+}
+
+// Slots of a delta-coded row, from its list or, beyond cap, from the scan.
+__device__ inline int32_t row_slots(const NbrView& nv, const PartView& pv, const OpParams& op, int32_t row, int32_t c,
+                                    const int32_t* __restrict__ list, int32_t cap) {
+    SlotCounter sc;
+    if (c <= cap) {
+        const int32_t* lst = list + list_base(row, cap);
+        for (int32_t k = 0; k < c; ++k) sc.add(lst[list_off(k)]);
+    } else {
+        const int kind = row_kind(pv, op, row);
+        for_each_neighbor(nv, row, [&](int32_t a, double) {
+            if (kind == kRowFluid || pv.type[a] == SPH_FLUID) sc.add(a);
+        });
+    }
+    return sc.slots;
+}
+
+// Slots per row: cnt, or (null) the entries of windowed columns, which need
+// no escapes (*wmax <= wlim), or those of the delta code, counted here.
 __global__ __launch_bounds__(kBlock) void k_slice_size(int64_t n, int64_t nslices, int32_t pack,
+                                                       NbrView nv, PartView pv, OpParams op,
+                                                       const int32_t* __restrict__ list, int32_t cap,
                                                        const int32_t* __restrict__ wmax, int32_t wlim,
                                                        const int32_t* __restrict__ cnt,
                                                        const int32_t* __restrict__ creal,
@@ -278,7 +321,7 @@ __global__ __launch_bounds__(kBlock) void k_slice_size(int64_t n, int64_t nslice
         int32_t w = 0;
         if (r < n) {
             const int32_t c = creal[r];
-            w = windowed ? c : cnt[r];
+            w = cnt ? cnt[r] : windowed ? c : row_slots(nv, pv, op, (int32_t)r, c, list, cap);
             tot += c;
             longest = max(longest, c);
         }
@@ -304,112 +347,6 @@ __global__ __launch_bounds__(kBlock) void k_slice_size(int64_t n, int64_t nslice
             atomicMax(reinterpret_cast<int32_t*>(nnz + 1), longest);
         }
     }
-}
-
-// The windows of a block of kWinRows rows, one wave per block: the cells of
-// the rows taken x-row by x-row of the cell grid, the neighbouring runs of
-// cells of each as index ranges, sorted and merged where they touch or nearly
-// do.  A block whose window would exceed `limit` takes one per half, or one
-// per slice.  wmax receives the largest window (kWinMax + 1 when a slice's
-// does not fit either).
-__global__ __launch_bounds__(kWave) void k_windows(NbrView nv, int32_t limit, WinRange* __restrict__ win,
-                                                   int32_t* __restrict__ wmax) {
-    constexpr int kGap = 4;     // particles between two ranges that are rather staged
-    constexpr int kRuns = 256;  // runs before merging
-    const Grid& g = nv.g;
-    const int lane = threadIdx.x;
-    const int64_t bid = blockIdx.x;
-    const int32_t nx = g.nc[0], ny = g.nc[1];
-    __shared__ int32_t beg[kRuns], end[kRuns], sb[kRuns], se[kRuns];
-    // ranges of rows [r0, r1] into tab; the window's size, or kWinMax + 1
-    const auto window = [&](int64_t r0, int64_t r1, WinRange* tab, int32_t parts) -> int32_t {
-        const int32_t ca = nv.scell[r0], cb = nv.scell[r1];
-        const int32_t l0 = ca / nx, l1 = cb / nx;  // x-rows of cells
-        if (l1 - l0 >= kRuns / 9) return kWinMax + 1;
-        // tasks: x-row, z and y neighbour, part of the run (middle, wrapped low, wrapped high)
-        const int32_t ntask = (l1 - l0 + 1) * 27;
-        int32_t cnt = 0;
-        for (int32_t t0 = 0; t0 < ntask; t0 += kWave) {
-            const int32_t t = t0 + lane;
-            int32_t b = 0, e = 0;
-            if (t < ntask) {
-                const int32_t l = l0 + t / 27, part = t % 3, iy = (t / 3) % 3, iz = (t / 9) % 3;
-                int32_t zs[3], ys[3];
-                const int nzs = axis_cells(l / ny, g.nc[2], g.per[2], zs);
-                const int nys = axis_cells(l % ny, ny, g.per[1], ys);
-                const int32_t xa = l == l0 ? ca % nx : 0, xe = l == l1 ? cb % nx : nx - 1;
-                int32_t lo = xa > 0 ? xa - 1 : 0, hi = xe < nx - 1 ? xe + 1 : nx - 1;
-                if (g.per[0] && nx < 3) {
-                    lo = 0;
-                    hi = nx - 1;
-                }
-                bool on = iz < nzs && iy < nys;
-                if (part == 1) {
-                    on = on && g.per[0] && nx >= 3 && xa == 0;
-                    lo = hi = nx - 1;
-                } else if (part == 2) {
-                    on = on && g.per[0] && nx >= 3 && xe == nx - 1;
-                    lo = hi = 0;
-                }
-                if (on) {
-                    const int32_t base = (zs[iz] * ny + ys[iy]) * nx;
-                    b = nv.cell_start[base + lo];
-                    e = nv.cell_start[base + hi + 1];
-                }
-            }
-            const uint64_t m = __ballot(e > b);
-            const int32_t at =
-                cnt + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0));
-            cnt += __popcll(m);
-            if (cnt > kRuns) return kWinMax + 1;
-            if (e > b) {
-                beg[at] = b;
-                end[at] = e;
-            }
-        }
-        __syncthreads();
-        for (int32_t k = lane; k < cnt; k += kWave) {
-            int32_t rank = 0;
-            for (int32_t i = 0; i < cnt; ++i) rank += beg[i] < beg[k] || (beg[i] == beg[k] && i < k);
-            sb[rank] = beg[k];
-            se[rank] = end[k];
-        }
-        __syncthreads();
-        int32_t nr = 0, next = 1;  // window index 0 stays free for the unit before the first range
-        if (lane == 0) {
-            for (int32_t i = 0; i < cnt;) {
-                const int32_t b = sb[i];
-                int32_t e = se[i];
-                for (++i; i < cnt && sb[i] <= e + kGap; ++i) e = max(e, se[i]);
-                // base = b modulo 4; a 16-byte unit may reach one 3-vector over either end
-                const int32_t base = next + ((b - next) & 3);
-                if (nr == kWinRanges || (int64_t)base + (e - b) + 3 > kWinMax) {
-                    next = kWinMax;
-                    break;
-                }
-                tab[nr++] = WinRange{b, e - b, base, 0};
-                next = base + (e - b) + 2;
-            }
-            tab[0].head = nr | parts << 16;  // (at least the rows' own cells)
-        }
-        __syncthreads();
-        return __builtin_amdgcn_readfirstlane(next) + 1;
-    };
-    int32_t largest = kWinMax + 1, parts = 1;
-    for (; parts <= kWinParts; parts *= 2) {
-        largest = 0;
-        const int32_t rows = kWinRows / parts;
-        for (int32_t k = 0; k < parts && largest <= limit; ++k) {
-            const int64_t r0 = bid * kWinRows + k * rows;
-            WinRange* tab = win + (bid * kWinParts + k) * kWinRanges;
-            if (r0 < nv.n)
-                largest = max(largest, window(r0, min(r0 + rows, nv.n) - 1, tab, parts));
-            else if (lane == 0)
-                tab[0].head = parts << 16;
-        }
-        if (largest <= limit) break;
-    }
-    if (lane == 0) atomicMax(wmax, largest > limit ? kWinMax + 1 : largest);
 }
 
 // Pass 2: write the slots (coefficients evaluated inside the scan).
@@ -464,81 +401,298 @@ __global__ __launch_bounds__(kBlock) void k_row_fill(NbrView nv, PartView pv, Op
 // ---------------------------------------------------------------------------
 // List-based matrix build (the default).
 //
-// k_row_scan: one thread per row runs the neighbour scan, counts entries and
-//   slots and records the neighbour indices.  The lanes of a wave reach their
-//   k-th neighbour at different points of the scan, so a direct store of each
-//   index would scatter partial cache lines (several times the list size
-//   written to HBM); each lane instead collects kChunk indices in LDS and
-//   writes them as one 64-byte segment.  List layout, with cap entries per
-//   row (cap / kChunk segments): entry k of row r sits at
-//   ((r/64 * cap/kChunk + k/kChunk) * 64 + r%64) * kChunk + k%kChunk.
-// k_row_fill_list: one lane per row of a slice, the lanes walking their
-//   lists in step: the pair weights in list order (= scan order) give the
-//   row sum and the FP64 diagonal and are kept, slot-major (entry k of the
-//   64 rows of a slice written together); a second walk scales them into the
-//   slots, which the lanes also write together.  A row with more than cap
-//   neighbours keeps no list and is rescanned here.  cap is 96 for the
-//   Wendland kernel (~80 neighbours) and 288 for the truncated Gaussian
-//   (~250), unless the lists of a large system would not fit their budget
-//   (then 96, and its rows are all rescanned).
+// k_row_scan: one wave per cell finds the neighbours of the cell's rows, counts
+//   them and writes their indices.  List layout, with cap entries per row
+//   (cap / kChunk segments): entry k of row r sits at
+//   ((r/64 * cap/kChunk + k/kChunk) * 64 + r%64) * kChunk + k%kChunk, so that
+//   a lane walking its row reads 16-byte pieces and a slice's lists lie
+//   together.
+// k_slice_fill: one block per slice evaluates the pair weights in list order
+//   (= scan order), which gives the row sum and the FP64 diagonal, scales them
+//   and writes the slots.
+// k_row_fill_list: the same by one lane per row, for the delta code, the
+//   paper's single precision and matrices with a row beyond the list (such a
+//   row keeps no list and is rescanned here); the weights are kept in memory
+//   between its two walks.
+// cap is 96 for the Wendland kernel (~80 neighbours) and 288 for the truncated
+// Gaussian (~250), unless the lists of a large system would not fit their
+// budget (then 96, and its rows are all rescanned).
 // Same pairs, summation order and coefficients as the scan-order build.
 // ---------------------------------------------------------------------------
-constexpr int kChunk = 16;                    // indices per segment
-constexpr int kListCap = 96;                  // listed neighbours per row, Wendland kernel
-constexpr int kListCapGauss = 288;            // the same, truncated Gaussian
-constexpr size_t kListBudget = size_t(24) << 30;  // bytes of lists and weights at most
-constexpr int kBufStride = kChunk + 1;        // LDS words per lane (odd: no bank conflicts)
-constexpr int kFillGroup = 8;                 // list entries whose gathers are issued together
-static_assert(kListCap % kChunk == 0 && kListCapGauss % kChunk == 0, "whole segments");
+// Largest window (3-vectors) that a block stages at once: 40.1 KB in FP32,
+// four blocks (all that the registers allow) in the 160 KB of LDS; 80.2 KB in
+// FP64, two blocks.  About a fifth of the blocks then take two windows.
+// Operator launch at 33.7M particles, FP32, by limit 1760 / 2250 / 2700 /
+// 3340 / 4400 (three blocks) / 4480 (two): 4.23 / 3.79 / 3.58 / 3.44 / 3.54 /
+// 4.00 ms; FP64 at 328k by 1760 / 2250 / 2700 / 3340 / 4480 (one block): 91 /
+// 80 / 74 / 66 / 81 us.
+constexpr int32_t kWinLimit = 3340;
+static_assert(kWinLimit <= kWinMax, "window offsets fit 16 bits");
 
-__device__ inline int64_t list_base(int64_t r, int32_t cap) {
-    return ((r / kWave) * (cap / kChunk) * kWave + (r % kWave)) * kChunk;
-}
-__device__ inline int64_t list_off(int32_t k) {
-    return (int64_t)(k / kChunk) * (kWave * kChunk) + (k % kChunk);
-}
+constexpr int kWinRuns = 160;  // runs of cells of a window before merging
 
-// Row kinds: fluid rows take every neighbour, dummy-wall rows their fluid
-// neighbours, other wall rows none (identity rows).
-enum { kRowNone = 0, kRowFluid = 1, kRowDummy = 2 };
-__device__ inline int row_kind(const PartView& pv, const OpParams& op, int32_t row) {
-    if (pv.type[row] == SPH_FLUID) return kRowFluid;
-    return op.wall == SPH_WALL_DUMMY ? kRowDummy : kRowNone;
-}
-
-__global__ __launch_bounds__(kBlock) void k_row_scan(NbrView nv, PartView pv, OpParams op,
-                                                     int32_t* __restrict__ cnt, int32_t* __restrict__ creal,
-                                                     int32_t* __restrict__ list, int32_t cap) {
-    __shared__ int32_t buf[kBlock * kBufStride];
-    const int64_t b = (int64_t)xcd_block(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x;
-    if (b >= nv.n) return;  // (each lane uses only its own LDS words)
-    const int32_t row = (int32_t)b;
-    int32_t* my = buf + threadIdx.x * kBufStride;
-    int32_t* out = list + list_base(b, cap);
-    const auto flush = [&](int32_t q) {
-        int4* dst = reinterpret_cast<int4*>(out + (int64_t)q * (kWave * kChunk));
-#pragma unroll
-        for (int i = 0; i < kChunk / 4; ++i)
-            dst[i] = make_int4(my[4 * i], my[4 * i + 1], my[4 * i + 2], my[4 * i + 3]);
+// The windows of a block of kWinRows rows, by one wave: the cells of
+// the rows taken x-row by x-row of the cell grid, the neighbouring runs of
+// cells of each as index ranges, sorted and merged where they touch or nearly
+// do.  A block whose window would exceed `limit` takes one per half, or one
+// per slice.  wmax receives the largest window (kWinMax + 1 when a slice's
+// does not fit either).
+__device__ inline void block_windows(const NbrView& nv, int64_t bid, int32_t limit, WinRange* __restrict__ win,
+                                     int32_t* __restrict__ wmax, int32_t* lds, int lane) {
+    constexpr int kGap = 4;  // particles between two ranges that are rather staged
+    constexpr int kRuns = kWinRuns;
+    const Grid& g = nv.g;
+    const int32_t nx = g.nc[0], ny = g.nc[1];
+    int32_t *beg = lds, *end = lds + kRuns, *sb = lds + 2 * kRuns, *se = lds + 3 * kRuns;
+    // ranges of rows [r0, r1] into tab; the window's size, or kWinMax + 1
+    const auto window = [&](int64_t r0, int64_t r1, WinRange* tab, int32_t parts) -> int32_t {
+        const int32_t ca = nv.scell[r0], cb = nv.scell[r1];
+        const int32_t l0 = ca / nx, l1 = cb / nx;  // x-rows of cells
+        if (l1 - l0 >= kRuns / 9) return kWinMax + 1;
+        // tasks: x-row, z and y neighbour, part of the run (middle, wrapped low, wrapped high)
+        const int32_t ntask = (l1 - l0 + 1) * 27;
+        int32_t cnt = 0;
+        for (int32_t t0 = 0; t0 < ntask; t0 += kWave) {
+            const int32_t t = t0 + lane;
+            int32_t b = 0, e = 0;
+            if (t < ntask) {
+                const int32_t l = l0 + t / 27, part = t % 3, iy = (t / 3) % 3, iz = (t / 9) % 3;
+                int32_t zs[3], ys[3];
+                const int nzs = axis_cells(l / ny, g.nc[2], g.per[2], zs);
+                const int nys = axis_cells(l % ny, ny, g.per[1], ys);
+                const int32_t xa = l == l0 ? ca % nx : 0, xe = l == l1 ? cb % nx : nx - 1;
+                int32_t lo = xa > 0 ? xa - 1 : 0, hi = xe < nx - 1 ? xe + 1 : nx - 1;
+                if (g.per[0] && nx < 3) {
+                    lo = 0;
+                    hi = nx - 1;
+                }
+                bool on = iz < nzs && iy < nys;
+                if (part == 1) {
+                    on = on && g.per[0] && nx >= 3 && xa == 0;
+                    lo = hi = nx - 1;
+                } else if (part == 2) {
+                    on = on && g.per[0] && nx >= 3 && xe == nx - 1;
+                    lo = hi = 0;
+                }
+                if (on) {
+                    const int32_t base = (zs[iz] * ny + ys[iy]) * nx;
+                    b = nv.cell_start[base + lo];
+                    e = nv.cell_start[base + hi + 1];
+                }
+            }
+            const uint64_t m = __ballot(e > b);
+            const int32_t at = cnt + mbcnt64(m);
+            cnt += __popcll(m);
+            if (cnt > kRuns) return kWinMax + 1;
+            if (e > b) {
+                beg[at] = b;
+                end[at] = e;
+            }
+        }
+        wave_sync();
+        for (int32_t k = lane; k < cnt; k += kWave) {
+            int32_t rank = 0;
+            for (int32_t i = 0; i < cnt; ++i) rank += beg[i] < beg[k] || (beg[i] == beg[k] && i < k);
+            sb[rank] = beg[k];
+            se[rank] = end[k];
+        }
+        wave_sync();
+        int32_t nr = 0, next = 1;  // window index 0 stays free for the unit before the first range
+        if (lane == 0) {
+            for (int32_t i = 0; i < cnt;) {
+                const int32_t b = sb[i];
+                int32_t e = se[i];
+                for (++i; i < cnt && sb[i] <= e + kGap; ++i) e = max(e, se[i]);
+                // base = b modulo 4; a 16-byte unit may reach one 3-vector over either end
+                const int32_t base = next + ((b - next) & 3);
+                if (nr == kWinRanges || (int64_t)base + (e - b) + 3 > kWinMax) {
+                    next = kWinMax;
+                    break;
+                }
+                tab[nr++] = WinRange{b, e - b, base, 0};
+                next = base + (e - b) + 2;
+            }
+            tab[0].head = nr | parts << 16;  // (at least the rows' own cells)
+        }
+        wave_sync();
+        return __builtin_amdgcn_readfirstlane(next) + 1;
     };
-    SlotCounter sc;
-    const auto push = [&](int32_t a) {
-        const int32_t e = sc.c % kChunk;
-        my[e] = a;
-        if (e == kChunk - 1 && sc.c < cap) flush(sc.c / kChunk);
-        sc.add(a);
-    };
-    const int kind = row_kind(pv, op, row);
-    if (kind == kRowFluid) {
-        for_each_neighbor(nv, row, [&](int32_t a, double) { push(a); });
-    } else if (kind == kRowDummy) {
-        for_each_neighbor(nv, row, [&](int32_t a, double) {
-            if (pv.type[a] == SPH_FLUID) push(a);
-        });
+    int32_t largest = kWinMax + 1, parts = 1;
+    for (; parts <= kWinParts; parts *= 2) {
+        largest = 0;
+        const int32_t rows = kWinRows / parts;
+        for (int32_t k = 0; k < parts && largest <= limit; ++k) {
+            const int64_t r0 = bid * kWinRows + k * rows;
+            WinRange* tab = win + (bid * kWinParts + k) * kWinRanges;
+            if (r0 < nv.n)
+                largest = max(largest, window(r0, min(r0 + rows, nv.n) - 1, tab, parts));
+            else if (lane == 0)
+                tab[0].head = parts << 16;
+        }
+        if (largest <= limit) break;
     }
-    if (sc.c <= cap && sc.c % kChunk) flush(sc.c / kChunk);
-    cnt[row] = sc.slots;
-    creal[row] = sc.c;
+    if (lane == 0) atomicMax(wmax, largest > limit ? kWinMax + 1 : largest);
+}
+
+// One wave per cell: the cell's rows share their neighbour candidates, which
+// the lanes hold in registers (kScanRounds rounds of 64 at a time, taken from
+// the runs of cells around the cell laid end to end); every row is tested
+// against each round at once and its neighbours are appended in ascending
+// order by their rank in the ballot.  Against one thread per row walking its
+// candidates one after the other this loads each candidate once per cell
+// instead of once per row, and has no serial chain of loads.  A cell's rows
+// are dealt to `split` waves where the grid alone would leave the chip idle.
+// The first blocks of the launch compute the operator's windows instead
+// (win_blocks, 0 for none): their latency hides behind the scan.
+constexpr int kScanRounds = 8;
+constexpr int kScanBatch = kScanRounds * kWave;
+
+__global__ __launch_bounds__(kBlock) void k_row_scan(NbrView nv, PartView pv, OpParams op, int64_t ncell,
+                                                     int32_t split, int32_t* creal, int32_t* __restrict__ list,
+                                                     int32_t cap, int32_t win_blocks, WinRange* __restrict__ win,
+                                                     int32_t* __restrict__ wmax) {
+    constexpr int kW = kBlock / kWave;
+    __shared__ int32_t cand_lds[kW][kScanBatch > 4 * kWinRuns ? kScanBatch : 4 * kWinRuns];
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    if ((int32_t)blockIdx.x < win_blocks) {
+        const int64_t b = (int64_t)blockIdx.x * kW + wid;
+        if (b * kWinRows < nv.n) block_windows(nv, b, kWinLimit, win, wmax, cand_lds[wid], lane);
+        return;
+    }
+    const int64_t w64 = (int64_t)xcd_block(blockIdx.x - win_blocks, gridDim.x - win_blocks) * kW + wid;
+    if (w64 >= ncell * split) return;
+    const int32_t c = (int32_t)(w64 / split), share = (int32_t)(w64 % split);
+    const int32_t rb = nv.cell_start[c], re = nv.cell_start[c + 1];
+    if (rb >= re) return;
+    const Grid& g = nv.g;
+    int32_t* cand = cand_lds[wid];
+    // the runs of cells around the cell, one per lane, in ascending order, and
+    // their places in the sequence of candidates
+    int32_t beg = 0, len = 0;
+    if (lane < 27) {
+        const int32_t nx = g.nc[0], ny = g.nc[1];
+        const int32_t cx = c % nx, l = c / nx;
+        const int32_t part = lane % 3, iy = (lane / 3) % 3, iz = lane / 9;
+        int32_t zs[3], ys[3];
+        const int nzs = axis_cells(l / ny, g.nc[2], g.per[2], zs);
+        const int nys = axis_cells(l % ny, ny, g.per[1], ys);
+        const bool wraps = g.per[0] && nx >= 3;
+        int32_t lo = cx > 0 ? cx - 1 : 0, hi = cx < nx - 1 ? cx + 1 : nx - 1;
+        if (g.per[0] && nx < 3) {
+            lo = 0;
+            hi = nx - 1;
+        }
+        bool on = iz < nzs && iy < nys;
+        if (part == 0) {  // the first cell, from the last one
+            on = on && wraps && cx == nx - 1;
+            lo = hi = 0;
+        } else if (part == 2) {  // the last cell, from the first one
+            on = on && wraps && cx == 0;
+            lo = hi = nx - 1;
+        }
+        if (on) {
+            const int32_t base = (zs[iz] * ny + ys[iy]) * nx;
+            beg = nv.cell_start[base + lo];
+            len = nv.cell_start[base + hi + 1] - beg;
+        }
+    }
+    int32_t pre = len;
+#pragma unroll
+    for (int o = 1; o < 32; o <<= 1) {
+        const int32_t v = __shfl_up(pre, o, kWave);
+        if (lane >= o) pre += v;
+    }
+    const int32_t total = __builtin_amdgcn_readlane(pre, 26);
+    pre -= len;
+    for (int32_t b0 = 0; b0 < total; b0 += kScanBatch) {
+        uint64_t runs = __ballot(len > 0 && pre < b0 + kScanBatch && pre + len > b0);
+        while (runs) {
+            const int t = __builtin_ctzll(runs);
+            runs &= runs - 1;
+            const int32_t B = __builtin_amdgcn_readlane(beg, t), L = __builtin_amdgcn_readlane(len, t);
+            const int32_t P = __builtin_amdgcn_readlane(pre, t) - b0;
+            const int32_t j1 = min(L, kScanBatch - P);
+            for (int32_t j = max(0, -P) + lane; j < j1; j += kWave) cand[P + j] = B + j;
+        }
+        wave_sync();
+        const int32_t nc = min(total - b0, kScanBatch);
+        int32_t a[kScanRounds];
+        double ax[kScanRounds], ay[kScanRounds], az[kScanRounds];
+        uint64_t fluid[kScanRounds];  // the fluid candidates of a round
+        bool far = false;
+        const Pos4 ref = nv.pos[rb];
+#pragma unroll
+        for (int q = 0; q < kScanRounds; ++q) {
+            const bool ok = q * kWave + lane < nc;
+            a[q] = ok ? cand[q * kWave + lane] : rb;
+            const Pos4* s = nv.pos + a[q];
+            // a lane without a candidate never passes the distance test
+            ax[q] = ok ? s->x : __builtin_nan("");
+            ay[q] = s->y;
+            az[q] = s->z;
+            fluid[q] = __ballot(pv.type[a[q]] == SPH_FLUID);
+            far = far || (ok && ((g.period[0] > 0.0 && !(fabs(ref.x - ax[q]) <= 0.24 * g.period[0])) ||
+                                 (g.period[1] > 0.0 && !(fabs(ref.y - ay[q]) <= 0.24 * g.period[1])) ||
+                                 (g.period[2] > 0.0 && !(fabs(ref.z - az[q]) <= 0.24 * g.period[2]))));
+        }
+        wave_sync();
+        // All candidates (the cell's rows among them, so far as they fit one
+        // batch) within a quarter of the period of one of the rows: every
+        // displacement is below half a period and the minimum image is the
+        // plain difference.
+        const bool image = __any(far) || total > kScanBatch;
+        for (int32_t g0 = rb; g0 < re; g0 += kWave) {
+            // the rows, one per lane
+            const int32_t row = g0 + lane;
+            const bool on = row < re;
+            Pos4 pb{};
+            int kind = kRowNone;
+            int32_t mine = 0;  // neighbours so far
+            if (on) {
+                pb = nv.pos[row];
+                kind = row_kind(pv, op, row);
+                if (b0 > 0) mine = creal[row];
+            }
+            const int32_t nrow = min(re - g0, kWave);
+            for (int32_t i = share; i < nrow; i += split) {  // (split divides the wave's 64 rows)
+                const int kd = __builtin_amdgcn_readlane(kind, i);
+                if (kd == kRowNone) continue;
+                const double xb = read_lane(pb.x, i), yb = read_lane(pb.y, i), zb = read_lane(pb.z, i);
+                const int32_t ri = g0 + i;
+                int32_t cnt = __builtin_amdgcn_readlane(mine, i);
+                int32_t* out = list + list_base(ri, cap);  // (uniform: a scalar base)
+                const auto tests = [&](auto img, auto all) {
+#pragma unroll
+                    for (int q = 0; q < kScanRounds; ++q) {
+                        if (q * kWave >= nc) break;
+                        double dx = xb - ax[q], dy = yb - ay[q], dz = zb - az[q];
+                        if constexpr (decltype(img)::value) {
+                            dx = disp(xb, ax[q], g.period[0]);
+                            dy = disp(yb, ay[q], g.period[1]);
+                            dz = disp(zb, az[q], g.period[2]);
+                        }
+                        const double r2 = (dx * dx + dy * dy) + dz * dz;
+                        uint64_t m = __ballot(r2 < g.cut2) & __ballot(a[q] != ri);
+                        if constexpr (!decltype(all)::value) m &= fluid[q];
+                        const uint32_t k = (uint32_t)(cnt + mbcnt64(m));
+                        cnt = __builtin_amdgcn_readfirstlane(cnt + __popcll(m));
+                        if (cnt > cap) m &= __ballot((int32_t)k < cap);
+                        if (__builtin_amdgcn_inverse_ballot_w64(m)) out[list_off(k)] = a[q];
+                    }
+                };
+                if (image) {
+                    if (kd == kRowFluid) tests(std::true_type{}, std::true_type{});
+                    else tests(std::true_type{}, std::false_type{});
+                } else {
+                    if (kd == kRowFluid) tests(std::false_type{}, std::true_type{});
+                    else tests(std::false_type{}, std::false_type{});
+                }
+                if (lane == i) mine = cnt;
+            }
+            if (on && lane % split == share) creal[row] = mine;
+        }
+    }
 }
 
 template <typename T, bool WIN>
@@ -711,6 +865,146 @@ __global__ __launch_bounds__(kBlock) void k_row_fill_list(NbrView nv, PartView p
     }
 }
 
+// The fill of a windowed FP64-evaluated matrix whose rows are all listed: one
+// block per slice, lane = row, the four waves sharing the rows' entries in
+// blocks of 8 (wave w takes entries 32 t + 8 w + 0..7): weights first, kept in
+// registers and laid out in LDS in list order, where every wave adds them up
+// one after the other (the same sum as one thread's); then each wave scales
+// its own weights and writes their slots, whole packs of the slice at a time.
+// Against one lane per row for the whole row this has a quarter of the serial
+// work per wave and no weights in memory.
+template <typename T, int CAP, int W>
+__global__ __launch_bounds__(W* kWave) __attribute__((amdgpu_waves_per_eu(2))) void k_slice_fill(NbrView nv, PartView pv, OpParams op, int64_t nslices,
+                                                       const int32_t* __restrict__ creal,
+                                                       const int32_t* __restrict__ list,
+                                                       const int64_t* __restrict__ sl_ptr, T* __restrict__ coef,
+                                                       uint16_t* __restrict__ dcol, float* __restrict__ lo,
+                                                       T* __restrict__ dg, double* __restrict__ rs64,
+                                                       double* __restrict__ diag64, const WinRange* __restrict__ win) {
+    constexpr int kW = W;
+    constexpr int E = 8;                              // entries of a wave per round
+    constexpr int R = (CAP + E * kW - 1) / (E * kW);  // rounds
+    constexpr int P = pack_of<T>();
+    static_assert(CAP % E == 0 && kChunk % E == 0 && E % P == 0, "whole groups");
+    __shared__ double buf[2][E * kW][kWave];
+    __shared__ WinRange tab[kWinRanges];
+    const int64_t s = xcd_block(blockIdx.x, gridDim.x);
+    if (s >= nslices) return;
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int64_t r = s * kWave + lane;
+    const Grid& g = nv.g;
+    {  // the window that serves the slice
+        const int64_t blk = s / (kWinRows / kWave);
+        const int32_t np = win[blk * kWinParts * kWinRanges].head >> 16;
+        const int32_t part = (int32_t)(s % (kWinRows / kWave)) * np / (kWinRows / kWave);
+        if (threadIdx.x < kWinRanges) tab[threadIdx.x] = win[(blk * kWinParts + part) * kWinRanges + threadIdx.x];
+    }
+    const bool valid = r < nv.n;
+    const int32_t row = (int32_t)(valid ? r : s * kWave);  // lanes beyond the last row pad with the slice's first
+    const int kind = valid ? row_kind(pv, op, row) : kRowNone;
+    const int32_t c = kind != kRowNone ? creal[row] : 0;
+    const int32_t width = (int32_t)((sl_ptr[s + 1] - sl_ptr[s]) / kWave);
+    const int32_t* lst = list + list_base(s * kWave + lane, CAP);
+    const Pos4 pb = nv.pos[row];
+    const double mu_b = pv.mu[row], ir_b = pv.inv_rho[row];
+    double w[R][E];
+    int32_t a[R][E];
+    double sum = 0.0;
+#pragma unroll
+    for (int t = 0; t < R; ++t) {
+        const int32_t k0 = t * E * kW + wid * E;
+#pragma unroll
+        for (int u = 0; u < E; ++u) a[t][u] = k0 + u < c ? lst[list_off(k0 + u)] : row;
+    }
+#pragma unroll
+    for (int t = 0; t < R; ++t) {
+        if (t * E * kW >= width) break;
+        const int32_t k0 = t * E * kW + wid * E;
+        Pos4 pa[E];
+        double2 ma[E];
+#pragma unroll
+        for (int u = 0; u < E; ++u) pa[u] = nv.pos[a[t][u]];
+#pragma unroll
+        for (int u = 0; u < E; ++u) ma[u] = pv.mu_mr[a[t][u]];
+#pragma unroll
+        for (int u = 0; u < E; ++u) {
+            // r^2 exactly as the scan computes it
+            const double dx = disp(pb.x, pa[u].x, g.period[0]);
+            const double dy = disp(pb.y, pa[u].y, g.period[1]);
+            const double dz = disp(pb.z, pa[u].z, g.period[2]);
+            const double r2 = (dx * dx + dy * dy) + dz * dz;
+            double v = 0.0;  // (adding 0 to the sum of a shorter row changes nothing)
+            if (k0 + u < c)
+                v = kind != kRowFluid ? pair_W(g, r2) : pair_w_v(g, op.avg, ma[u].x, ma[u].y, mu_b, ir_b, r2);
+            w[t][u] = v;
+            buf[t & 1][wid * E + u][lane] = v;
+        }
+        __syncthreads();  // (the other buffer is read in the next round only after its own barrier)
+#pragma unroll
+        for (int u = 0; u < E * kW; ++u) sum += buf[t & 1][u][lane];
+    }
+    if (width == 0) __syncthreads();  // (tab)
+    const double D = kind == kRowFluid ? 1.0 + op.dt * sum : 1.0;
+    const bool identity = kind == kRowNone || (kind == kRowDummy && !(sum > 0.0));
+    const int64_t base = lane_base<T>(sl_ptr[s], lane);
+    // the range of the last column coded: its end, and base - beg
+    int32_t q = -1, q_end = 0, q_off = 0;
+    const auto code = [&](int32_t col) {
+        while (col >= q_end) {
+            const WinRange x = tab[++q];
+            q_end = x.beg + x.len;
+            q_off = x.base - x.beg;
+        }
+        return (uint16_t)((col + q_off) * kWinStep);
+    };
+    const uint16_t own = code(row);
+    q = -1;
+    q_end = 0;
+#pragma unroll
+    for (int t = 0; t < R; ++t) {
+        if (t * E * kW >= width) break;
+        const int32_t k0 = t * E * kW + wid * E;
+#pragma unroll
+        for (int e = 0; e < E / P; ++e) {
+            if (k0 + e * P >= width) break;
+            typename Pack<T, P>::v cv;
+            typename Pack<uint16_t, P>::v dv;
+            typename Pack<float, P>::v lv;
+#pragma unroll
+            for (int u = 0; u < P; ++u) {
+                const int32_t k = k0 + e * P + u;
+                const bool on = k < c && !identity;
+                double v = 0.0;
+                if (on) {
+                    if (kind == kRowFluid) {
+                        const double aba = -op.dt * w[t][e * P + u];
+                        v = op.jacobi ? aba / D : aba;
+                    } else {
+                        v = w[t][e * P + u] / sum;
+                    }
+                }
+                cv[u] = (T)v;
+                dv[u] = on ? code(a[t][e * P + u]) : own;
+                if constexpr (sizeof(T) == 4) lv[u] = (float)(v - (double)cv[u]);
+            }
+            const int64_t i = slot_of<T>(base, k0 + e * P);
+            *reinterpret_cast<typename Pack<T, P>::v*>(coef + i) = cv;
+            *reinterpret_cast<typename Pack<uint16_t, P>::v*>(dcol + i) = dv;
+            if constexpr (sizeof(T) == 4) *reinterpret_cast<typename Pack<float, P>::v*>(lo + i) = lv;
+        }
+    }
+    if (valid && wid == 0) {
+        // row sums: 1/A_rr (Jacobi) or 1 on fluid rows (eqs. diag, offdiag),
+        // 2 on dummy rows with fluid neighbours (eq. implicit-system-dummy-full),
+        // 1 on identity rows
+        const double rs = kind == kRowFluid ? (op.jacobi ? 1.0 / D : 1.0) : (identity || c == 0 ? 1.0 : 2.0);
+        dg[row] = (T)rs;
+        rs64[row] = rs;
+        diag64[row] = D;
+    }
+}
+
 sph_status row_diag64(sph_ctx* ctx, const sph_nbr* nb, const PartView& pv, const OpParams& op,
                       const double** diag64) {
     double* d = nullptr;
@@ -722,19 +1016,9 @@ sph_status row_diag64(sph_ctx* ctx, const sph_nbr* nb, const PartView& pv, const
     return SPH_OK;
 }
 
-// Largest window (3-vectors) that a block stages at once: 40.1 KB in FP32,
-// four blocks (all that the registers allow) in the 160 KB of LDS; 80.2 KB in
-// FP64, two blocks.  About a fifth of the blocks then take two windows.
-// Operator launch at 33.7M particles, FP32, by limit 1760 / 2250 / 2700 /
-// 3340 / 4400 (three blocks) / 4480 (two): 4.23 / 3.79 / 3.58 / 3.44 / 3.54 /
-// 4.00 ms; FP64 at 328k by 1760 / 2250 / 2700 / 3340 / 4480 (one block): 91 /
-// 80 / 74 / 66 / 81 us.
-constexpr int32_t kWinLimit = 3340;
-static_assert(kWinLimit <= kWinMax, "window offsets fit 16 bits");
-
 template <typename T>
 sph_status build_sell(sph_ctx* ctx, const sph_nbr* nb, const PartView& pv, const OpParams& op, Sell<T>* out,
-                      const double** diag64, bool reused, int64_t* nnz_out, int64_t* slots_out) {
+                      const double** diag64, int64_t* nnz_out, int64_t* slots_out) {
     const int64_t n = nb->n;
     const int64_t nslices = ceil_div(n, kWave);
     // Test hook: the environment variable SPH_BUILD_LEGACY=1 selects the
@@ -743,10 +1027,7 @@ sph_status build_sell(sph_ctx* ctx, const sph_nbr* nb, const PartView& pv, const
     if (op.f32cell && nb->g.kernel != SPH_KERNEL_WENDLAND)
         return ctx->fail(SPH_E_ARG, "SPH_OP_PAPER32 is defined for the Wendland kernel");
     const bool legacy = env_int("SPH_BUILD_LEGACY", 0) > 0 && !op.f32cell;
-    // The windows cost one latency-bound launch (21 us on 5,632 particles, 46
-    // on 187k with the Gaussian kernel) and save 5 to 30 us per operator pass:
-    // a matrix that is applied once keeps the delta code.
-    const bool windows = reused && !legacy;
+    const bool windows = !legacy;
     // list entries per row: room for every neighbour of the kernel's support
     // (int32 index + FP64 weight each) while that fits the budget
     const int32_t cap = nb->g.kernel == SPH_KERNEL_GAUSSIAN &&
@@ -756,7 +1037,6 @@ sph_status build_sell(sph_ctx* ctx, const sph_nbr* nb, const PartView& pv, const
     int32_t *cnt = nullptr, *creal = nullptr, *list = nullptr;
     double *d = nullptr, *ws = nullptr, *wlist = nullptr;
     int64_t *size = nullptr, *ptr = nullptr;
-    SPH_TRY(ctx->ensure_t(kCnt, n, &cnt));
     SPH_TRY(ctx->ensure_t(kCntReal, n, &creal));
     SPH_TRY(ctx->ensure_t(kDiag64, n, &d));
     SPH_TRY(ctx->ensure_t(kSlSize, nslices, &size));
@@ -764,31 +1044,33 @@ sph_status build_sell(sph_ctx* ctx, const sph_nbr* nb, const PartView& pv, const
     unsigned long long* nnz_dev = nullptr;  // [0] nonzeros, [1] longest row, [2] largest window
     SPH_TRY(ctx->ensure_t(kNnzCount, 3, &nnz_dev));
     SPH_HIP(hipMemsetAsync(nnz_dev, 0, 3 * sizeof(unsigned long long), ctx->stream));
-    // row kernels: whole XCD rounds of blocks (xcd_block needs a multiple of 8)
     // windows of the operator's blocks; [2] of the counters: the largest
     WinRange* win = nullptr;
-    const int64_t nwb = ceil_div(n, (int64_t)kWinRows);
-    if (windows) {
-        SPH_TRY(ctx->ensure_t(kWin, (size_t)nwb * kWinParts * kWinRanges, &win));
-        hipLaunchKernelGGL(k_windows, dim3((unsigned)nwb), dim3(kWave), 0, ctx->stream, nb->view(), kWinLimit, win,
-                           reinterpret_cast<int32_t*>(nnz_dev + 2));
-        SPH_LAUNCHED("k_windows");
-    }
-    const dim3 rows_grid((unsigned)(ceil_div(ceil_div(n, kBlock), kNumXcd) * kNumXcd));
+    if (windows)
+        SPH_TRY(ctx->ensure_t(kWin, (size_t)ceil_div(n, (int64_t)kWinRows) * kWinParts * kWinRanges, &win));
+    // slice kernels: whole XCD rounds of blocks (xcd_block needs a multiple of 8)
     const dim3 slice_grid((unsigned)(ceil_div(ceil_div(nslices * kWave, kBlock), kNumXcd) * kNumXcd));
     if (legacy) {
+        SPH_TRY(ctx->ensure_t(kCnt, n, &cnt));
         SPH_TRY(ctx->ensure_t(kWsum, n, &ws));
         hipLaunchKernelGGL(k_row_count, dim3((unsigned)ceil_div(n, kBlock)), dim3(kBlock), 0, ctx->stream,
                            nb->view(), pv, op, cnt, creal, d, ws);
     } else {
         SPH_TRY(ctx->ensure_t(kList, (size_t)nslices * cap * kWave, &list));
         SPH_TRY(ctx->ensure_t(kWList, (size_t)nslices * cap * kWave, &wlist));
-        hipLaunchKernelGGL(k_row_scan, rows_grid, dim3(kBlock), 0, ctx->stream, nb->view(), pv, op, cnt, creal,
-                           list, cap);
+        constexpr int64_t kW = kBlock / kWave;
+        const int64_t wblk = windows ? ceil_div(ceil_div(n, (int64_t)kWinRows), kW) : 0;
+        // four waves per SIMD (what the scan's registers allow) on every CU
+        int32_t split = 1;
+        while (split < 8 && nb->ncell * split < 4096) split *= 2;
+        const int64_t sblk = ceil_div(ceil_div(nb->ncell * split, kW), (int64_t)kNumXcd) * kNumXcd;
+        hipLaunchKernelGGL(k_row_scan, dim3((unsigned)(wblk + sblk)), dim3(kBlock), 0, ctx->stream, nb->view(), pv, op,
+                           nb->ncell, split, creal, list, cap, (int32_t)wblk, win, reinterpret_cast<int32_t*>(nnz_dev + 2));
     }
     hipLaunchKernelGGL(k_slice_size, dim3((unsigned)std::min<int64_t>(ceil_div(nslices * kWave, kBlock), 1024)),
                        dim3(kBlock), 0, ctx->stream,
-                       n, nslices, (int32_t)pack_of<T>(), reinterpret_cast<const int32_t*>(nnz_dev + 2),
+                       n, nslices, (int32_t)pack_of<T>(), nb->view(), pv, op, (const int32_t*)list, cap,
+                       reinterpret_cast<const int32_t*>(nnz_dev + 2),
                        windows ? kWinLimit : -1, cnt, creal, size, nnz_dev);
     SPH_LAUNCHED("k_row_count/k_slice_size");
     SPH_TRY(scan_i64(ctx, size, ptr, nslices));
@@ -822,7 +1104,15 @@ sph_status build_sell(sph_ctx* ctx, const sph_nbr* nb, const PartView& pv, const
         // flight on an XCD then fit its L2 (with eight blocks per CU they
         // did not): 8.1 -> 5.8 ms at 4.49M particles.
         constexpr size_t kFillLdsReserve = 60 * 1024;
-        if (windowed)
+        const bool listed = (int64_t)(uint32_t)hcnt[1] <= cap;  // (the longest row)
+        const dim3 wave_grid((unsigned)(ceil_div(nslices, kNumXcd) * kNumXcd));
+        if (windowed && listed && !op.f32cell && cap == kListCap)
+            hipLaunchKernelGGL((k_slice_fill<T, kListCap, 4>), wave_grid, dim3(4 * kWave), 0, ctx->stream, nb->view(), pv, op,
+                               nslices, creal, list, ptr, coef, dcol, lo, dg, rs64, d, win);
+        else if (windowed && listed && !op.f32cell)
+            hipLaunchKernelGGL((k_slice_fill<T, kListCapGauss, 8>), wave_grid, dim3(8 * kWave), 0, ctx->stream,
+                               nb->view(), pv, op, nslices, creal, list, ptr, coef, dcol, lo, dg, rs64, d, win);
+        else if (windowed)
             hipLaunchKernelGGL((k_row_fill_list<T, true>), slice_grid, dim3(kBlock), kFillLdsReserve, ctx->stream,
                                nb->view(), pv, op, nslices, creal, list, wlist, ptr, coef, dcol, lo, c0, dg, rs64, d,
                                cap, *out);
@@ -849,9 +1139,9 @@ sph_status build_sell(sph_ctx* ctx, const sph_nbr* nb, const PartView& pv, const
 }
 
 template sph_status build_sell<float>(sph_ctx*, const sph_nbr*, const PartView&, const OpParams&, Sell<float>*,
-                                      const double**, bool, int64_t*, int64_t*);
+                                      const double**, int64_t*, int64_t*);
 template sph_status build_sell<double>(sph_ctx*, const sph_nbr*, const PartView&, const OpParams&,
-                                       Sell<double>*, const double**, bool, int64_t*, int64_t*);
+                                       Sell<double>*, const double**, int64_t*, int64_t*);
 
 
 // Launch geometry of the row kernels.
@@ -945,7 +1235,7 @@ static sph_status apply_entry(sph_ctx* ctx, const sph_nbr* nb, const sph_particl
     SPH_TRY(gather_vec3<T>(ctx, nb, x, xin));
     Sell<T> sell{};
     if (v->op_mode == SPH_OP_PAPER32) op.f32cell = 1;
-    if (v->op_mode != SPH_OP_ONTHEFLY) SPH_TRY(build_sell<T>(ctx, nb, pv, op, &sell, nullptr, false));
+    if (v->op_mode != SPH_OP_ONTHEFLY) SPH_TRY(build_sell<T>(ctx, nb, pv, op, &sell, nullptr));
     SPH_TRY(apply_plain<T>(ctx, nb, pv, op, v->op_mode, &sell, xin, yout));
     SPH_TRY(scatter_vec3<T>(ctx, nb, yout, y));
     return SPH_OK;

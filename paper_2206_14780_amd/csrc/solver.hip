@@ -803,8 +803,8 @@ sph_status solve_impl(sph_ctx* ctx, const sph_nbr* nb, const sph_particles* part
     ++S.launches;
     S.profile = std::max(o->profile, 0);
     if (S.mode == SPH_OP_CACHED) {
-        SPH_TRY(build_sell<T>(ctx, nb, S.pv, S.op, &S.sell, &S.diag64, true, &rep->mat_nnz, &rep->mat_slots));
-        S.launches += 7;
+        SPH_TRY(build_sell<T>(ctx, nb, S.pv, S.op, &S.sell, &S.diag64, &rep->mat_nnz, &rep->mat_slots));
+        S.launches += 6;
     } else {
         SPH_TRY(row_diag64(ctx, nb, S.pv, S.op, &S.diag64));
         ++S.launches;

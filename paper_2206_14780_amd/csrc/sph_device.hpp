@@ -296,6 +296,17 @@ __device__ inline double wave_sum(double v) {
     return (read_lane(v, 15) + read_lane(v, 31)) + (read_lane(v, 47) + read_lane(v, 63));
 }
 
+// Set bits of a ballot below this lane.
+__device__ inline int32_t mbcnt64(uint64_t m) {
+    return (int32_t)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0));
+}
+// Orders a wave's own LDS writes before its later LDS reads by other lanes.
+__device__ inline void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // Block-wide sum of K values per thread; result valid in every thread.
 // `lds` must hold K * kMaxWaves doubles.
 template <int K>

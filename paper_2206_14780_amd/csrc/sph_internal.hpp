@@ -93,8 +93,7 @@ struct OpParams {
 //     column (a byte offset into the window of FP32 3-vectors that the
 //     operator stages in LDS).  Rows shorter than their slice are padded with
 //     (own row, coef 0).
-//   delta coded (wmax = 0; a matrix for one product, or a system with a
-//     window too large to stage): the row
+//   delta coded (wmax = 0; a system with a window too large to stage): the row
 //     starts at column c0[r] and each slot adds its 16-bit step dcol (the
 //     first entry steps by 0).  A step that does not fit takes an escape slot
 //     (dcol = kEscape) whose coefficient bits hold the whole jump and which
@@ -336,12 +335,11 @@ template <typename S, typename T>
 sph_status gather_vec3_cvt(sph_ctx* ctx, const sph_nbr* nb, const void* const src[3], T* dst);
 template <typename T>
 sph_status scatter_vec3(sph_ctx* ctx, const sph_nbr* nb, const T* src, void* const dst[3]);
-// Builds the cached matrix, windowed where it is applied more than once
-// (reused) and the windows fit; *nnz / *slots (host, optional) receive the
+// Builds the cached matrix, windowed where the windows fit; *nnz / *slots (host, optional) receive the
 // off-diagonal entry count and the stored slot count.
 template <typename T>
 sph_status build_sell(sph_ctx* ctx, const sph_nbr* nb, const PartView& pv, const OpParams& op,
-                      Sell<T>* out, const double** diag64, bool reused, int64_t* nnz = nullptr,
+                      Sell<T>* out, const double** diag64, int64_t* nnz = nullptr,
                       int64_t* slots = nullptr);
 template <typename T>
 sph_status apply_plain(sph_ctx* ctx, const sph_nbr* nb, const PartView& pv, const OpParams& op,

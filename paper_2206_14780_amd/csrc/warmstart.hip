@@ -451,7 +451,7 @@ sph_status prepare(sph_ctx* ctx, const sph_nbr* nb, const sph_particles* p, cons
     w->mode = v->op_mode == SPH_OP_PAPER32 ? SPH_OP_CACHED : v->op_mode;
     w->sell = sell;
     if (w->mode == SPH_OP_CACHED)
-        SPH_TRY(build_sell<T>(ctx, nb, w->pv, w->op, sell, &w->diag64, false));
+        SPH_TRY(build_sell<T>(ctx, nb, w->pv, w->op, sell, &w->diag64));
     else
         SPH_TRY(row_diag64(ctx, nb, w->pv, w->op, &w->diag64));
     SPH_TRY(ctx->ensure_t(kApplyIn, (size_t)nb->n * 3 + kVecPad, ucell));
