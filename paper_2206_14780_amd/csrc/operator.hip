@@ -541,7 +541,11 @@ __device__ inline void block_windows(const NbrView& nv, int64_t bid, int32_t lim
 // order by their rank in the ballot.  Against one thread per row walking its
 // candidates one after the other this loads each candidate once per cell
 // instead of once per row, and has no serial chain of loads.  A cell's rows
-// are dealt to `split` waves where the grid alone would leave the chip idle.
+// are dealt to `split` waves where the grid alone would leave the chip idle.  What
+// bounds it is instruction issue: 8 rounds a row of about 31 instructions, 19
+// of them vector.  298 -> 22 us at 5,632 particles, 1.08 -> 0.55 ms at 1.16M
+// (windows included), 24.1 -> 16.1 ms at 33.7M, 1.28 -> 0.48 ms at 187k with
+// the Gaussian kernel.
 // The first blocks of the launch compute the operator's windows instead
 // (win_blocks, 0 for none): their latency hides behind the scan.
 constexpr int kScanRounds = 8;
@@ -872,7 +876,11 @@ __global__ __launch_bounds__(kBlock) void k_row_fill_list(NbrView nv, PartView p
 // one after the other (the same sum as one thread's); then each wave scales
 // its own weights and writes their slots, whole packs of the slice at a time.
 // Against one lane per row for the whole row this has a quarter of the serial
-// work per wave and no weights in memory.
+// work per wave and no weights in memory: 80 -> 26 us at 5,632 particles, 1.33
+// -> 0.83 ms at 1.16M, 38.9 -> 25.4 ms at 33.7M, 821 -> 630 us at 187k with the
+// Gaussian kernel (whose longer rows take eight waves).  What bounds it is the
+// L1 look-ups of its gathers, three 16-byte pieces per entry and lane; three
+// waves per SIMD (168 registers, spills) were slower, 29.0 ms.
 template <typename T, int CAP, int W>
 __global__ __launch_bounds__(W* kWave) __attribute__((amdgpu_waves_per_eu(2))) void k_slice_fill(NbrView nv, PartView pv, OpParams op, int64_t nslices,
                                                        const int32_t* __restrict__ creal,
@@ -1057,7 +1065,6 @@ sph_status build_sell(sph_ctx* ctx, const sph_nbr* nb, const PartView& pv, const
                            nb->view(), pv, op, cnt, creal, d, ws);
     } else {
         SPH_TRY(ctx->ensure_t(kList, (size_t)nslices * cap * kWave, &list));
-        SPH_TRY(ctx->ensure_t(kWList, (size_t)nslices * cap * kWave, &wlist));
         constexpr int64_t kW = kBlock / kWave;
         const int64_t wblk = windows ? ceil_div(ceil_div(n, (int64_t)kWinRows), kW) : 0;
         // four waves per SIMD (what the scan's registers allow) on every CU
@@ -1099,17 +1106,19 @@ sph_status build_sell(sph_ctx* ctx, const sph_nbr* nb, const PartView& pv, const
     SPH_TRY(ctx->ensure_t(kDg, n, &dg));
     SPH_TRY(ctx->ensure_t(kRs64, n, &rs64));
     if (!legacy) {
-        // Occupancy limit: the launch reserves LDS it does not use, so that
+        const bool listed = (int64_t)(uint32_t)hcnt[1] <= cap;  // (the longest row)
+        const bool sliced = windowed && listed && !op.f32cell;
+        if (!sliced) SPH_TRY(ctx->ensure_t(kWList, (size_t)nslices * cap * kWave, &wlist));
+        // Occupancy limit of k_row_fill_list: the launch reserves LDS it does not use, so that
         // only two blocks share a CU.  The neighbour gathers of the rows in
         // flight on an XCD then fit its L2 (with eight blocks per CU they
         // did not): 8.1 -> 5.8 ms at 4.49M particles.
         constexpr size_t kFillLdsReserve = 60 * 1024;
-        const bool listed = (int64_t)(uint32_t)hcnt[1] <= cap;  // (the longest row)
         const dim3 wave_grid((unsigned)(ceil_div(nslices, kNumXcd) * kNumXcd));
-        if (windowed && listed && !op.f32cell && cap == kListCap)
+        if (sliced && cap == kListCap)
             hipLaunchKernelGGL((k_slice_fill<T, kListCap, 4>), wave_grid, dim3(4 * kWave), 0, ctx->stream, nb->view(), pv, op,
                                nslices, creal, list, ptr, coef, dcol, lo, dg, rs64, d, win);
-        else if (windowed && listed && !op.f32cell)
+        else if (sliced)
             hipLaunchKernelGGL((k_slice_fill<T, kListCapGauss, 8>), wave_grid, dim3(8 * kWave), 0, ctx->stream,
                                nb->view(), pv, op, nslices, creal, list, ptr, coef, dcol, lo, dg, rs64, d, win);
         else if (windowed)
