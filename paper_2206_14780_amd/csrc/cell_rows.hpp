@@ -74,23 +74,28 @@ __device__ inline double row_sum(double v) {
     return v;
 }
 
-constexpr int kCellWaves = 4;     // waves of a block
+// Waves of a block: four with the Wendland kernel's ~500 candidates a cell
+// (three or four blocks share a CU); the truncated Gaussian's ~1600 fill the LDS of a
+// CU, so one block brings all the waves.
+constexpr int kCellWaves = 4, kCellWavesGauss = 16;
 constexpr int kCellRows = 4;      // rows of a wave at a time, 16 lanes each
 constexpr int kCellList = 192;    // listed neighbours of a row before they are summed
 enum { kTakeNone = 0, kTakeAll = 1, kTakeFluid = 2 };  // neighbours of a row
 
 // Candidates that a block stages: the mean of the 27 cells around a particle
-// and a third more, within what leaves three blocks of a CU room (a cell with
-// more is done in batches).
+// and a seventh more (the blocks of cells of a lattice hold up to 8^3 where
+// the mean is 7.95^3), within the LDS; a cell with more is done in batches.
 inline int32_t cell_cap(const sph_nbr* nb) {
-    const double mean = 27.0 * (double)nb->n / (double)nb->ncell;
-    const double want = mean * 1.35 + 64.0;
-    const int32_t most = nb->g.kernel == SPH_KERNEL_GAUSSIAN ? 2048 : 768;
+    const double want = 27.0 * (double)nb->n / (double)nb->ncell * 1.07;
+    const int32_t most = nb->g.kernel == SPH_KERNEL_GAUSSIAN ? 1900 : 1024;
     return (int32_t)(want < most ? want : most) / kWave * kWave + kWave;
 }
-template <class B>
+template <class B, int W>
 constexpr size_t cell_bytes(int32_t cap) {
-    return (size_t)cap * (8 * (3 + B::NX) + 4) + 8 * (cap / kWave) + kCellWaves * kCellRows * kCellList * 2;
+    // positions and extras, fluid masks, and the rows' lists, which share their
+    // place with the candidates' indices
+    return (size_t)cap * (24 + sizeof(typename B::X) * B::NX) + 8 * (cap / kWave) +
+           (W * kCellRows * kCellList * 2 > cap * 4 ? W * kCellRows * kCellList * 2 : cap * 4);
 }
 
 // For every row of cell c: acc = sum of body.term over its neighbours, then
@@ -98,8 +103,13 @@ constexpr size_t cell_bytes(int32_t cap) {
 // body.NX values each); a wave takes four rows at a time, tests them against
 // 64 candidates at once and lists the hits, and then sums a row's terms over
 // 16 lanes, so that the pair arithmetic runs only on neighbours (a sixth of
-// the candidates) with every lane busy.  Called by the whole block.
-template <class B>
+// the candidates) with every lane busy.  One thread per row walking all its
+// candidates, as before, ran the pair arithmetic for every candidate that any
+// lane took.  What bounds it is the vector ALU: about 200 instructions a row
+// for the tests, 200 for the pair terms, 70 for sums and results.  The
+// viscosity update (FP64): 2.08 -> 1.19 ms at 1.03M particles, 487 -> 154 us at
+// 118k; the operator (FP32 x): 558 -> 322 us at 227k.  Called by the whole block.
+template <int W, class B>
 __device__ inline void cell_rows(const NbrView& nv, int32_t c, int32_t cap, unsigned char* lds, const B& body) {
     const Grid& g = nv.g;
     const int32_t rb = nv.cell_start[c], re = nv.cell_start[c + 1];
@@ -107,10 +117,12 @@ __device__ inline void cell_rows(const NbrView& nv, int32_t c, int32_t cap, unsi
     const int tid = threadIdx.x, lane = tid & (kWave - 1);
     const int wid = __builtin_amdgcn_readfirstlane(tid / kWave);
     double* px = reinterpret_cast<double*>(lds);
-    double *py = px + cap, *pz = py + cap, *ext = pz + cap;
-    uint64_t* fluid = reinterpret_cast<uint64_t*>(ext + (size_t)B::NX * cap);
-    int32_t* cand = reinterpret_cast<int32_t*>(fluid + cap / kWave);
-    uint16_t* list = reinterpret_cast<uint16_t*>(cand + cap) + wid * (kCellRows * kCellList);
+    typedef typename B::X X;
+    double *py = px + cap, *pz = py + cap;
+    uint64_t* fluid = reinterpret_cast<uint64_t*>(pz + cap);
+    X* ext = reinterpret_cast<X*>(fluid + cap / kWave);
+    int32_t* cand = reinterpret_cast<int32_t*>(ext + (size_t)B::NX * cap);
+    uint16_t* list = reinterpret_cast<uint16_t*>(cand) + wid * (kCellRows * kCellList);
     int32_t beg, len, total;
     cell_run(nv, c, lane, beg, len);
     const int32_t pre = run_prefix(len, lane, total);
@@ -118,10 +130,10 @@ __device__ inline void cell_rows(const NbrView& nv, int32_t c, int32_t cap, unsi
     const int own_run = __builtin_ctzll(own);
     const int32_t self0 = __builtin_amdgcn_readlane(pre - beg, own_run);  // place of the cell's particles, less their index
     const int32_t nbatch = (total + cap - 1) / cap;
-    const int32_t turns = (re - rb + kCellRows * kCellWaves - 1) / (kCellRows * kCellWaves);
+    const int32_t turns = (re - rb + kCellRows * W - 1) / (kCellRows * W);
     bool image = false;
     for (int32_t turn = 0; turn < turns; ++turn) {
-        const int32_t g0 = rb + (turn * kCellWaves + wid) * kCellRows;
+        const int32_t g0 = rb + (turn * W + wid) * kCellRows;
         const int32_t nr = min(re - g0, kCellRows);  // may be <= 0: the wave only helps to stage
         const int sub = lane >> 4;
         const int32_t my = g0 + min(sub, max(nr, 1) - 1);  // the row whose terms the lane sums
@@ -150,7 +162,7 @@ __device__ inline void cell_rows(const NbrView& nv, int32_t c, int32_t cap, unsi
                 for (int at = 0; runs; ++at) {
                     const int t = __builtin_ctzll(runs);
                     runs &= runs - 1;
-                    if (at % kCellWaves != wid) continue;
+                    if (at % W != wid) continue;
                     const int32_t B0 = __builtin_amdgcn_readlane(beg, t), L = __builtin_amdgcn_readlane(len, t);
                     const int32_t P = __builtin_amdgcn_readlane(pre, t) - b0;
                     const int32_t j1 = min(L, cap - P);
@@ -159,11 +171,11 @@ __device__ inline void cell_rows(const NbrView& nv, int32_t c, int32_t cap, unsi
                 __syncthreads();
                 const Pos4 ref = nv.pos[rb];
                 bool far = false;
-                for (int32_t p = tid; p < (nc + kWave - 1) / kWave * kWave; p += kCellWaves * kWave) {
+                for (int32_t p = tid; p < (nc + kWave - 1) / kWave * kWave; p += W * kWave) {
                     const bool ok = p < nc;
                     const int32_t a = ok ? cand[p] : rb;
                     const Pos4 s = nv.pos[a];
-                    double v[B::NX];
+                    X v[B::NX];
                     body.stage(a, v);
                     // a place without a candidate never passes the distance test
                     px[p] = ok ? s.x : __builtin_nan("");
@@ -191,7 +203,7 @@ __device__ inline void cell_rows(const NbrView& nv, int32_t c, int32_t cap, unsi
                         dy = disp(pm.y, py[p], g.period[1]);
                         dz = disp(pm.z, pz[p], g.period[2]);
                     }
-                    double v[B::NX];
+                    X v[B::NX];
 #pragma unroll
                     for (int k = 0; k < B::NX; ++k) v[k] = ext[(size_t)k * cap + p];
                     body.term(g, mine, (dx * dx + dy * dy) + dz * dz, dx, dy, dz, v, acc);

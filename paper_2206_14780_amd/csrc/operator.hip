@@ -573,42 +573,9 @@ __global__ __launch_bounds__(kBlock) void k_row_scan(NbrView nv, PartView pv, Op
     int32_t* cand = cand_lds[wid];
     // the runs of cells around the cell, one per lane, in ascending order, and
     // their places in the sequence of candidates
-    int32_t beg = 0, len = 0;
-    if (lane < 27) {
-        const int32_t nx = g.nc[0], ny = g.nc[1];
-        const int32_t cx = c % nx, l = c / nx;
-        const int32_t part = lane % 3, iy = (lane / 3) % 3, iz = lane / 9;
-        int32_t zs[3], ys[3];
-        const int nzs = axis_cells(l / ny, g.nc[2], g.per[2], zs);
-        const int nys = axis_cells(l % ny, ny, g.per[1], ys);
-        const bool wraps = g.per[0] && nx >= 3;
-        int32_t lo = cx > 0 ? cx - 1 : 0, hi = cx < nx - 1 ? cx + 1 : nx - 1;
-        if (g.per[0] && nx < 3) {
-            lo = 0;
-            hi = nx - 1;
-        }
-        bool on = iz < nzs && iy < nys;
-        if (part == 0) {  // the first cell, from the last one
-            on = on && wraps && cx == nx - 1;
-            lo = hi = 0;
-        } else if (part == 2) {  // the last cell, from the first one
-            on = on && wraps && cx == 0;
-            lo = hi = nx - 1;
-        }
-        if (on) {
-            const int32_t base = (zs[iz] * ny + ys[iy]) * nx;
-            beg = nv.cell_start[base + lo];
-            len = nv.cell_start[base + hi + 1] - beg;
-        }
-    }
-    int32_t pre = len;
-#pragma unroll
-    for (int o = 1; o < 32; o <<= 1) {
-        const int32_t v = __shfl_up(pre, o, kWave);
-        if (lane >= o) pre += v;
-    }
-    const int32_t total = __builtin_amdgcn_readlane(pre, 26);
-    pre -= len;
+    int32_t beg, len, total;
+    cell_run(nv, c, lane, beg, len);
+    const int32_t pre = run_prefix(len, lane, total);
     for (int32_t b0 = 0; b0 < total; b0 += kScanBatch) {
         uint64_t runs = __ballot(len > 0 && pre < b0 + kScanBatch && pre + len > b0);
         while (runs) {
@@ -636,15 +603,9 @@ __global__ __launch_bounds__(kBlock) void k_row_scan(NbrView nv, PartView pv, Op
             ay[q] = s->y;
             az[q] = s->z;
             fluid[q] = __ballot(pv.type[a[q]] == SPH_FLUID);
-            far = far || (ok && ((g.period[0] > 0.0 && !(fabs(ref.x - ax[q]) <= 0.24 * g.period[0])) ||
-                                 (g.period[1] > 0.0 && !(fabs(ref.y - ay[q]) <= 0.24 * g.period[1])) ||
-                                 (g.period[2] > 0.0 && !(fabs(ref.z - az[q]) <= 0.24 * g.period[2]))));
+            far = far || (ok && far_image(g, ref, ax[q], ay[q], az[q]));
         }
         wave_sync();
-        // All candidates (the cell's rows among them, so far as they fit one
-        // batch) within a quarter of the period of one of the rows: every
-        // displacement is below half a period and the minimum image is the
-        // plain difference.
         const bool image = __any(far) || total > kScanBatch;
         for (int32_t g0 = rb; g0 < re; g0 += kWave) {
             // the rows, one per lane
@@ -1195,9 +1156,7 @@ sph_status apply_plain(sph_ctx* ctx, const sph_nbr* nb, const PartView& pv, cons
     } else if (mode == SPH_OP_CACHED) {
         launch_apply_sell<T, kDotNone>(ctx->stream, L, nullptr, *sell, x, y, nullptr, nullptr, nullptr);
     } else {
-        hipLaunchKernelGGL((k_apply_otf<T, kDotNone>), dim3(L.grid_apply), dim3(L.block_apply), 0, ctx->stream,
-                           (const int32_t*)nullptr, nb->view(), pv, op, x, y, (const T*)nullptr,
-                           (const double*)nullptr, (double*)nullptr);
+        launch_apply_otf<T, kDotNone>(ctx->stream, L, nullptr, nb, pv, op, x, y, nullptr, nullptr, nullptr);
     }
     SPH_LAUNCHED("apply");
     return SPH_OK;

@@ -5,7 +5,7 @@
 
 #include <cmath>
 
-#include "sph_device.hpp"
+#include "cell_rows.hpp"
 
 namespace sph {
 
@@ -499,74 +499,89 @@ __global__ __launch_bounds__(kApplyMaxBlock) void k_apply_sell(const int32_t* __
     if constexpr (MODE != kDotNone) write_partials_kh<K, KH>(acc, cmp, lds, part);
 }
 
-// One row of the operator evaluated from positions in FP64 (the paper's
-// matrix-free gemv): returns (A x)_b, or (D^-1 A x)_b with Jacobi.
-template <typename T>
-__device__ inline void row_apply_otf(const NbrView& nv, const PartView& pv, const OpParams& op,
-                                     const T* __restrict__ x, int32_t b, double (&y)[3]) {
-    const V3<T> xb = ld3(x, b);
-    y[0] = (double)xb.x;
-    y[1] = (double)xb.y;
-    y[2] = (double)xb.z;
-    if (pv.type[b] == SPH_FLUID) {
-        double sw = 0.0, s0 = 0.0, s1 = 0.0, s2 = 0.0;
-        for_each_neighbor(nv, b, [&](int32_t a, double r2) {
-            const double wgt = pair_w(pv, nv.g, op.avg, b, a, r2);
-            const V3<T> xa = ld3(x, a);
-            sw += wgt;
-            s0 += wgt * (double)xa.x;
-            s1 += wgt * (double)xa.y;
-            s2 += wgt * (double)xa.z;
-        });
-        const double diag = 1.0 + op.dt * sw;
-        y[0] = diag * y[0] - op.dt * s0;
-        y[1] = diag * y[1] - op.dt * s1;
-        y[2] = diag * y[2] - op.dt * s2;
-        if (op.jacobi) {
-            y[0] /= diag;
-            y[1] /= diag;
-            y[2] /= diag;
-        }
-    } else if (op.wall == SPH_WALL_DUMMY) {
-        double sW = 0.0, s0 = 0.0, s1 = 0.0, s2 = 0.0;
-        for_each_neighbor(nv, b, [&](int32_t a, double r2) {
-            if (pv.type[a] != SPH_FLUID) return;
-            const double W = pair_W(nv.g, r2);
-            const V3<T> xa = ld3(x, a);
-            sW += W;
-            s0 += W * (double)xa.x;
-            s1 += W * (double)xa.y;
-            s2 += W * (double)xa.z;
-        });
-        if (sW > 0.0) {
-            y[0] += s0 / sW;
-            y[1] += s1 / sW;
-            y[2] += s2 / sW;
-        }
+// Row of the operator evaluated from positions in FP64 (the paper's
+// matrix-free gemv) for cell_rows: staged per candidate the vector x and the
+// pair data (mu, m/rho); sums of the weights and of weight times x; finish
+// forms (A x)_b, or (D^-1 A x)_b with Jacobi, and hands it to out(row, y).
+template <typename T, class F>
+struct OtfBody {
+    typedef T X;
+    static constexpr int NX = 3 + 16 / sizeof(T);  // x, and (mu, m / rho) in 16 bytes
+    static constexpr int NA = 4;  // sum of weights, of weight * x
+    PartView pv;
+    OpParams op;
+    const T* x;
+    F out;
+    struct Row {
+        int take;
+        double mu, ir;
+        V3<T> x;
+    };
+    __device__ Row row(int32_t b) const {
+        const bool fluid = pv.type[b] == SPH_FLUID;
+        const int take = fluid ? kTakeAll : op.wall == SPH_WALL_DUMMY ? kTakeFluid : kTakeNone;
+        return Row{take, pv.mu[b], pv.inv_rho[b], ld3(x, b)};
     }
-}
+    struct Pair {
+        T v[16 / sizeof(T)];
+    };
+    __device__ void stage(int32_t a, T (&v)[NX]) const {
+        const V3<T> xa = ld3(x, a);
+        const Pair ma = __builtin_bit_cast(Pair, pv.mu_mr[a]);
+        v[0] = xa.x;
+        v[1] = xa.y;
+        v[2] = xa.z;
+        for (int k = 3; k < NX; ++k) v[k] = ma.v[k - 3];
+    }
+    __device__ bool fluid(int32_t a) const { return pv.type[a] == SPH_FLUID; }
+    __device__ void term(const Grid& g, const Row& b, double r2, double, double, double, const T (&v)[NX],
+                         double (&acc)[NA]) const {
+        Pair p;
+        for (int k = 3; k < NX; ++k) p.v[k - 3] = v[k];
+        const double2 ma = __builtin_bit_cast(double2, p);
+        const double w = b.take == kTakeAll ? pair_w_v(g, op.avg, ma.x, ma.y, b.mu, b.ir, r2) : pair_W(g, r2);
+        acc[0] += w;
+        acc[1] += w * (double)v[0];
+        acc[2] += w * (double)v[1];
+        acc[3] += w * (double)v[2];
+    }
+    __device__ void finish(int32_t b, const Row& r, const double (&acc)[NA]) const {
+        double y[3] = {(double)r.x.x, (double)r.x.y, (double)r.x.z};
+        if (r.take == kTakeAll) {
+            const double diag = 1.0 + op.dt * acc[0];
+            for (int c = 0; c < 3; ++c) {
+                y[c] = diag * y[c] - op.dt * acc[1 + c];
+                if (op.jacobi) y[c] /= diag;
+            }
+        } else if (r.take == kTakeFluid && acc[0] > 0.0) {
+            for (int c = 0; c < 3; ++c) y[c] += acc[1 + c] / acc[0];
+        }
+        out(b, r.x, y);
+    }
+};
 
-// On-the-fly operator over rows in cell order; with kDotResid it writes
-// y = b64 - A x instead (FP64 residual rounded to T) and its squared norm,
-// x then being of precision XT; with kDotCG, b64 holds the weights D.
-template <typename T, int MODE, typename XT = T>
-__global__ __launch_bounds__(kApplyMaxBlock) void k_apply_otf(const int32_t* __restrict__ halt, NbrView nv, PartView pv,
-                                                         OpParams op, const XT* __restrict__ x, T* __restrict__ y,
-                                                         const T* __restrict__ w, const double* __restrict__ b64,
-                                                         double* __restrict__ part) {
+// On-the-fly operator over the cells, each block a contiguous share of them;
+// with kDotResid it writes y = b64 - A x instead (FP64 residual rounded to T)
+// and its squared norm, x then being of precision XT; with kDotCG, b64 holds
+// the weights D.
+template <typename T, int MODE, typename XT, int W>
+__global__ __launch_bounds__(W* kWave) void k_apply_otf(const int32_t* __restrict__ halt, NbrView nv,
+                                                                 PartView pv, OpParams op, int64_t ncell, int32_t cap,
+                                                                 const XT* __restrict__ x, T* __restrict__ y,
+                                                                 const T* __restrict__ w,
+                                                                 const double* __restrict__ b64,
+                                                                 double* __restrict__ part) {
     if (halt && *halt) return;
     constexpr int K = DotK<MODE>::K;
     __shared__ double lds[K * kMaxWaves];
+    extern __shared__ __align__(16) unsigned char cell_lds[];
     double acc[K];
 #pragma unroll
     for (int k = 0; k < K; ++k) acc[k] = 0.0;
     const int64_t bid = xcd_block(blockIdx.x, gridDim.x);
-    const int64_t rpb = ceil_div(nv.n, (int64_t)gridDim.x);
-    const int64_t r0 = bid * rpb;
-    const int64_t r1 = min(r0 + rpb, nv.n);
-    for (int64_t r = r0 + threadIdx.x; r < r1; r += blockDim.x) {
-        double yv[3];
-        row_apply_otf<XT>(nv, pv, op, x, (int32_t)r, yv);
+    const int64_t cpb = ceil_div(ncell, (int64_t)gridDim.x);
+    const int64_t c0 = bid * cpb, c1 = min(c0 + cpb, ncell);
+    const auto out = [&](int32_t r, const V3<XT>& xr, double (&yv)[3]) {
         if constexpr (MODE == kDotResid) {
             const V3<double> bb = ld3(b64, r);
             yv[0] = bb.x - yv[0];
@@ -576,21 +591,39 @@ __global__ __launch_bounds__(kApplyMaxBlock) void k_apply_otf(const int32_t* __r
             acc[1] += yv[1] * yv[1];
             acc[2] += yv[2] * yv[2];
         }
-        V3<T> out;
-        out.x = (T)yv[0];
-        out.y = (T)yv[1];
-        out.z = (T)yv[2];
-        st3(y, r, out);
+        const V3<T> o{(T)yv[0], (T)yv[1], (T)yv[2]};
+        st3(y, r, o);
         if constexpr (MODE != kDotNone && MODE != kDotResid) {
             V3<T> wv{};
             if constexpr (MODE == kDotA1) wv = ld3(w, r);
             double dw = 1.0;
             if constexpr (MODE == kDotCG) dw = b64 ? b64[r] : 1.0;
             float cmp[K];
-            accumulate_dots<T, MODE>(acc, cmp, ld3(x, r), out, wv, dw);
+            accumulate_dots<T, MODE>(acc, cmp, xr, o, wv, dw);
         }
-    }
+    };
+    const OtfBody<XT, decltype(out)> body{pv, op, x, out};
+    for (int64_t c = c0; c < c1; ++c) cell_rows<W>(nv, (int32_t)c, cap, cell_lds, body);
     if constexpr (MODE != kDotNone) write_partials<K>(acc, lds, part);
+}
+
+// Launch of the on-the-fly operator: a block per cell, or (dot products) the
+// operator's grid, whose blocks write the partials.
+template <typename T, int MODE, typename XT = T>
+inline void launch_apply_otf(hipStream_t stream, const Launch& L, const int32_t* halt, const sph_nbr* nb,
+                             const PartView& pv, const OpParams& op, const XT* x, T* y, const T* w, const double* b64,
+                             double* part) {
+    const int32_t cap = cell_cap(nb);
+    const int64_t cells = ceil_div(nb->ncell, (int64_t)kNumXcd) * kNumXcd;
+    const unsigned grid = MODE == kDotNone ? (unsigned)cells : (unsigned)L.grid_apply;
+    const auto go = [&](auto waves) {
+        constexpr int W = decltype(waves)::value;
+        hipLaunchKernelGGL((k_apply_otf<T, MODE, XT, W>), dim3(grid), dim3(W * kWave),
+                           (cell_bytes<OtfBody<XT, int>, W>(cap)), stream, halt, nb->view(), pv, op, nb->ncell, cap, x,
+                           y, w, b64, part);
+    };
+    if (nb->g.kernel == SPH_KERNEL_GAUSSIAN) go(std::integral_constant<int, kCellWavesGauss>{});
+    else go(std::integral_constant<int, kCellWaves>{});
 }
 
 // Launch of the cached operator in the matrix's column code.

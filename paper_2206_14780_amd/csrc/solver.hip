@@ -691,8 +691,6 @@ struct Solver {
         return SPH_OK;
     }
 
-    dim3 ga() const { return dim3(L.grid_apply); }
-    dim3 ba() const { return dim3(L.block_apply); }
     dim3 gs() const { return dim3(L.grid_stream); }
     dim3 bs() const { return dim3(L.block_stream); }
 
@@ -705,8 +703,7 @@ struct Solver {
             launch_apply_sell<T, MODE, XT, KH && MODE != kDotResid>(ctx->stream, L, halt, sell, xin, yout, w, aux,
                                                                    part);
         else
-            hipLaunchKernelGGL((k_apply_otf<T, MODE, XT>), ga(), ba(), 0, ctx->stream, halt, nb->view(), pv, op,
-                               xin, yout, w, aux, part);
+            launch_apply_otf<T, MODE, XT>(ctx->stream, L, halt, nb, pv, op, xin, yout, w, aux, part);
         ++launches;
     }
 

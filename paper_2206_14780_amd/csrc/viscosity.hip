@@ -4,7 +4,7 @@
 // mu = tau0 Ybar(D) + mu0 with the regularised yield term Ybar.
 #include <cmath>
 
-#include "sph_device.hpp"
+#include "cell_rows.hpp"
 
 namespace sph {
 
@@ -22,51 +22,70 @@ __device__ inline double ybar(double D, double m, double x0) {
     return m * t;
 }
 
-// One thread per particle in cell order.  G = sum_a (m_a/rho_a) F(r_ab)
+// Viscosity update of a row for cell_rows.  G = sum_a (m_a/rho_a) F(r_ab)
 // r_ab u_ab^T over the neighbours a (r_ab = r_a - r_b by minimum image,
 // u_ab = u_a - u_b; the printed form, minus the usual SPH gradient, which
 // the symmetric quadratic invariant does not see), S = (G + G^T)/2,
-// D = sqrt(2 S:S) (the shear rate in simple shear).  Fluid rows get
-// tau0 Ybar(D) + mu0, wall rows keep their viscosity; both outputs are
-// written in the caller's order.
+// D = sqrt(2 S:S) (the shear rate in simple shear).  Only the six sums of S
+// are kept, the off-diagonal ones as G_ij + G_ji.  Fluid rows get tau0
+// Ybar(D) + mu0, wall rows keep their viscosity; both outputs are written in
+// the caller's order.
 template <typename T>
-__global__ __launch_bounds__(kBlock) void k_papa_visc(NbrView nv, PartView pv, const T* __restrict__ u,
-                                                      const int32_t* __restrict__ perm, double tau0, double m,
-                                                      double mu0, double x0, double* __restrict__ mu_out,
-                                                      double* __restrict__ d_out) {
-    const int64_t b = (int64_t)xcd_block(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x;
-    if (b >= nv.n) return;
-    const Grid& g = nv.g;
-    const int32_t row = (int32_t)b;
-    const Pos4 pb = nv.pos[row];
-    const V3<T> ub = ld3(u, row);
-    double G[3][3] = {{0.0, 0.0, 0.0}, {0.0, 0.0, 0.0}, {0.0, 0.0, 0.0}};
-    for_each_neighbor(nv, row, [&](int32_t a, double r2) {
-        const Pos4 pa = nv.pos[a];
-        const double r[3] = {disp(pa.x, pb.x, g.period[0]), disp(pa.y, pb.y, g.period[1]),
-                             disp(pa.z, pb.z, g.period[2])};
-        const double F = kernel_f(g, sqrt(r2) * g.inv_h) * g.inv_h5;
-        const double vf = pv.mu_mr[a].y * F;
+struct PapaBody {
+    typedef double X;
+    static constexpr int NX = 4;  // u, m / rho
+    static constexpr int NA = 6;  // xx, yy, zz, xy, xz, yz
+    PartView pv;
+    const T* u;
+    const int32_t* perm;
+    double tau0, m, mu0, x0;
+    double *mu_out, *d_out;
+    struct Row {
+        int take;
+        double u[3];
+    };
+    __device__ Row row(int32_t b) const {
+        const V3<T> ub = ld3(u, b);
+        return Row{kTakeAll, {(double)ub.x, (double)ub.y, (double)ub.z}};
+    }
+    __device__ void stage(int32_t a, double (&v)[NX]) const {
         const V3<T> ua = ld3(u, a);
-        const double du[3] = {(double)ua.x - (double)ub.x, (double)ua.y - (double)ub.y,
-                              (double)ua.z - (double)ub.z};
-#pragma unroll
-        for (int i = 0; i < 3; ++i)
-#pragma unroll
-            for (int j = 0; j < 3; ++j) G[i][j] += vf * r[i] * du[j];
-    });
-    double ss = 0.0;
-#pragma unroll
-    for (int i = 0; i < 3; ++i)
-#pragma unroll
-        for (int j = 0; j < 3; ++j) {
-            const double s = 0.5 * (G[i][j] + G[j][i]);
-            ss += s * s;
-        }
-    const double D = sqrt(2.0 * ss);
-    const int32_t o = perm[row];
-    mu_out[o] = pv.type[row] == SPH_FLUID ? tau0 * ybar(D, m, x0) + mu0 : pv.mu[row];
-    if (d_out) d_out[o] = D;
+        v[0] = (double)ua.x;
+        v[1] = (double)ua.y;
+        v[2] = (double)ua.z;
+        v[3] = pv.mu_mr[a].y;
+    }
+    __device__ bool fluid(int32_t) const { return true; }
+    __device__ void term(const Grid& g, const Row& b, double r2, double dx, double dy, double dz,
+                         const double (&v)[NX], double (&acc)[NA]) const {
+        const double F = kernel_f(g, sqrt(r2) * g.inv_h) * g.inv_h5;
+        const double vf = v[3] * F;
+        // r_ab = -(dx, dy, dz)
+        const double rx = -dx, ry = -dy, rz = -dz;
+        const double ux = v[0] - b.u[0], uy = v[1] - b.u[1], uz = v[2] - b.u[2];
+        acc[0] += vf * rx * ux;
+        acc[1] += vf * ry * uy;
+        acc[2] += vf * rz * uz;
+        acc[3] += vf * rx * uy + vf * ry * ux;
+        acc[4] += vf * rx * uz + vf * rz * ux;
+        acc[5] += vf * ry * uz + vf * rz * uy;
+    }
+    __device__ void finish(int32_t b, const Row&, const double (&s)[NA]) const {
+        // S:S with the off-diagonal pairs (G_ij + G_ji)/2 counted twice
+        const double ss = (s[0] * s[0] + s[1] * s[1] + s[2] * s[2]) +
+                          0.5 * (s[3] * s[3] + s[4] * s[4] + s[5] * s[5]);
+        const double D = sqrt(2.0 * ss);
+        const int32_t o = perm[b];
+        mu_out[o] = pv.type[b] == SPH_FLUID ? tau0 * ybar(D, m, x0) + mu0 : pv.mu[b];
+        if (d_out) d_out[o] = D;
+    }
+};
+
+template <typename T, int W>
+__global__ __launch_bounds__(W* kWave) void k_papa_visc(NbrView nv, int64_t ncell, int32_t cap, PapaBody<T> body) {
+    extern __shared__ __align__(16) unsigned char cell_lds[];
+    const int64_t c = xcd_block(blockIdx.x, gridDim.x);
+    if (c < ncell) cell_rows<W>(nv, (int32_t)c, cap, cell_lds, body);
 }
 
 template <typename T>
@@ -78,10 +97,16 @@ static sph_status papa_entry(sph_ctx* ctx, const sph_nbr* nb, const sph_particle
     SPH_TRY(ctx->ensure_t(kViscU, (size_t)nb->n * 3, &ucell));
     SPH_TRY(gather_vec3<T>(ctx, nb, u, ucell));
     const double x0 = std::pow(362880.0 * std::ldexp(1.0, -23), 0.125);
-    const int64_t nblk = ceil_div(nb->n, (int64_t)kBlock);
-    const dim3 grid((unsigned)(nblk >= 64 ? ceil_div(nblk, (int64_t)kNumXcd) * kNumXcd : nblk));
-    hipLaunchKernelGGL(k_papa_visc<T>, grid, dim3(kBlock), 0, ctx->stream, nb->view(), pv, (const T*)ucell,
-                       (const int32_t*)nb->perm, tau0, m, mu0, x0, mu_out, d_out);
+    const int32_t cap = cell_cap(nb);
+    const dim3 grid((unsigned)(ceil_div(nb->ncell, (int64_t)kNumXcd) * kNumXcd));
+    const auto go = [&](auto waves) {
+        constexpr int W = decltype(waves)::value;
+        hipLaunchKernelGGL((k_papa_visc<T, W>), grid, dim3(W * kWave), (cell_bytes<PapaBody<T>, W>(cap)), ctx->stream,
+                           nb->view(), nb->ncell, cap,
+                           (PapaBody<T>{pv, ucell, nb->perm, tau0, m, mu0, x0, mu_out, d_out}));
+    };
+    if (nb->g.kernel == SPH_KERNEL_GAUSSIAN) go(std::integral_constant<int, kCellWavesGauss>{});
+    else go(std::integral_constant<int, kCellWaves>{});
     SPH_LAUNCHED("k_papa_visc");
     return SPH_OK;
 }
