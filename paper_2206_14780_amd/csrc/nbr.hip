@@ -194,22 +194,34 @@ __global__ __launch_bounds__(kBlock) void k_gather_pos(int64_t n, const int32_t*
 // ---------------------------------------------------------------------------
 // Canonical export: CSR over original indices, columns ascending.
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(kBlock) void k_count_orig(NbrView nv, const int32_t* __restrict__ iperm,
-                                                       int64_t* __restrict__ cnt) {
+__global__ __launch_bounds__(kBlock) void k_count_orig(int64_t n, const int32_t* __restrict__ iperm,
+                                                       const int32_t* __restrict__ count, int64_t* __restrict__ cnt,
+                                                       int32_t* __restrict__ longest) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= nv.n) return;
-    int64_t c = 0;
-    for_each_neighbor(nv, iperm[i], [&](int32_t, double) { ++c; });
-    cnt[i] = c;
+    int32_t c = 0;
+    if (i < n) {
+        c = count[iperm[i]];
+        cnt[i] = c;
+    }
+    __shared__ int32_t most[kBlock / kWave];
+    for (int o = kWave / 2; o > 0; o >>= 1) c = max(c, __shfl_xor(c, o, kWave));
+    if (threadIdx.x % kWave == 0) most[threadIdx.x / kWave] = c;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int k = 1; k < kBlock / kWave; ++k) c = max(c, most[k]);
+        atomicMax(longest, c);
+    }
 }
 
+// Rows with more than `above` neighbours, one thread each.
 __global__ __launch_bounds__(kBlock) void k_fill_orig(NbrView nv, const int32_t* __restrict__ iperm,
                                                       const int32_t* __restrict__ perm,
-                                                      const int64_t* __restrict__ row_ptr,
+                                                      const int64_t* __restrict__ row_ptr, int32_t above,
                                                       int32_t* __restrict__ cols) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= nv.n) return;
     const int64_t b = row_ptr[i];
+    if (row_ptr[i + 1] - b <= above) return;
     int64_t k = b;
     for_each_neighbor(nv, iperm[i], [&](int32_t a, double) { cols[k++] = perm[a]; });
     for (int64_t u = b + 1; u < k; ++u) {
@@ -344,11 +356,18 @@ extern "C" sph_status sph_build_neighbors(sph_ctx* ctx, const sph_particles* p, 
     return SPH_OK;
 }
 
-static sph_status count_pairs(sph_ctx* ctx, const sph_nbr* nb, int64_t** cnt_out) {
+// Pairs per particle (caller order) into cnt and the lists behind them (cap
+// entries per row, 0: none); *longest: device, the longest row.
+static sph_status count_pairs(sph_ctx* ctx, const sph_nbr* nb, int32_t cap, int64_t** cnt_out, int32_t** count,
+                              int32_t** list, int32_t** longest) {
     int64_t* cnt = nullptr;
     SPH_TRY(ctx->ensure_t(kExportCnt, (size_t)(nb->n + 1), &cnt));
-    hipLaunchKernelGGL(k_count_orig, dim3((unsigned)ceil_div(nb->n, kBlock)), dim3(kBlock), 0, ctx->stream,
-                       nb->view(), nb->iperm, cnt);
+    SPH_TRY(ctx->ensure_t(kCntReal, (size_t)nb->n + 1, count));
+    *longest = *count + nb->n;
+    SPH_HIP(hipMemsetAsync(*longest, 0, sizeof(int32_t), ctx->stream));
+    SPH_TRY(neighbour_scan(ctx, nb, cap, *count, list));
+    hipLaunchKernelGGL(k_count_orig, dim3((unsigned)ceil_div(nb->n, kBlock)), dim3(kBlock), 0, ctx->stream, nb->n,
+                       nb->iperm, (const int32_t*)*count, cnt, *longest);
     SPH_LAUNCHED("k_count_orig");
     *cnt_out = cnt;
     return SPH_OK;
@@ -361,7 +380,8 @@ extern "C" sph_status sph_neighbors_info(sph_ctx* ctx, const sph_nbr* nb, int64_
     *n = nb->n;
     if (nb->nnz < 0) {
         int64_t* cnt = nullptr;
-        SPH_TRY(count_pairs(ctx, nb, &cnt));
+        int32_t *count = nullptr, *longest = nullptr;
+        SPH_TRY(count_pairs(ctx, nb, 0, &cnt, &count, nullptr, &longest));
         int64_t* rp = nullptr;
         SPH_TRY(ctx->ensure_t(kApplyOut, (size_t)(nb->n + 1), &rp));
         SPH_TRY(scan_i64(ctx, cnt, rp, nb->n));
@@ -380,17 +400,31 @@ extern "C" sph_status sph_neighbors_export(sph_ctx* ctx, const sph_nbr* nb, int6
     if (!nb || !row_ptr || !nnz) return ctx->fail(SPH_E_ARG, "neighbors_export: null argument");
     if (nb->device != ctx->device) return ctx->fail(SPH_E_ARG, "neighbors_export: handle of another device");
     int64_t* cnt = nullptr;
-    SPH_TRY(count_pairs(ctx, nb, &cnt));
+    int32_t *count = nullptr, *list = nullptr, *longest = nullptr;
+    // without room for the lists every row is scanned again by the fill
+    int32_t lcap = export_cap(nb);
+    sph_status st = count_pairs(ctx, nb, lcap, &cnt, &count, &list, &longest);
+    if (st == SPH_E_OOM && lcap > 0) {
+        (void)hipGetLastError();
+        lcap = 0;
+        st = count_pairs(ctx, nb, 0, &cnt, &count, nullptr, &longest);
+    }
+    SPH_TRY(st);
     SPH_TRY(scan_i64(ctx, cnt, row_ptr, nb->n));
     int64_t total = 0;
+    int32_t most = 0;
     SPH_HIP(hipMemcpyAsync(&total, row_ptr + nb->n, sizeof(int64_t), hipMemcpyDeviceToHost, ctx->stream));
+    SPH_HIP(hipMemcpyAsync(&most, longest, sizeof(int32_t), hipMemcpyDeviceToHost, ctx->stream));
     SPH_HIP(hipStreamSynchronize(ctx->stream));
     const_cast<sph_nbr*>(nb)->nnz = total;
     *nnz = total;
     if (total > cap || (!cols && total > 0)) return ctx->fail(SPH_E_OVERFLOW, "neighbors_export: cols too small");
-    hipLaunchKernelGGL(k_fill_orig, dim3((unsigned)ceil_div(nb->n, kBlock)), dim3(kBlock), 0, ctx->stream,
-                       nb->view(), nb->iperm, nb->perm, row_ptr, cols);
-    SPH_LAUNCHED("k_fill_orig");
+    if (lcap > 0) SPH_TRY(export_rows(ctx, nb, lcap, count, list, row_ptr, cols));
+    if (most > lcap) {
+        hipLaunchKernelGGL(k_fill_orig, dim3((unsigned)ceil_div(nb->n, kBlock)), dim3(kBlock), 0, ctx->stream,
+                           nb->view(), nb->iperm, nb->perm, row_ptr, lcap, cols);
+        SPH_LAUNCHED("k_fill_orig");
+    }
     SPH_HIP(hipStreamSynchronize(ctx->stream));
     return SPH_OK;
 }

@@ -546,15 +546,16 @@ __device__ inline void block_windows(const NbrView& nv, int64_t bid, int32_t lim
 // of them vector.  298 -> 22 us at 5,632 particles, 1.08 -> 0.55 ms at 1.16M
 // (windows included), 24.1 -> 16.1 ms at 33.7M, 1.28 -> 0.48 ms at 187k with
 // the Gaussian kernel.
+// all: every row takes every neighbour (the neighbour lists themselves).
 // The first blocks of the launch compute the operator's windows instead
 // (win_blocks, 0 for none): their latency hides behind the scan.
 constexpr int kScanRounds = 8;
 constexpr int kScanBatch = kScanRounds * kWave;
 
 __global__ __launch_bounds__(kBlock) void k_row_scan(NbrView nv, PartView pv, OpParams op, int64_t ncell,
-                                                     int32_t split, int32_t* creal, int32_t* __restrict__ list,
-                                                     int32_t cap, int32_t win_blocks, WinRange* __restrict__ win,
-                                                     int32_t* __restrict__ wmax) {
+                                                     int32_t split, bool all, int32_t* creal,
+                                                     int32_t* __restrict__ list, int32_t cap, int32_t win_blocks,
+                                                     WinRange* __restrict__ win, int32_t* __restrict__ wmax) {
     constexpr int kW = kBlock / kWave;
     __shared__ int32_t cand_lds[kW][kScanBatch > 4 * kWinRuns ? kScanBatch : 4 * kWinRuns];
     const int lane = threadIdx.x & (kWave - 1);
@@ -602,7 +603,7 @@ __global__ __launch_bounds__(kBlock) void k_row_scan(NbrView nv, PartView pv, Op
             ax[q] = ok ? s->x : __builtin_nan("");
             ay[q] = s->y;
             az[q] = s->z;
-            fluid[q] = __ballot(pv.type[a[q]] == SPH_FLUID);
+            fluid[q] = all ? 0 : __ballot(pv.type[a[q]] == SPH_FLUID);
             far = far || (ok && far_image(g, ref, ax[q], ay[q], az[q]));
         }
         wave_sync();
@@ -616,7 +617,7 @@ __global__ __launch_bounds__(kBlock) void k_row_scan(NbrView nv, PartView pv, Op
             int32_t mine = 0;  // neighbours so far
             if (on) {
                 pb = nv.pos[row];
-                kind = row_kind(pv, op, row);
+                kind = all ? (int)kRowFluid : row_kind(pv, op, row);
                 if (b0 > 0) mine = creal[row];
             }
             const int32_t nrow = min(re - g0, kWave);
@@ -985,6 +986,83 @@ sph_status row_diag64(sph_ctx* ctx, const sph_nbr* nb, const PartView& pv, const
     return SPH_OK;
 }
 
+static void launch_row_scan(sph_ctx* ctx, const sph_nbr* nb, const PartView& pv, const OpParams& op, bool all,
+                            int32_t* creal, int32_t* list, int32_t cap, WinRange* win, int32_t* wmax) {
+    constexpr int64_t kW = kBlock / kWave;
+    const int64_t wblk = win ? ceil_div(ceil_div(nb->n, (int64_t)kWinRows), kW) : 0;
+    // four waves per SIMD (what the scan's registers allow) on every CU
+    int32_t split = 1;
+    while (split < 8 && nb->ncell * split < 4096) split *= 2;
+    const int64_t sblk = ceil_div(ceil_div(nb->ncell * split, kW), (int64_t)kNumXcd) * kNumXcd;
+    hipLaunchKernelGGL(k_row_scan, dim3((unsigned)(wblk + sblk)), dim3(kBlock), 0, ctx->stream, nb->view(), pv, op,
+                       nb->ncell, split, all, creal, list, cap, (int32_t)wblk, win, wmax);
+}
+
+// Lists of every particle's neighbours for the canonical export: caller order,
+// columns ascending.  A wave per row reads the row's list, maps it to the
+// caller's indices and ranks the entries against each other in registers.
+template <int CAP>
+__global__ __launch_bounds__(kBlock) void k_export_rows(int64_t n, const int32_t* __restrict__ creal,
+                                                        const int32_t* __restrict__ list,
+                                                        const int32_t* __restrict__ perm,
+                                                        const int64_t* __restrict__ row_ptr,
+                                                        int32_t* __restrict__ cols) {
+    constexpr int E = (CAP + kWave - 1) / kWave;
+    const int lane = threadIdx.x & (kWave - 1);
+    const int64_t r = (int64_t)xcd_block(blockIdx.x, gridDim.x) * (kBlock / kWave) + threadIdx.x / kWave;
+    if (r >= n) return;
+    const int32_t c = __builtin_amdgcn_readfirstlane(creal[r]);
+    if (c > CAP) return;  // no list: k_fill_orig
+    const int32_t* lst = list + list_base(r, CAP);
+    int32_t* out = cols + row_ptr[perm[r]];
+    int32_t v[E], rank[E];
+#pragma unroll
+    for (int j = 0; j < E; ++j) {
+        const int32_t k = j * kWave + lane;
+        v[j] = k < c ? perm[lst[list_off(k)]] : INT32_MAX;
+        rank[j] = 0;
+    }
+#pragma unroll
+    for (int i = 0; i < E; ++i) {
+        const int32_t m = min(c - i * kWave, kWave);
+        for (int32_t l = 0; l < m; ++l) {
+            const int32_t x = __builtin_amdgcn_readlane(v[i], l);
+#pragma unroll
+            for (int j = 0; j < E; ++j) rank[j] += x < v[j];
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < E; ++j)
+        if (j * kWave + lane < c) out[rank[j]] = v[j];
+}
+
+int32_t export_cap(const sph_nbr* nb) {
+    const int32_t cap = nb->g.kernel == SPH_KERNEL_GAUSSIAN ? kListCapGauss : kListCap;
+    return (size_t)ceil_div(nb->n, (int64_t)kWave) * kWave * cap * 4 <= kListBudget ? cap : 0;
+}
+
+sph_status neighbour_scan(sph_ctx* ctx, const sph_nbr* nb, int32_t cap, int32_t* count, int32_t** list) {
+    int32_t* l = nullptr;
+    if (cap > 0) SPH_TRY(ctx->ensure_t(kList, (size_t)ceil_div(nb->n, (int64_t)kWave) * kWave * cap, &l));
+    launch_row_scan(ctx, nb, PartView{}, OpParams{}, true, count, l, cap, nullptr, nullptr);
+    SPH_LAUNCHED("k_row_scan");
+    if (list) *list = l;
+    return SPH_OK;
+}
+
+sph_status export_rows(sph_ctx* ctx, const sph_nbr* nb, int32_t cap, const int32_t* count, const int32_t* list,
+                       const int64_t* row_ptr, int32_t* cols) {
+    const int64_t blocks = ceil_div(ceil_div(nb->n, (int64_t)(kBlock / kWave)), (int64_t)kNumXcd) * kNumXcd;
+    if (cap == kListCap)
+        hipLaunchKernelGGL(k_export_rows<kListCap>, dim3((unsigned)blocks), dim3(kBlock), 0, ctx->stream, nb->n, count,
+                           list, nb->perm, row_ptr, cols);
+    else
+        hipLaunchKernelGGL(k_export_rows<kListCapGauss>, dim3((unsigned)blocks), dim3(kBlock), 0, ctx->stream, nb->n,
+                           count, list, nb->perm, row_ptr, cols);
+    SPH_LAUNCHED("k_export_rows");
+    return SPH_OK;
+}
+
 template <typename T>
 sph_status build_sell(sph_ctx* ctx, const sph_nbr* nb, const PartView& pv, const OpParams& op, Sell<T>* out,
                       const double** diag64, int64_t* nnz_out, int64_t* slots_out) {
@@ -1026,14 +1104,7 @@ sph_status build_sell(sph_ctx* ctx, const sph_nbr* nb, const PartView& pv, const
                            nb->view(), pv, op, cnt, creal, d, ws);
     } else {
         SPH_TRY(ctx->ensure_t(kList, (size_t)nslices * cap * kWave, &list));
-        constexpr int64_t kW = kBlock / kWave;
-        const int64_t wblk = windows ? ceil_div(ceil_div(n, (int64_t)kWinRows), kW) : 0;
-        // four waves per SIMD (what the scan's registers allow) on every CU
-        int32_t split = 1;
-        while (split < 8 && nb->ncell * split < 4096) split *= 2;
-        const int64_t sblk = ceil_div(ceil_div(nb->ncell * split, kW), (int64_t)kNumXcd) * kNumXcd;
-        hipLaunchKernelGGL(k_row_scan, dim3((unsigned)(wblk + sblk)), dim3(kBlock), 0, ctx->stream, nb->view(), pv, op,
-                           nb->ncell, split, creal, list, cap, (int32_t)wblk, win, reinterpret_cast<int32_t*>(nnz_dev + 2));
+        launch_row_scan(ctx, nb, pv, op, false, creal, list, cap, win, reinterpret_cast<int32_t*>(nnz_dev + 2));
     }
     hipLaunchKernelGGL(k_slice_size, dim3((unsigned)std::min<int64_t>(ceil_div(nslices * kWave, kBlock), 1024)),
                        dim3(kBlock), 0, ctx->stream,

@@ -347,6 +347,15 @@ sph_status apply_plain(sph_ctx* ctx, const sph_nbr* nb, const PartView& pv, cons
 sph_status row_diag64(sph_ctx* ctx, const sph_nbr* nb, const PartView& pv, const OpParams& op,
                       const double** diag64);
 
+// Neighbour counts (cell order) of every particle and, with cap > 0, their
+// lists of at most cap entries; export_cap: the entries that an export lists
+// per row (0: none, beyond the lists' budget).  export_rows writes the listed
+// rows of the canonical lists; rows beyond cap are left out.
+int32_t export_cap(const sph_nbr* nb);
+sph_status neighbour_scan(sph_ctx* ctx, const sph_nbr* nb, int32_t cap, int32_t* count, int32_t** list);
+sph_status export_rows(sph_ctx* ctx, const sph_nbr* nb, int32_t cap, const int32_t* count, const int32_t* list,
+                       const int64_t* row_ptr, int32_t* cols);
+
 __host__ __device__ inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
 // Looks up the device address of the allocation-free entry point's staging

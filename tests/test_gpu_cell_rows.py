@@ -66,6 +66,19 @@ def test_viscosity_update(ctx, kernel):
         _compare(w, mu, D, muo, Do)
 
 
+@pytest.mark.parametrize("kernel", [W.KERNEL_WENDLAND, W.KERNEL_GAUSSIAN])
+def test_lists(ctx, kernel):
+    # rows within, at and beyond the entries that the export lists per row
+    for w in _systems() + [dataclasses.replace(small_tank(seed=110, n=(10, 10, 6)), h=1.5)]:
+        w = dataclasses.replace(w, kernel=kernel)
+        print(f"[cells, lists] {w.name} n={w.n} kernel={kernel}", flush=True)
+        g = GpuCase(ctx, w)
+        rp, cols = g.export()
+        orp, ocols = O.neighbors(w.pos, w.period, w.h, method="brute",
+                                 support=3.0 if kernel == W.KERNEL_GAUSSIAN else 2.0)
+        assert np.array_equal(rp, orp) and np.array_equal(cols, ocols)
+
+
 @pytest.mark.parametrize("variant", [S.SPH_ROBUST, S.SPH_STANDARD])
 def test_solves_with_the_on_the_fly_operator(ctx, variant):
     for w in _systems()[1:]:
