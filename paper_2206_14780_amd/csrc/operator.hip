@@ -1186,7 +1186,7 @@ template sph_status build_sell<double>(sph_ctx*, const sph_nbr*, const PartView&
 
 
 // Launch geometry of the row kernels.
-Launch make_launch(int64_t n) {
+Launch make_launch(int64_t n, bool fp64) {
     Launch L;
     L.n = n;
     const int64_t nslices = ceil_div(n, kWave);
@@ -1204,11 +1204,17 @@ Launch make_launch(int64_t n) {
     // partials, so each thread should stream at least 8 rows of the (at most
     // 256-block) grid: the largest power-of-two block up to 1024 that keeps
     // that (512 at N = 1.16M, 1024 from N = 2.1M; measured 28.8 against
-    // 29.3 ms per step on the 1.16M tank, no change at 4.7M)
-    int32_t bs_def = 1024;
-    while (bs_def > kWave && (int64_t)bs_def * 256 * 8 > n) bs_def /= 2;
+    // 29.3 ms per step on the 1.16M tank, no change at 4.7M).  FP64 vectors,
+    // twice the bytes per row, fill blocks of up to 512 threads with two rows
+    // each (p update / close-out: 12.7 / 14.3 us with 128 threads at 328k
+    // particles, 10.6 / 14.1 with 512).  FP32 vectors would gain less, and
+    // their iterates depend on the order of the sums: a flipped rounding of a
+    // scalar to FP32 moves a solution by a part of the tolerance.
+    const int rows = fp64 ? 2 : 8;
+    int32_t bs_def = !fp64 || (int64_t)1024 * 256 * 8 <= n ? 1024 : 512;
+    while (bs_def > kWave && (int64_t)bs_def * 256 * rows > n) bs_def /= 2;
     const int32_t bs = bs_def;
-    int64_t gs = std::min<int64_t>(ceil_div(n, (int64_t)bs * 4), 256);
+    int64_t gs = std::min<int64_t>(ceil_div(n, (int64_t)bs * (fp64 ? 2 : 4)), 256);
     if (gs >= 64) gs = gs / kNumXcd * kNumXcd;
     L.grid_stream = (int32_t)std::max<int64_t>(gs, 1);
     L.block_stream = bs;
@@ -1218,7 +1224,7 @@ Launch make_launch(int64_t n) {
 template <typename T>
 sph_status apply_plain(sph_ctx* ctx, const sph_nbr* nb, const PartView& pv, const OpParams& op, int mode,
                        const Sell<T>* sell, const T* x, T* y) {
-    const Launch L = make_launch(nb->n);
+    const Launch L = make_launch(nb->n, sizeof(T) == 8);
     if (mode == SPH_OP_PAPER32) {
         if constexpr (sizeof(T) == 4)
             launch_apply_sell<T, kDotNone, T, true>(ctx->stream, L, nullptr, *sell, x, y, nullptr, nullptr, nullptr);

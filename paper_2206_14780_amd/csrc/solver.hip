@@ -194,6 +194,18 @@ __device__ inline void p_scalars(const Ctl* __restrict__ ctl, int32_t it, const 
     o.reason = reason;
 }
 
+// The control block as earlier kernels left it, copied to LDS beside the loads
+// of the partials: p_scalars would otherwise fetch its two dozen fields one
+// after the other.  Read after a barrier.
+struct CtlCopy {
+    static_assert(sizeof(Ctl) % 4 == 0, "whole words");
+    alignas(8) int32_t w[sizeof(Ctl) / 4];
+    __device__ void load(const Ctl* c) {
+        for (int i = threadIdx.x; i < (int)(sizeof(Ctl) / 4); i += blockDim.x) w[i] = reinterpret_cast<const int32_t*>(c)[i];
+    }
+    __device__ const Ctl* get() const { return reinterpret_cast<const Ctl*>(w); }
+};
+
 // CG: dw (null: 1) weighs the partials of rho = <r, r>_D written to
 // part_rho, taken after any restart copy (the r that p is built from).
 template <typename T, bool KH = false>
@@ -204,23 +216,26 @@ __global__ __launch_bounds__(kMaxBlock) void k_pupd(Ctl* __restrict__ ctl, int32
                                                     const T* __restrict__ ap, const T* __restrict__ rt,
                                                     double* __restrict__ hist, int32_t* __restrict__ stallhist,
                                                     const double* __restrict__ dw, double* __restrict__ part_rho) {
-    if (ctl->halt) return;
     __shared__ double lds[2 * kKp * kMaxWaves];
+    __shared__ CtlCopy copy;
+    const int32_t halt = ctl->halt;
+    copy.load(ctl);
     double red[kKp];
-    reduce_partials_kh<kKp, KH>(part, nblk, red, lds);
+    if (!reduce_partials_kh<kKp, KH>(part, nblk, red, lds, [&] { return halt != 0; })) return;
     rsc_all(sc, red);
+    const Ctl* old = copy.get();  // (the block's sum has passed its barriers)
     const int32_t j = it - 1;
     // periodic FP64 true residual of iteration j, unless a host-issued check
     // already covered it
     const bool check = sc.true_res_period > 0 && j > 0 && j % sc.true_res_period == 0 &&
-                       ctl->host_checked_iter != j;
+                       old->host_checked_iter != j;
     double tr[3] = {0.0, 0.0, 0.0};
     if (check) {
         reduce_partials<3>(part_tr, sc.tr_blocks, tr, lds);
         rsc_all(sc, tr);
     }
     PScalars s;
-    p_scalars(ctl, it, sc, red, tr, check, s);
+    p_scalars(old, it, sc, red, tr, check, s);
     const int cur = it & 1;
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         for (int c = 0; c < 3; ++c) {
@@ -262,7 +277,7 @@ __global__ __launch_bounds__(kMaxBlock) void k_pupd(Ctl* __restrict__ ctl, int32
     const bool use_ap = !textbook ? (s.ap[0] != 0.0 || s.ap[1] != 0.0 || s.ap[2] != 0.0) : use_p;
     const bool any_rs = s.restart[0] | s.restart[1] | s.restart[2];
     double om[3];
-    for (int c = 0; c < 3; ++c) om[c] = !textbook ? 0.0 : (it > 1 ? ctl->omega[j & 1][c] : 1.0);
+    for (int c = 0; c < 3; ++c) om[c] = !textbook ? 0.0 : (it > 1 ? old->omega[j & 1][c] : 1.0);
     double acc[3] = {0.0, 0.0, 0.0};
     float cmp[3] = {0.f, 0.f, 0.f};
     const int64_t bid = xcd_block(blockIdx.x, gridDim.x);
@@ -310,21 +325,24 @@ __global__ __launch_bounds__(kMaxBlock) void k_supd(Ctl* __restrict__ ctl, int32
                                                     const double* __restrict__ part, int32_t nblk, int64_t n,
                                                     const T* __restrict__ r, const T* __restrict__ ap,
                                                     T* __restrict__ s) {
-    if (ctl->halt) return;
     __shared__ double lds[2 * 3 * kMaxWaves];
-    double red[3];
-    reduce_partials_kh<3, KH>(part, nblk, red, lds);
-    rsc_all(sc, red);
     const int cur = it & 1;
-    double al[3];
+    const int32_t halt = ctl->halt;
+    double gam[3], red[3];
     int32_t stall[3];
+    for (int c = 0; c < 3; ++c) {
+        gam[c] = ctl->gam[cur][c];
+        stall[c] = ctl->stall0[cur][c];
+    }
+    if (!reduce_partials_kh<3, KH>(part, nblk, red, lds, [&] { return halt != 0; })) return;
+    rsc_all(sc, red);
+    double al[3];
     for (int c = 0; c < 3; ++c) {
         double d = red[c];
         if (it == sc.force_stall_iter && c == sc.force_stall_comp) d = 0.0;
         red[c] = d;
-        stall[c] = ctl->stall0[cur][c];
         double a = 0.0;
-        if (d != 0.0 && finite_d(d)) a = rsc(sc, ctl->gam[cur][c] / d);
+        if (d != 0.0 && finite_d(d)) a = rsc(sc, gam[c] / d);
         if (!finite_d(a) || d == 0.0 || !finite_d(d)) {
             a = 0.0;
             stall[c] = 1;
@@ -359,25 +377,28 @@ __global__ __launch_bounds__(kMaxBlock) void k_close(Ctl* __restrict__ ctl, int3
                                                      const T* __restrict__ s, const T* __restrict__ as,
                                                      T* __restrict__ r, const T* __restrict__ rh0,
                                                      double* __restrict__ part_out) {
-    if (ctl->halt) return;
     __shared__ double lds[2 * kKp * kMaxWaves];
-    double red[KA];
-    reduce_partials_kh<KA, KH>(part, nblk, red, lds);
-    rsc_all(sc, red);
     const int cur = it & 1;
-    double om[3], al[3];
+    const int32_t halt = ctl->halt;
+    double om[3], al[3], tau2[3], red[KA];
     int32_t stall[3];
+    for (int c = 0; c < 3; ++c) {
+        al[c] = ctl->alpha[cur][c];
+        stall[c] = ctl->stallA[cur][c];
+        tau2[c] = ctl->tau2[c];
+    }
+    if (!reduce_partials_kh<KA, KH>(part, nblk, red, lds, [&] { return halt != 0; })) return;
+    rsc_all(sc, red);
     for (int c = 0; c < 3; ++c) {
         const double ts = red[c], tt = red[3 + c];
         double w = 0.0;
         if (tt != 0.0) w = rsc(sc, ts / tt);
         if (!finite_d(w)) w = 0.0;
-        stall[c] = ctl->stallA[cur][c] | (w == 0.0 ? 1 : 0);
+        stall[c] |= w == 0.0 ? 1 : 0;
         if constexpr (KA == 9) {
-            if (red[6 + c] < ctl->tau2[c]) w = 0.0;  // r_star already meets the threshold
+            if (red[6 + c] < tau2[c]) w = 0.0;  // r_star already meets the threshold
         }
         om[c] = w;
-        al[c] = ctl->alpha[cur][c];
     }
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         for (int c = 0; c < 3; ++c) {
@@ -436,11 +457,11 @@ __global__ __launch_bounds__(kMaxBlock) void k_cg_close(Ctl* __restrict__ ctl, i
                                                         const T* __restrict__ ap, T* __restrict__ r,
                                                         const double* __restrict__ dw,
                                                         double* __restrict__ part_out) {
-    if (ctl->halt) return;
     __shared__ double lds[2 * kKp * kMaxWaves];
+    const int32_t halt = ctl->halt;
     double rho[3], pap[3];
-    reduce_partials_kh<3, KH>(part_rho, nrho, rho, lds);
-    reduce_partials_kh<3, KH>(part_pap, npap, pap, lds);
+    if (!reduce_partials_kh<3, KH>(part_rho, nrho, rho, lds, [&] { return halt != 0; })) return;
+    reduce_partials_kh<3, KH>(part_pap, npap, pap, lds, [] { return false; });
     rsc_all(sc, rho);
     rsc_all(sc, pap);
     const int cur = it & 1;
@@ -584,7 +605,7 @@ __global__ __launch_bounds__(kMaxBlock) void k_check_finish(Ctl* __restrict__ ct
                                                             int32_t nblk, SolveConst sc) {
     __shared__ double lds[2 * 6 * kMaxWaves];
     double red[6];
-    reduce_partials_kh<6, KH>(part, nblk, red, lds);
+    reduce_partials_kh<6, KH>(part, nblk, red, lds, [] { return false; });
     rsc_all(sc, red);
     if (threadIdx.x != 0) return;
     for (int c = 0; c < 3; ++c) {
@@ -791,7 +812,7 @@ sph_status solve_impl(sph_ctx* ctx, const sph_nbr* nb, const sph_particles* part
     S.op = OpParams{vp->dt, vp->wall, vp->avg, vp->jacobi ? 1 : 0};
     S.op.f32cell = KH ? 1 : 0;
     const int64_t n = nb->n;
-    S.L = make_launch(n);
+    S.L = make_launch(n, sizeof(T) == 8);
     const Launch& L = S.L;
     hipEvent_t e0 = ctx->ev[0], e1 = ctx->ev[1], e2 = ctx->ev[2];
     SPH_HIP(hipEventRecord(e0, ctx->stream));

@@ -331,17 +331,39 @@ __device__ inline void block_sum(double (&v)[K], double* lds) {
     __syncthreads();
 }
 
-// Sums K partials per block written by a previous kernel:
-// part[blk * K + k], blk < nblk.  Every block computes the same result.
+// A thread's share of K partials per block written by a previous kernel,
+// part[blk * K + k], blk < nblk, added in block order; four blocks' loads are
+// in flight at a time.
 template <int K>
-__device__ inline void reduce_partials(const double* __restrict__ part, int nblk, double (&out)[K],
-                                       double* lds) {
+__device__ inline void load_partials(const double* __restrict__ part, int nblk, double (&out)[K]) {
+    constexpr int U = 4;
 #pragma unroll
     for (int k = 0; k < K; ++k) out[k] = 0.0;
-    for (int b = threadIdx.x; b < nblk; b += blockDim.x) {
+    const int step = (int)blockDim.x;
+    int b = threadIdx.x;
+    for (; b + (U - 1) * step < nblk; b += U * step) {
+        double v[U][K];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int k = 0; k < K; ++k) v[u][k] = part[(int64_t)(b + u * step) * K + k];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int k = 0; k < K; ++k) out[k] += v[u][k];
+    }
+    for (; b < nblk; b += step) {
 #pragma unroll
         for (int k = 0; k < K; ++k) out[k] += part[(int64_t)b * K + k];
     }
+}
+
+// Sums K partials per block written by a previous kernel.  Every block
+// computes the same result.
+template <int K>
+__device__ inline void reduce_partials(const double* __restrict__ part, int nblk, double (&out)[K],
+                                       double* lds) {
+    load_partials<K>(part, nblk, out);
     block_sum<K>(out, lds);
 }
 
@@ -471,12 +493,17 @@ __device__ inline void write_partials_kh(double (&v)[K], float (&cmp)[K], double
 }
 
 // reduce_partials, or (KH) the compensated FP32 sum of the partials.
-template <int K, bool KH>
-__device__ inline void reduce_partials_kh(const double* __restrict__ part, int nblk, double (&out)[K],
-                                          double* lds) {
+// stop(), asked between the thread's loads and the block's sum, ends it early
+// (the same for the whole block): false is then returned.
+template <int K, bool KH, typename F>
+__device__ inline bool reduce_partials_kh(const double* __restrict__ part, int nblk, double (&out)[K], double* lds,
+                                          F&& stop) {
     if constexpr (!KH) {
-        reduce_partials<K>(part, nblk, out, lds);
+        load_partials<K>(part, nblk, out);
+        if (stop()) return false;
+        block_sum<K>(out, lds);
     } else {
+        if (stop()) return false;
         float cmp[K];
 #pragma unroll
         for (int k = 0; k < K; ++k) {
@@ -487,6 +514,7 @@ __device__ inline void reduce_partials_kh(const double* __restrict__ part, int n
         }
         block_sum_kahan<K>(out, cmp, lds);
     }
+    return true;
 }
 
 // XCD-aware block order: the hardware hands consecutive block ids to the 8

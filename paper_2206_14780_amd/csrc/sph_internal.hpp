@@ -229,7 +229,7 @@ struct Launch {
     int32_t block_stream;  // threads per streaming block
 };
 
-Launch make_launch(int64_t n);
+Launch make_launch(int64_t n, bool fp64);
 
 // ---------------------------------------------------------------------------
 // Device workspace: named, monotonically growing allocations of a context.
