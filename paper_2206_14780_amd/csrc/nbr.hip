@@ -157,13 +157,46 @@ __global__ __launch_bounds__(kBlock) void k_scatter(int64_t n, const int32_t* __
 }
 
 // The scatter above leaves each cell in arrival order; sort every cell by
-// original index so the layout is deterministic.
+// original index so the layout is deterministic.  Bounded by the chain of
+// dependent accesses: one wave per cell loads up to kSortWave particles at
+// once and ranks them against each other in registers (n steps of one readlane
+// and a compare per 64 particles).  Against one thread's insertion sort in
+// global memory: 57 -> 3.7 us at 1.5k particles, 66 -> 5.7 us at 128k, and at
+// 33.7M, where bandwidth is in reach, 0.66 ms.  A fuller cell, which a smoothing
+// length suited to the spacing does not make, is sorted by insertion.
+constexpr int kSortWave = 4 * kWave;
 __global__ __launch_bounds__(kBlock) void k_sort_cells(int64_t ncell,
                                                        const int32_t* __restrict__ cell_start,
                                                        int32_t* __restrict__ perm) {
-    const int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    constexpr int E = kSortWave / kWave;
+    const int lane = threadIdx.x & (kWave - 1);
+    const int64_t c = (int64_t)blockIdx.x * (kBlock / kWave) + threadIdx.x / kWave;
     if (c >= ncell) return;
-    const int32_t b = cell_start[c], e = cell_start[c + 1];
+    const int32_t b = __builtin_amdgcn_readfirstlane(cell_start[c]), e = __builtin_amdgcn_readfirstlane(cell_start[c + 1]);
+    const int32_t n = e - b;
+    if (n <= 1) return;
+    if (n <= kSortWave) {
+        int32_t v[E], rank[E];
+#pragma unroll
+        for (int j = 0; j < E; ++j) {
+            v[j] = j * kWave + lane < n ? perm[b + j * kWave + lane] : INT32_MAX;
+            rank[j] = 0;
+        }
+#pragma unroll
+        for (int i = 0; i < E; ++i) {
+            const int32_t m = min(n - i * kWave, kWave);
+            for (int32_t l = 0; l < m; ++l) {
+                const int32_t x = __builtin_amdgcn_readlane(v[i], l);
+#pragma unroll
+                for (int j = 0; j < E; ++j) rank[j] += x < v[j];
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < E; ++j)
+            if (j * kWave + lane < n) perm[b + rank[j]] = v[j];
+        return;
+    }
+    if (lane != 0) return;
     for (int32_t i = b + 1; i < e; ++i) {
         int32_t v = perm[i];
         int32_t j = i - 1;
@@ -338,7 +371,7 @@ extern "C" sph_status sph_build_neighbors(sph_ctx* ctx, const sph_particles* p, 
     if ((e = hipMemsetAsync(count, 0, sizeof(int32_t) * ncell, ctx->stream)) != hipSuccess) return hip_err("memset");
     if ((e = hipMemsetAsync(fill, 0, sizeof(int32_t) * ncell, ctx->stream)) != hipSuccess) return hip_err("memset");
     const unsigned gp = (unsigned)ceil_div(n, kBlock);
-    const unsigned gc = (unsigned)ceil_div(ncell, kBlock);
+    const unsigned gc = (unsigned)ceil_div(ncell, kBlock / kWave);
     hipLaunchKernelGGL(k_cell_of, dim3(gp), dim3(kBlock), 0, ctx->stream, n, p->x, p->y, p->z, g, cell, count);
     if ((e = hipGetLastError()) != hipSuccess) return hip_err("k_cell_of");
     sph_status st = scan_i32(ctx, count, nb->cell_start, ncell);

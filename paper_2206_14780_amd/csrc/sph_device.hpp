@@ -499,6 +499,8 @@ template <int K, bool KH, typename F>
 __device__ inline bool reduce_partials_kh(const double* __restrict__ part, int nblk, double (&out)[K], double* lds,
                                           F&& stop) {
     if constexpr (!KH) {
+        // (many partials: not for a launch that ends here)
+        if (nblk > 8 * (int)blockDim.x && stop()) return false;
         load_partials<K>(part, nblk, out);
         if (stop()) return false;
         block_sum<K>(out, lds);
