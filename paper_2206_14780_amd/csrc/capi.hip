@@ -49,10 +49,20 @@ extern "C" sph_status sph_create(sph_ctx** out, int32_t device, void* hip_stream
     sph_ctx* ctx = new sph_ctx();
     ctx->device = device;
     ctx->stream = static_cast<hipStream_t>(hip_stream);
-    if (hipHostMalloc(&ctx->host_mail, sph::kHostMailBytes, hipHostMallocDefault) != hipSuccess) {
+    // coherent: kernels write the mail while the host reads it
+    void* mail = nullptr;
+    if (hipHostMalloc(&mail, sizeof(sph::HostMail), hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess) {
         delete ctx;
         return SPH_E_OOM;
     }
+    ctx->host_mail = static_cast<sph::HostMail*>(mail);
+    void* mail_dev = nullptr;
+    if (hipHostGetDevicePointer(&mail_dev, mail, 0) != hipSuccess) {
+        sph_destroy(ctx);
+        return SPH_E_HIP;
+    }
+    ctx->mail_dev = static_cast<sph::HostMail*>(mail_dev);
+    ctx->host_mail->mail.word = 0;
     for (auto& e : ctx->ev) {
         if (hipEventCreate(&e) != hipSuccess) {
             sph_destroy(ctx);

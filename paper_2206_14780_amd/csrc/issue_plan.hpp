@@ -10,9 +10,8 @@
 
 namespace sph {
 
-// The fields of the solver's control block that the host polls between
-// batches of iterations, in one contiguous copy: residuals, tolerances,
-// states, iteration and halt.
+// What the host knows of the solver's control block between iterations:
+// residuals, tolerances, states, iteration and halt.
 struct CtlPoll {
     double rr[3];
     double bb[3];

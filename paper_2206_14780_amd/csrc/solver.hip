@@ -22,6 +22,7 @@
 // the control block.  All inner products and scalars are FP64.
 #include <algorithm>
 #include <cfloat>
+#include <chrono>
 #include <cmath>
 
 #include "mlp.hpp"
@@ -268,6 +269,15 @@ __global__ __launch_bounds__(kMaxBlock) void k_pupd(Ctl* __restrict__ ctl, int32
         ctl->halt_reason = s.reason;
         ctl->iter = s.reason ? j : it;
         if (s.reason) ctl->halt = 1;
+        uint64_t word = (uint64_t)(uint32_t)(s.reason ? j : it) | (uint64_t)s.reason << kMailReason |
+                        (uint64_t)s.nonfinite << kMailNonfinite | (uint64_t)s.checked << kMailChecked |
+                        (uint64_t)sc.tag << kMailTag;
+        for (int c = 0; c < 3; ++c) {
+            word |= (uint64_t)s.state[c] << (kMailState + 2 * c);
+            __hip_atomic_store(&sc.mail->rr[c], s.rr[c], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+            __hip_atomic_store(&sc.mail->tau2[c], s.tau2[c], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        }
+        __hip_atomic_store(&sc.mail->word, word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     }
     if (s.reason) return;
     // body: p update; a zero coefficient skips its vector (the robust form
@@ -661,10 +671,29 @@ using namespace sph;
 
 namespace {
 
-sph_status read_ctl(sph_ctx* ctx, const Ctl* d, Ctl* h) {
-    SPH_HIP(hipMemcpyAsync(h, d, sizeof(Ctl), hipMemcpyDeviceToHost, ctx->stream));
-    SPH_HIP(hipStreamSynchronize(ctx->stream));
-    return SPH_OK;
+// The word that the p updates of a round mail, once it differs from *last.
+// Ends for every state of the stream: now and then the host asks whether the
+// stream has drained or failed.
+sph_status wait_mail(sph_ctx* ctx, uint32_t tag, uint64_t* last) {
+    const SolveMail& mail = ctx->host_mail->mail;
+    bool drained = false;
+    auto next = std::chrono::steady_clock::now() + std::chrono::microseconds(500);
+    for (uint32_t spin = 1;; ++spin) {
+        const uint64_t w = __atomic_load_n(&mail.word, __ATOMIC_ACQUIRE);
+        if ((uint32_t)(w >> kMailTag) == tag && w != *last) {
+            *last = w;
+            return SPH_OK;
+        }
+        if (drained) return ctx->fail(SPH_E_HIP, "visc_solve: iterations ended without a word from them");
+        if (spin % 64 == 0 && std::chrono::steady_clock::now() >= next) {
+            const hipError_t e = hipStreamQuery(ctx->stream);
+            if (e == hipSuccess) drained = true;  // (read the mail once more)
+            else if (e != hipErrorNotReady) return ctx->hip_fail(e, "visc_solve: iteration kernels");
+            else (void)hipGetLastError();
+            next = std::chrono::steady_clock::now() + std::chrono::microseconds(500);
+        }
+        __builtin_ia32_pause();
+    }
 }
 
 // T: precision of the operator and of the Krylov vectors; X: precision of
@@ -882,7 +911,7 @@ sph_status solve_impl(sph_ctx* ctx, const sph_nbr* nb, const sph_particles* part
     if (o->warm_params) {
         // learned start (x_l in s, its residual in as) against the plain
         // start (x, its residual in tmp), per component by true r.r
-        SPH_HIP(hipEventRecord(ctx->ev[5], ctx->stream));
+        SPH_HIP(hipEventRecord(ctx->ev[3], ctx->stream));
         SPH_TRY(ctx->ensure_t(kWarmInfo, kWiSize, &winfo));
         // u: warm_u, or per null component the initial guess (x0_given) or
         // b.  When u is the plain start itself and the matrix is cached, the
@@ -923,7 +952,7 @@ sph_status solve_impl(sph_ctx* ctx, const sph_nbr* nb, const sph_particles* part
                                    S.x, S.s, S.as, S.b, S.tmp, winfo)));
         r0 = S.tmp;
         S.launches += 11;
-        SPH_HIP(hipEventRecord(ctx->ev[6], ctx->stream));
+        SPH_HIP(hipEventRecord(ctx->ev[4], ctx->stream));
     } else if (o->x0_given) {
         SPH_TRY(gather_vec3<X>(ctx, nb, (const void* const*)xout, S.x));
     } else {
@@ -948,14 +977,26 @@ sph_status solve_impl(sph_ctx* ctx, const sph_nbr* nb, const sph_particles* part
     SPH_LAUNCHED("solve setup");
     SPH_HIP(hipEventRecord(e1, ctx->stream));
 
-    // Iterate.  The host issues iterations in batches (sized by IssuePlan)
-    // and reads the device's control block one batch behind; kernels issued
-    // after a halt return at once.
-    CtlPoll* mail = static_cast<CtlPoll*>(ctx->host_mail);
+    // Iterate.  Each p update mails its outcome (SolveMail); the host keeps at
+    // most kAhead iterations queued beyond the one whose p update it has seen
+    // and, near the halt that IssuePlan forecasts, none, which leaves no gap:
+    // the p update is the first kernel of its iteration, and the others run
+    // while the host queues the next.  Kernels issued after a halt return at
+    // once, but cost a launch each: with polls by copy and event, one batch
+    // behind, a solve of 8 iterations at 1.5k particles issued 20.  Round
+    // trips at the end: with at most kEagerRows rows the solution is written
+    // before the host knows that no further round follows (a scatter of some
+    // 10 us against a round trip of 20).
+    constexpr int32_t kAhead = 2;
+    constexpr int64_t kEagerRows = 1 << 18;
+    const int32_t most = o->poll_every > 0 ? o->poll_every : kAhead;
     IssuePlan plan(o->poll_every > 0 ? o->poll_every : 8);
     const int32_t last_it = o->max_iter + 1;  // P of this iteration always halts
     int32_t j = 0;
-    Ctl hctl;
+    int32_t checked_j = -1;  // last iteration whose true residual a host-issued check took
+    HostMail& host = *ctx->host_mail;
+    const Ctl& hctl = host.ctl;
+    S.sc.mail = &ctx->mail_dev->mail;
     for (;;) {
         const int32_t j0 = j;
         int32_t it = j + 1;
@@ -963,66 +1004,87 @@ sph_status solve_impl(sph_ctx* ctx, const sph_nbr* nb, const sph_particles* part
             // the round starts after the residual check of iteration j: the
             // state of the pupd of j + 1, with the true residuals
             CtlPoll m;
-            std::memcpy(&m, &hctl.rr, sizeof(CtlPoll));
-            for (int c = 0; c < 3; ++c) m.rr[c] = hctl.trr[c];
+            std::memcpy(m.rr, hctl.trr, sizeof(m.rr));
+            std::memcpy(m.bb, hctl.bb, sizeof(m.bb));
+            std::memcpy(m.tau2, hctl.tau2, sizeof(m.tau2));
+            std::memcpy(m.state, hctl.state, sizeof(m.state));
             m.iter = j + 1;
             m.halt = 0;
             plan.restart(m);
         }
-        int pend[2], npend = 0, batch = 0;
-        bool halted = false;
-        while (!halted) {
-            const int k = it <= last_it && npend < 2 ? plan.batch(it, npend > 0) : 0;
-            if (k > 0) {
-                for (int q = 0; q < k && it <= last_it; ++q) SPH_TRY(S.iteration(it++));
-                SPH_LAUNCHED("iteration kernels");
-                const int slot = batch++ & 1;
-                SPH_HIP(hipMemcpyAsync(&mail[slot], &S.ctl->rr, sizeof(CtlPoll), hipMemcpyDeviceToHost,
-                                       ctx->stream));
-                SPH_HIP(hipEventRecord(ctx->ev[3 + slot], ctx->stream));
-                pend[npend++] = slot;
+        S.sc.tag = ++ctx->mail_tag & 0xFFFF;
+        int32_t seen = j;  // last iteration whose p update has been seen
+        uint64_t word = 0;
+        int32_t reason = 0;
+        while (!reason) {
+            const int32_t ahead = it - 1 - seen;
+            const int32_t k = it <= last_it && ahead < most ? std::min(plan.batch(it, ahead > 0), most - ahead) : 0;
+            for (int32_t q = 0; q < k && it <= last_it; ++q) SPH_TRY(S.iteration(it++));
+            if (k > 0) SPH_LAUNCHED("iteration kernels");
+            else if (ahead == 0) return ctx->fail(SPH_E_HIP, "visc_solve: iteration issue ended without a halt");
+            const uint64_t now = __atomic_load_n(&host.mail.word, __ATOMIC_ACQUIRE);
+            if (k > 0 && (now == word || (uint32_t)(now >> kMailTag) != S.sc.tag)) continue;
+            SPH_TRY(wait_mail(ctx, S.sc.tag, &word));
+            reason = (int32_t)(word >> kMailReason & 7);
+            CtlPoll m{};
+            m.iter = (int32_t)(uint32_t)word;
+            m.halt = reason != 0;
+            for (int c = 0; c < 3; ++c) {
+                m.rr[c] = host.mail.rr[c];
+                m.tau2[c] = host.mail.tau2[c];
+                m.state[c] = (int32_t)(word >> (kMailState + 2 * c) & 3);
             }
-            // read the older poll once two are in flight, or when nothing is
-            // to be issued before it
-            if (npend == 2 || (npend > 0 && k == 0)) {
-                const int slot = pend[0];
-                pend[0] = pend[1];
-                --npend;
-                SPH_HIP(hipEventSynchronize(ctx->ev[3 + slot]));
-                if (mail[slot].halt) halted = true;
-                else plan.observe(mail[slot]);
-            } else if (it > last_it && npend == 0) {
-                halted = true;
-            }
+            seen = m.iter;
+            plan.observe(m);
         }
         S.issued_iters += (it - 1) - j0;
-        SPH_TRY(read_ctl(ctx, S.ctl, &hctl));
-        if (hctl.nonfinite) return ctx->fail(SPH_E_NONFINITE, "visc_solve: non-finite right-hand side");
-        if (!hctl.halt) return ctx->fail(SPH_E_HIP, "visc_solve: iteration issue ended without a halt");
-        j = hctl.iter;
+        j = seen;  // (of a halt: the iteration before the p update's)
+        if (word >> kMailNonfinite & 1) {
+            SPH_HIP(hipStreamSynchronize(ctx->stream));
+            return ctx->fail(SPH_E_NONFINITE, "visc_solve: non-finite right-hand side");
+        }
         S.round_end.push_back(j);
         ++S.round;
-        if ((hctl.halt_reason & kHaltNoProg) && hctl.dev_checked_iter != j && hctl.host_checked_iter != j) {
+        const bool covered = (word >> kMailChecked & 1) || checked_j == j;
+        const bool check = (reason & kHaltNoProg) && !covered;
+        if (check) {
             S.host_check();
+            checked_j = j;
             SPH_LAUNCHED("residual check");
-            SPH_TRY(read_ctl(ctx, S.ctl, &hctl));
+        } else if (!covered) {
+            // the iteration limit: FP64 true residual of the final x for the report
+            S.true_residual(nullptr, S.pchk);
+            hipLaunchKernelGGL(k_final_trr, dim3(1), dim3(kMaxBlock), 0, ctx->stream, S.ctl, S.pchk, L.grid_apply);
+            S.launches += 1;
         }
+        // only a check lets a component go on
+        auto finish = [&]() -> sph_status {
+            SPH_TRY(scatter_vec3<X>(ctx, nb, S.x, xout));
+            SPH_LAUNCHED("solve finish");
+            SPH_HIP(hipEventRecord(e2, ctx->stream));
+            return SPH_OK;
+        };
+        const bool eager = !check || n <= kEagerRows;
+        if (eager) SPH_TRY(finish());
+        SPH_HIP(hipMemcpyAsync(&host.ctl, S.ctl, sizeof(Ctl), hipMemcpyDeviceToHost, ctx->stream));
+        const int32_t stalls = std::min({j + 1, hist_rows, kMailStallRows});
+        SPH_HIP(hipMemcpyAsync(host.stall, S.stallhist, sizeof(int32_t) * 3 * (size_t)stalls, hipMemcpyDeviceToHost,
+                               ctx->stream));
+        SPH_HIP(hipStreamSynchronize(ctx->stream));
+        if (!hctl.halt || hctl.iter != j)
+            return ctx->fail(SPH_E_HIP, "visc_solve: iteration issue ended without a halt");
         bool any_prog = false;
         for (int c = 0; c < 3; ++c) any_prog |= hctl.state[c] == SPH_PROGRESSING;
-        if (!any_prog || j >= o->max_iter) break;
+        if (!any_prog || j >= o->max_iter) {
+            if (!eager) {
+                SPH_TRY(finish());
+                SPH_HIP(hipStreamSynchronize(ctx->stream));
+            }
+            break;
+        }
         SPH_HIP(hipMemsetAsync(&S.ctl->halt, 0, sizeof(int32_t), ctx->stream));
     }
-    // FP64 true residual of the final x for the report, unless the last check covered it
-    if (hctl.dev_checked_iter != j && hctl.host_checked_iter != j) {
-        S.true_residual(nullptr, S.pchk);
-        hipLaunchKernelGGL(k_final_trr, dim3(1), dim3(kMaxBlock), 0, ctx->stream, S.ctl, S.pchk, L.grid_apply);
-        S.launches += 1;
-    }
-    SPH_TRY(scatter_vec3<X>(ctx, nb, S.x, xout));
     ++S.launches;
-    SPH_LAUNCHED("solve finish");
-    SPH_HIP(hipEventRecord(e2, ctx->stream));
-    SPH_TRY(read_ctl(ctx, S.ctl, &hctl));
 
     rep->iters = hctl.iter;
     int any_prog = 0, any_stall = 0;
@@ -1038,9 +1100,16 @@ sph_status solve_impl(sph_ctx* ctx, const sph_nbr* nb, const sph_particles* part
     rep->n_true_checks = hctl.n_true_checks;
     rep->n_replaced = hctl.n_replaced;
     const int32_t rows = std::min(hctl.iter + 1, hist_rows);
-    std::vector<int32_t> sh((size_t)rows * 3);
-    SPH_HIP(hipMemcpyAsync(sh.data(), S.stallhist, sizeof(int32_t) * sh.size(), hipMemcpyDeviceToHost, ctx->stream));
-    SPH_HIP(hipStreamSynchronize(ctx->stream));
+    // (the flags came with the control block, unless they are more than the pinned copy holds)
+    std::vector<int32_t> all;
+    const int32_t* sh = host.stall;
+    if (rows > kMailStallRows) {
+        all.resize((size_t)rows * 3);
+        SPH_HIP(hipMemcpyAsync(all.data(), S.stallhist, sizeof(int32_t) * all.size(), hipMemcpyDeviceToHost,
+                               ctx->stream));
+        SPH_HIP(hipStreamSynchronize(ctx->stream));
+        sh = all.data();
+    }
     for (int c = 0; c < 3; ++c) {
         int32_t cnt = 0;
         for (int32_t q = 1; q < rows; ++q) cnt += sh[(size_t)q * 3 + c];
@@ -1085,7 +1154,7 @@ sph_status solve_impl(sph_ctx* ctx, const sph_nbr* nb, const sph_particles* part
         }
         rep->warm_scale = wi[kWiU];
         float ms = 0.f;
-        SPH_HIP(hipEventElapsedTime(&ms, ctx->ev[5], ctx->ev[6]));
+        SPH_HIP(hipEventElapsedTime(&ms, ctx->ev[3], ctx->ev[4]));
         rep->warm_ms = ms;
     }
     rep->status = any_prog ? SPH_NOT_CONVERGED : (any_stall ? SPH_STALLED : SPH_OK);

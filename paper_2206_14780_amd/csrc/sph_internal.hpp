@@ -197,13 +197,29 @@ struct Ctl {
     int32_t nonfinite;
 };
 
-// CtlPoll (issue_plan.hpp) mirrors a contiguous run of Ctl.
-static_assert(offsetof(Ctl, halt_reason) + sizeof(int32_t) - offsetof(Ctl, rr) == sizeof(CtlPoll) &&
-                  offsetof(Ctl, state) - offsetof(Ctl, rr) == offsetof(CtlPoll, state) &&
-                  offsetof(Ctl, halt) - offsetof(Ctl, rr) == offsetof(CtlPoll, halt),
-              "CtlPoll mirrors a contiguous run of Ctl");
-constexpr size_t kHostMailBytes = 256;  // two CtlPoll slots
-static_assert(2 * sizeof(CtlPoll) <= kHostMailBytes, "mailbox holds two polls");
+// What the p update of each iteration tells the host, in pinned host memory
+// that the kernel writes and the host reads with no copy or event between.
+// The words are stored one by one with no order among them: `word` alone
+// decides anything (one 8-byte store), the residuals only feed the forecast
+// of the halt.
+struct SolveMail {
+    // [0, 32) iteration; from 32: two bits of state per component, three bits
+    // of halt reason (0: going on), a non-finite right-hand side, an FP64
+    // check by this p update; [48, 64) tag of the round
+    uint64_t word;
+    double rr[3];
+    double tau2[3];
+};
+constexpr int kMailState = 32, kMailReason = 38, kMailNonfinite = 41, kMailChecked = 42, kMailTag = 48;
+
+// The context's pinned host memory: the mail and what a solve copies back
+// when it ends (per iteration: three stall flags).
+constexpr int32_t kMailStallRows = 4096;
+struct HostMail {
+    SolveMail mail;
+    alignas(64) Ctl ctl;
+    int32_t stall[3 * kMailStallRows];
+};
 
 // Constants of one solve, passed by value to the iteration kernels.
 struct SolveConst {
@@ -218,6 +234,8 @@ struct SolveConst {
     int32_t force_stall_comp;
     int32_t hist_cap;      // rows of the device history arrays
     int32_t fp32;          // 1: every reduced inner product and every scalar rounded to FP32
+    uint32_t tag;          // of the round, in the mail's word
+    SolveMail* mail;       // device address of the context's mail
 };
 
 // Launch geometry of the row kernels.
@@ -250,8 +268,10 @@ struct sph_ctx {
     std::string err;
     void* ws[sph::kNumSlots] = {};
     size_t ws_bytes[sph::kNumSlots] = {};
-    void* host_mail = nullptr;   // pinned host mailbox for polling the control block
-    hipEvent_t ev[7] = {};        // 0-2: solve timing, 3-4: halt polls, 5-6: learned start
+    sph::HostMail* host_mail = nullptr;  // pinned; mail_dev: its device address
+    sph::HostMail* mail_dev = nullptr;
+    uint32_t mail_tag = 0;        // of the latest round of iterations
+    hipEvent_t ev[5] = {};        // 0-2: solve timing, 3-4: learned start
     std::vector<hipEvent_t> prof_ev;  // pairs bracketing profiled launches
 
     sph_status fail(sph_status s, const std::string& what);
