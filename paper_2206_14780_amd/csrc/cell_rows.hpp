@@ -94,8 +94,45 @@ template <class B, int W>
 constexpr size_t cell_bytes(int32_t cap) {
     // positions and extras, fluid masks, and the rows' lists, which share their
     // place with the candidates' indices
-    return (size_t)cap * (24 + sizeof(typename B::X) * B::NX) + 8 * (cap / kWave) +
+    return W == 0 ? 0 : (size_t)cap * (24 + sizeof(typename B::X) * B::NX) + 8 * (cap / kWave) +
            (W * kCellRows * kCellList * 2 > cap * 4 ? W * kCellRows * kCellList * 2 : cap * 4);
+}
+
+// Whether the sums are taken a cell at a time, or by one thread per row
+// (cell_rows<0>).  Blocks pay for cells that are empty or hold a row or two,
+// as in a box that the particles fill in part: the operator (FP64) by cells /
+// by rows at 1M scattered particles with 4, 8, 21 in the mean cell: 2.57 /
+// 0.82, 1.77 / 1.23, 1.82 / 2.54 ms; at 65k with 4, 7, 16: 198 / 161, 154 / 226,
+// 152 / 400 us; Gaussian, 1M, 21, 64: 3.65 / 2.80, 4.72 / 6.49 ms; 65k, 7, 16:
+// 446 / 246, 317 / 441 us.  Cells with more candidates than a block stages at
+// once still gain while the rows alone are too few for the chip: 65k, 65 in a
+// cell, 0.62 / 1.30 ms, but 1M, 64: 7.2 / 5.9; and a few blocks do not fill it
+// either (4096 particles in 8 cells: 4.1 / 1.8 ms).
+inline bool by_cells(const sph_nbr* nb) {
+    const bool gauss = nb->g.kernel == SPH_KERNEL_GAUSSIAN, small = nb->n < (1 << 18);
+    const double mean = (double)nb->n / (double)nb->ncell;
+    if (mean < (gauss ? (small ? 12.0 : 32.0) : (small ? 5.0 : 12.0))) return false;
+    const double most = (gauss ? 1900.0 : 1024.0) / (27.0 * 1.07);
+    return mean <= most || (small && nb->ncell >= 64);
+}
+
+// cell_rows by one thread per row.
+template <class B>
+__device__ inline void row_terms(const NbrView& nv, int32_t b, const B& body) {
+    const auto r = body.row(b);
+    double acc[B::NA] = {};
+    if (r.take != kTakeNone) {
+        const Pos4 pb = nv.pos[b];
+        for_each_neighbor(nv, b, [&](int32_t a, double r2) {
+            if (r.take == kTakeFluid && !body.fluid(a)) return;
+            typename B::X v[B::NX];
+            body.stage(a, v);
+            const Pos4 pa = nv.pos[a];
+            body.term(nv.g, r, r2, disp(pb.x, pa.x, nv.g.period[0]), disp(pb.y, pa.y, nv.g.period[1]),
+                      disp(pb.z, pa.z, nv.g.period[2]), v, acc);
+        });
+    }
+    body.finish(b, r, acc);
 }
 
 // For every row of cell c: acc = sum of body.term over its neighbours, then

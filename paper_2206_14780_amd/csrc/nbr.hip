@@ -163,18 +163,14 @@ __global__ __launch_bounds__(kBlock) void k_scatter(int64_t n, const int32_t* __
 // and a compare per 64 particles).  Against one thread's insertion sort in
 // global memory: 57 -> 3.7 us at 1.5k particles, 66 -> 5.7 us at 128k, and at
 // 33.7M, where bandwidth is in reach, 0.66 ms.  A fuller cell, which a smoothing
-// length suited to the spacing does not make, is sorted by insertion.
+// length suited to the spacing does not make, is sorted by insertion.  Where
+// most cells are empty a wave looks at `per` of them at once (with one each,
+// 30M cells around 1000 particles took 1.5 ms).
 constexpr int kSortWave = 4 * kWave;
-__global__ __launch_bounds__(kBlock) void k_sort_cells(int64_t ncell,
-                                                       const int32_t* __restrict__ cell_start,
-                                                       int32_t* __restrict__ perm) {
+
+// The cell's n particles at perm[b], by one wave.
+__device__ inline void sort_cell(int32_t* __restrict__ perm, int32_t b, int32_t n, int lane) {
     constexpr int E = kSortWave / kWave;
-    const int lane = threadIdx.x & (kWave - 1);
-    const int64_t c = (int64_t)blockIdx.x * (kBlock / kWave) + threadIdx.x / kWave;
-    if (c >= ncell) return;
-    const int32_t b = __builtin_amdgcn_readfirstlane(cell_start[c]), e = __builtin_amdgcn_readfirstlane(cell_start[c + 1]);
-    const int32_t n = e - b;
-    if (n <= 1) return;
     if (n <= kSortWave) {
         int32_t v[E], rank[E];
 #pragma unroll
@@ -194,17 +190,33 @@ __global__ __launch_bounds__(kBlock) void k_sort_cells(int64_t ncell,
 #pragma unroll
         for (int j = 0; j < E; ++j)
             if (j * kWave + lane < n) perm[b + rank[j]] = v[j];
-        return;
-    }
-    if (lane != 0) return;
-    for (int32_t i = b + 1; i < e; ++i) {
-        int32_t v = perm[i];
-        int32_t j = i - 1;
-        while (j >= b && perm[j] > v) {
-            perm[j + 1] = perm[j];
-            --j;
+    } else if (lane == 0) {
+        for (int32_t i = b + 1; i < b + n; ++i) {
+            const int32_t v = perm[i];
+            int32_t j = i - 1;
+            while (j >= b && perm[j] > v) {
+                perm[j + 1] = perm[j];
+                --j;
+            }
+            perm[j + 1] = v;
         }
-        perm[j + 1] = v;
+    }
+}
+
+__global__ __launch_bounds__(kBlock) void k_sort_cells(int64_t ncell, int32_t per,
+                                                       const int32_t* __restrict__ cell_start,
+                                                       int32_t* __restrict__ perm) {
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int64_t c = ((int64_t)blockIdx.x * (kBlock / kWave) + wid) * per + lane;
+    int32_t beg = 0, len = 0;
+    if (lane < per && c < ncell) {
+        beg = cell_start[c];
+        len = cell_start[c + 1] - beg;
+    }
+    for (uint64_t todo = __ballot(len > 1); todo; todo &= todo - 1) {
+        const int l = __builtin_ctzll(todo);
+        sort_cell(perm, __builtin_amdgcn_readlane(beg, l), __builtin_amdgcn_readlane(len, l), lane);
     }
 }
 
@@ -371,7 +383,8 @@ extern "C" sph_status sph_build_neighbors(sph_ctx* ctx, const sph_particles* p, 
     if ((e = hipMemsetAsync(count, 0, sizeof(int32_t) * ncell, ctx->stream)) != hipSuccess) return hip_err("memset");
     if ((e = hipMemsetAsync(fill, 0, sizeof(int32_t) * ncell, ctx->stream)) != hipSuccess) return hip_err("memset");
     const unsigned gp = (unsigned)ceil_div(n, kBlock);
-    const unsigned gc = (unsigned)ceil_div(ncell, kBlock / kWave);
+    const int32_t per = (int32_t)std::min<int64_t>(std::max<int64_t>(16 * ncell / n, 1), kWave);
+    const unsigned gc = (unsigned)ceil_div(ncell, (int64_t)per * (kBlock / kWave));
     hipLaunchKernelGGL(k_cell_of, dim3(gp), dim3(kBlock), 0, ctx->stream, n, p->x, p->y, p->z, g, cell, count);
     if ((e = hipGetLastError()) != hipSuccess) return hip_err("k_cell_of");
     sph_status st = scan_i32(ctx, count, nb->cell_start, ncell);
@@ -380,7 +393,8 @@ extern "C" sph_status sph_build_neighbors(sph_ctx* ctx, const sph_particles* p, 
         return st;
     }
     hipLaunchKernelGGL(k_scatter, dim3(gp), dim3(kBlock), 0, ctx->stream, n, cell, nb->cell_start, fill, nb->perm);
-    hipLaunchKernelGGL(k_sort_cells, dim3(gc), dim3(kBlock), 0, ctx->stream, ncell, nb->cell_start, nb->perm);
+    hipLaunchKernelGGL(k_sort_cells, dim3(gc), dim3(kBlock), 0, ctx->stream, ncell, per, nb->cell_start,
+                       nb->perm);
     hipLaunchKernelGGL(k_gather_pos, dim3(gp), dim3(kBlock), 0, ctx->stream, n, nb->perm, cell, p->x, p->y,
                        p->z, nb->pos, nb->scell, nb->iperm);
     if ((e = hipGetLastError()) != hipSuccess) return hip_err("neighbour build kernels");

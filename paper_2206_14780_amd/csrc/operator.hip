@@ -321,7 +321,7 @@ __global__ __launch_bounds__(kBlock) void k_slice_size(int64_t n, int64_t nslice
         int32_t w = 0;
         if (r < n) {
             const int32_t c = creal[r];
-            w = cnt ? cnt[r] : windowed ? c : row_slots(nv, pv, op, (int32_t)r, c, list, cap);
+            w = windowed ? c : cnt ? cnt[r] : row_slots(nv, pv, op, (int32_t)r, c, list, cap);
             tot += c;
             longest = max(longest, c);
         }
@@ -402,7 +402,7 @@ __global__ __launch_bounds__(kBlock) void k_row_fill(NbrView nv, PartView pv, Op
 // List-based matrix build (the default).
 //
 // k_row_scan: one wave per cell finds the neighbours of the cell's rows, counts
-//   them and writes their indices.  List layout, with cap entries per row
+//   them and writes their indices (k_row_scan_rows: one thread per row does).  List layout, with cap entries per row
 //   (cap / kChunk segments): entry k of row r sits at
 //   ((r/64 * cap/kChunk + k/kChunk) * 64 + r%64) * kChunk + k%kChunk, so that
 //   a lane walking its row reads 16-byte pieces and a slice's lists lie
@@ -659,6 +659,42 @@ __global__ __launch_bounds__(kBlock) void k_row_scan(NbrView nv, PartView pv, Op
             if (on && lane % split == share) creal[row] = mine;
         }
     }
+}
+
+// The scan by one thread per row, for cells that are mostly empty or too full
+// (see launch_row_scan).  The lanes of a wave reach their k-th neighbour at
+// different points, so each collects kChunk indices in LDS and writes them as
+// one segment.
+__global__ __launch_bounds__(kBlock) void k_row_scan_rows(NbrView nv, PartView pv, OpParams op, bool all,
+                                                          int32_t* __restrict__ cnt, int32_t* __restrict__ creal,
+                                                          int32_t* __restrict__ list, int32_t cap) {
+    constexpr int kStride = kChunk + 1;  // LDS words per lane (odd: no bank conflicts)
+    __shared__ int32_t buf[kBlock * kStride];
+    const int64_t b = (int64_t)xcd_block(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x;
+    if (b >= nv.n) return;  // (each lane uses only its own LDS words)
+    const int32_t row = (int32_t)b;
+    int32_t* my = buf + threadIdx.x * kStride;
+    int32_t* out = list + list_base(b, cap);
+    SlotCounter sc;
+    const int32_t& c = sc.c;
+    const auto flush = [&](int32_t q) {
+        int4* dst = reinterpret_cast<int4*>(out + list_off(q * kChunk));
+#pragma unroll
+        for (int i = 0; i < kChunk / 4; ++i)
+            dst[i] = make_int4(my[4 * i], my[4 * i + 1], my[4 * i + 2], my[4 * i + 3]);
+    };
+    const int kind = all ? (int)kRowFluid : row_kind(pv, op, row);
+    if (kind != kRowNone)
+        for_each_neighbor(nv, row, [&](int32_t a, double) {
+            if (kind == kRowDummy && pv.type[a] != SPH_FLUID) return;
+            const int32_t e = c % kChunk;
+            my[e] = a;
+            if (e == kChunk - 1 && c < cap) flush(c / kChunk);
+            sc.add(a);
+        });
+    if (c < cap && c % kChunk) flush(c / kChunk);
+    creal[row] = c;
+    if (cnt) cnt[row] = sc.slots;
 }
 
 template <typename T, bool WIN>
@@ -986,9 +1022,33 @@ sph_status row_diag64(sph_ctx* ctx, const sph_nbr* nb, const PartView& pv, const
     return SPH_OK;
 }
 
+// Whether k_row_scan_rows scans, and the matrix keeps the delta code.  A wave
+// per cell pays for empty cells too (30M cells around 1000 particles: 4.6 ms),
+// the windows of scattered rows are many short ranges, and of rows that are
+// mostly longer than their list (the mean over the support's sphere) the
+// counts of slots are wanted.  Matrix and one product, FP64, by cells and
+// windows / by rows and delta code: 1M scattered particles with 2, 4, 8, 21 in
+// the mean cell 1.48 / 0.75, 1.27 / 1.05, 1.44 / 1.57, 10.4 / 10.6 ms, with 64
+// 29.4 / 27.3; 65k with 2, 4, 7: 196 / 180, 188 / 233, 199 / 301 us; Gaussian, 1M
+// with 8, 21: 1.73 / 1.61, 2.93 / 3.38 ms.
+static bool scan_by_rows(const sph_nbr* nb, int32_t cap) {
+    const double mean = (double)nb->n / (double)nb->ncell;
+    const double least = nb->n < (1 << 18) ? 3.0 : nb->g.kernel == SPH_KERNEL_GAUSSIAN ? 12.0 : 6.0;
+    const double row = mean * 4.19 * nb->g.cut2 * std::sqrt(nb->g.cut2) / (nb->g.cs[0] * nb->g.cs[1] * nb->g.cs[2]);
+    return mean < least || row > (cap > 0 ? cap : kListCapGauss);
+}
+
+// cnt: slots of the delta code per row (by rows only, may be null).
 static void launch_row_scan(sph_ctx* ctx, const sph_nbr* nb, const PartView& pv, const OpParams& op, bool all,
-                            int32_t* creal, int32_t* list, int32_t cap, WinRange* win, int32_t* wmax) {
+                            bool by_rows, int32_t* cnt, int32_t* creal, int32_t* list, int32_t cap, WinRange* win,
+                            int32_t* wmax) {
     constexpr int64_t kW = kBlock / kWave;
+    if (by_rows) {
+        const int64_t blocks = ceil_div(ceil_div(nb->n, (int64_t)kBlock), (int64_t)kNumXcd) * kNumXcd;
+        hipLaunchKernelGGL(k_row_scan_rows, dim3((unsigned)blocks), dim3(kBlock), 0, ctx->stream, nb->view(), pv, op,
+                           all, cnt, creal, list, cap);
+        return;
+    }
     const int64_t wblk = win ? ceil_div(ceil_div(nb->n, (int64_t)kWinRows), kW) : 0;
     // four waves per SIMD (what the scan's registers allow) on every CU
     int32_t split = 1;
@@ -1044,7 +1104,8 @@ int32_t export_cap(const sph_nbr* nb) {
 sph_status neighbour_scan(sph_ctx* ctx, const sph_nbr* nb, int32_t cap, int32_t* count, int32_t** list) {
     int32_t* l = nullptr;
     if (cap > 0) SPH_TRY(ctx->ensure_t(kList, (size_t)ceil_div(nb->n, (int64_t)kWave) * kWave * cap, &l));
-    launch_row_scan(ctx, nb, PartView{}, OpParams{}, true, count, l, cap, nullptr, nullptr);
+    launch_row_scan(ctx, nb, PartView{}, OpParams{}, true, scan_by_rows(nb, cap), nullptr, count, l, cap, nullptr,
+                    nullptr);
     SPH_LAUNCHED("k_row_scan");
     if (list) *list = l;
     return SPH_OK;
@@ -1074,13 +1135,14 @@ sph_status build_sell(sph_ctx* ctx, const sph_nbr* nb, const PartView& pv, const
     if (op.f32cell && nb->g.kernel != SPH_KERNEL_WENDLAND)
         return ctx->fail(SPH_E_ARG, "SPH_OP_PAPER32 is defined for the Wendland kernel");
     const bool legacy = env_int("SPH_BUILD_LEGACY", 0) > 0 && !op.f32cell;
-    const bool windows = !legacy;
     // list entries per row: room for every neighbour of the kernel's support
     // (int32 index + FP64 weight each) while that fits the budget
     const int32_t cap = nb->g.kernel == SPH_KERNEL_GAUSSIAN &&
                                 (size_t)nslices * kWave * kListCapGauss * 12 <= kListBudget
                             ? kListCapGauss
                             : kListCap;
+    const bool by_rows = scan_by_rows(nb, cap);
+    const bool windows = !legacy && !by_rows;
     int32_t *cnt = nullptr, *creal = nullptr, *list = nullptr;
     double *d = nullptr, *ws = nullptr, *wlist = nullptr;
     int64_t *size = nullptr, *ptr = nullptr;
@@ -1097,14 +1159,15 @@ sph_status build_sell(sph_ctx* ctx, const sph_nbr* nb, const PartView& pv, const
         SPH_TRY(ctx->ensure_t(kWin, (size_t)ceil_div(n, (int64_t)kWinRows) * kWinParts * kWinRanges, &win));
     // slice kernels: whole XCD rounds of blocks (xcd_block needs a multiple of 8)
     const dim3 slice_grid((unsigned)(ceil_div(ceil_div(nslices * kWave, kBlock), kNumXcd) * kNumXcd));
+    if (legacy || by_rows) SPH_TRY(ctx->ensure_t(kCnt, n, &cnt));
     if (legacy) {
-        SPH_TRY(ctx->ensure_t(kCnt, n, &cnt));
         SPH_TRY(ctx->ensure_t(kWsum, n, &ws));
         hipLaunchKernelGGL(k_row_count, dim3((unsigned)ceil_div(n, kBlock)), dim3(kBlock), 0, ctx->stream,
                            nb->view(), pv, op, cnt, creal, d, ws);
     } else {
         SPH_TRY(ctx->ensure_t(kList, (size_t)nslices * cap * kWave, &list));
-        launch_row_scan(ctx, nb, pv, op, false, creal, list, cap, win, reinterpret_cast<int32_t*>(nnz_dev + 2));
+        launch_row_scan(ctx, nb, pv, op, false, by_rows, cnt, creal, list, cap, win,
+                        reinterpret_cast<int32_t*>(nnz_dev + 2));
     }
     hipLaunchKernelGGL(k_slice_size, dim3((unsigned)std::min<int64_t>(ceil_div(nslices * kWave, kBlock), 1024)),
                        dim3(kBlock), 0, ctx->stream,

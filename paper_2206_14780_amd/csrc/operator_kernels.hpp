@@ -560,12 +560,12 @@ struct OtfBody {
     }
 };
 
-// On-the-fly operator over the cells, each block a contiguous share of them;
-// with kDotResid it writes y = b64 - A x instead (FP64 residual rounded to T)
+// On-the-fly operator over the cells, each block a contiguous share of them (W
+// waves), or over the rows (W = 0, one thread each); with kDotResid it writes y = b64 - A x instead (FP64 residual rounded to T)
 // and its squared norm, x then being of precision XT; with kDotCG, b64 holds
 // the weights D.
 template <typename T, int MODE, typename XT, int W>
-__global__ __launch_bounds__(W* kWave) void k_apply_otf(const int32_t* __restrict__ halt, NbrView nv,
+__global__ __launch_bounds__(W ? W * kWave : kApplyMaxBlock) void k_apply_otf(const int32_t* __restrict__ halt, NbrView nv,
                                                                  PartView pv, OpParams op, int64_t ncell, int32_t cap,
                                                                  const XT* __restrict__ x, T* __restrict__ y,
                                                                  const T* __restrict__ w,
@@ -579,8 +579,9 @@ __global__ __launch_bounds__(W* kWave) void k_apply_otf(const int32_t* __restric
 #pragma unroll
     for (int k = 0; k < K; ++k) acc[k] = 0.0;
     const int64_t bid = xcd_block(blockIdx.x, gridDim.x);
-    const int64_t cpb = ceil_div(ncell, (int64_t)gridDim.x);
-    const int64_t c0 = bid * cpb, c1 = min(c0 + cpb, ncell);
+    const int64_t all = W ? ncell : nv.n;
+    const int64_t share = ceil_div(all, (int64_t)gridDim.x);
+    const int64_t c0 = bid * share, c1 = min(c0 + share, all);
     const auto out = [&](int32_t r, const V3<XT>& xr, double (&yv)[3]) {
         if constexpr (MODE == kDotResid) {
             const V3<double> bb = ld3(b64, r);
@@ -603,26 +604,31 @@ __global__ __launch_bounds__(W* kWave) void k_apply_otf(const int32_t* __restric
         }
     };
     const OtfBody<XT, decltype(out)> body{pv, op, x, out};
-    for (int64_t c = c0; c < c1; ++c) cell_rows<W>(nv, (int32_t)c, cap, cell_lds, body);
+    if constexpr (W > 0) {
+        for (int64_t c = c0; c < c1; ++c) cell_rows<W>(nv, (int32_t)c, cap, cell_lds, body);
+    } else {
+        for (int64_t r = c0 + threadIdx.x; r < c1; r += blockDim.x) row_terms(nv, (int32_t)r, body);
+    }
     if constexpr (MODE != kDotNone) write_partials<K>(acc, lds, part);
 }
 
-// Launch of the on-the-fly operator: a block per cell, or (dot products) the
-// operator's grid, whose blocks write the partials.
+// Launch of the on-the-fly operator: a block per cell, or (dot products, and
+// rows) the operator's grid, whose blocks write the partials.
 template <typename T, int MODE, typename XT = T>
 inline void launch_apply_otf(hipStream_t stream, const Launch& L, const int32_t* halt, const sph_nbr* nb,
                              const PartView& pv, const OpParams& op, const XT* x, T* y, const T* w, const double* b64,
                              double* part) {
     const int32_t cap = cell_cap(nb);
     const int64_t cells = ceil_div(nb->ncell, (int64_t)kNumXcd) * kNumXcd;
-    const unsigned grid = MODE == kDotNone ? (unsigned)cells : (unsigned)L.grid_apply;
     const auto go = [&](auto waves) {
         constexpr int W = decltype(waves)::value;
-        hipLaunchKernelGGL((k_apply_otf<T, MODE, XT, W>), dim3(grid), dim3(W * kWave),
+        const unsigned grid = MODE == kDotNone && W ? (unsigned)cells : (unsigned)L.grid_apply;
+        hipLaunchKernelGGL((k_apply_otf<T, MODE, XT, W>), dim3(grid), dim3(W ? W * kWave : L.block_apply),
                            (cell_bytes<OtfBody<XT, int>, W>(cap)), stream, halt, nb->view(), pv, op, nb->ncell, cap, x,
                            y, w, b64, part);
     };
-    if (nb->g.kernel == SPH_KERNEL_GAUSSIAN) go(std::integral_constant<int, kCellWavesGauss>{});
+    if (!by_cells(nb)) go(std::integral_constant<int, 0>{});
+    else if (nb->g.kernel == SPH_KERNEL_GAUSSIAN) go(std::integral_constant<int, kCellWavesGauss>{});
     else go(std::integral_constant<int, kCellWaves>{});
 }
 

@@ -81,11 +81,18 @@ struct PapaBody {
     }
 };
 
+// A block of W waves per cell, or (W = 0) a thread per row.
 template <typename T, int W>
-__global__ __launch_bounds__(W* kWave) void k_papa_visc(NbrView nv, int64_t ncell, int32_t cap, PapaBody<T> body) {
-    extern __shared__ __align__(16) unsigned char cell_lds[];
+__global__ __launch_bounds__(W ? W * kWave : kBlock) void k_papa_visc(NbrView nv, int64_t ncell, int32_t cap,
+                                                                      PapaBody<T> body) {
     const int64_t c = xcd_block(blockIdx.x, gridDim.x);
-    if (c < ncell) cell_rows<W>(nv, (int32_t)c, cap, cell_lds, body);
+    if constexpr (W > 0) {
+        extern __shared__ __align__(16) unsigned char cell_lds[];
+        if (c < ncell) cell_rows<W>(nv, (int32_t)c, cap, cell_lds, body);
+    } else {
+        const int64_t b = c * kBlock + threadIdx.x;
+        if (b < nv.n) row_terms(nv, (int32_t)b, body);
+    }
 }
 
 template <typename T>
@@ -98,14 +105,16 @@ static sph_status papa_entry(sph_ctx* ctx, const sph_nbr* nb, const sph_particle
     SPH_TRY(gather_vec3<T>(ctx, nb, u, ucell));
     const double x0 = std::pow(362880.0 * std::ldexp(1.0, -23), 0.125);
     const int32_t cap = cell_cap(nb);
-    const dim3 grid((unsigned)(ceil_div(nb->ncell, (int64_t)kNumXcd) * kNumXcd));
     const auto go = [&](auto waves) {
         constexpr int W = decltype(waves)::value;
-        hipLaunchKernelGGL((k_papa_visc<T, W>), grid, dim3(W * kWave), (cell_bytes<PapaBody<T>, W>(cap)), ctx->stream,
+        const int64_t blocks = W ? nb->ncell : ceil_div(nb->n, (int64_t)kBlock);
+        const dim3 grid((unsigned)(ceil_div(blocks, (int64_t)kNumXcd) * kNumXcd));
+        hipLaunchKernelGGL((k_papa_visc<T, W>), grid, dim3(W ? W * kWave : kBlock), (cell_bytes<PapaBody<T>, W>(cap)), ctx->stream,
                            nb->view(), nb->ncell, cap,
                            (PapaBody<T>{pv, ucell, nb->perm, tau0, m, mu0, x0, mu_out, d_out}));
     };
-    if (nb->g.kernel == SPH_KERNEL_GAUSSIAN) go(std::integral_constant<int, kCellWavesGauss>{});
+    if (!by_cells(nb)) go(std::integral_constant<int, 0>{});
+    else if (nb->g.kernel == SPH_KERNEL_GAUSSIAN) go(std::integral_constant<int, kCellWavesGauss>{});
     else go(std::integral_constant<int, kCellWaves>{});
     SPH_LAUNCHED("k_papa_visc");
     return SPH_OK;
