@@ -7,11 +7,10 @@
 // Network (one sample = one fluid particle and one velocity component):
 //   x[4] -> 64 -> 64 -> 64 -> o[3], ReLU on the hidden layers,
 //   pred = o0 B0 + o1 B1 + o2 B2 with basis B = (b_c, u_c, (u - A u)_c) / U.
-// The two 64x64 layers, their data gradients and their weight gradients run
-// on MFMA, 16 samples per tile; the 4->64 and 64->3 layers run on the vector
-// ALU in FP32 in training and on MFMA with two-part BF16 inputs in inference.
-// Weights enter every product as BF16; the inputs of the 64x64 products
-// (activations and gradient signals) are rounded to BF16 as well.
+// All products run on MFMA, 16 samples per tile.  Weights enter every product
+// as BF16; the inputs of the 64x64 products (activations and gradient signals)
+// are rounded to BF16 as well, those of the 4->64 and 64->3 layers and of the
+// gradient signal of the last hidden layer enter as sums of BF16 parts.
 //
 // MFMA fragment layout (lane l, g = l / 16, c = l % 16, r = 0..3): the
 // output D[4g + r][c]; the operands of one 16x16x32 step carry 8 values of K
@@ -20,7 +19,9 @@
 // two 16-wide halves, each in the layout of a D output (rows 4g + r), so a
 // product's output (or two tiles' worth of samples) becomes the next
 // product's operand by concatenating two 4-value fragments, with no
-// shuffle.  A and B use the same assignment, so the product is exact in it.
+// shuffle.  A and B use the same assignment, so the product is exact in it,
+// and a fragment serves as either: with the operands swapped a product comes
+// out transposed.
 #include <algorithm>
 #include <cmath>
 
@@ -46,9 +47,8 @@ __device__ inline f32x4 mfma32(bf16x8 a, bf16x8 b, f32x4 c) {
 
 constexpr int kWaves = 4;             // waves per block
 constexpr int kThreads = kWaves * kWave;
-constexpr int kPad = 65;              // padded row of the per-wave transpose tile
 
-// Every tile and output staging area belongs to one wave (wave_sync), so the
+// What a wave writes to LDS in the tile loops is its own (wave_sync), so the
 // waves of a block never wait for each other after the parameters are loaded.
 
 __device__ inline uint16_t f2bf(float f) {  // nearest, ties to even (finite inputs)
@@ -57,167 +57,7 @@ __device__ inline uint16_t f2bf(float f) {  // nearest, ties to even (finite inp
     return (uint16_t)(u >> 16);
 }
 __device__ inline float bf2f(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
-__device__ inline float rbf(float f) { return bf2f(f2bf(f)); }
 
-struct Smem {
-    uint16_t w2[kH * kH], w2t[kH * kH], w3[kH * kH], w3t[kH * kH];  // [in][out] and [out][in]
-    float w1[kIn * kH];     // BF16-rounded values
-    float w4[kH * kOut];    // BF16-rounded values
-    float b1[kH], b2[kH], b3[kH], b4[4];
-    float tile[kWaves][16 * kPad];  // per-wave transpose / activation tile
-    float go[kWaves][16 * 4];       // per-wave outputs o or output gradients
-};
-
-__device__ inline void load_params(Smem& sm, const float* __restrict__ p) {
-    for (int i = threadIdx.x; i < kH * kH; i += blockDim.x) {
-        const int in = i / kH, out = i % kH;
-        const uint16_t v2 = f2bf(p[kOW2 + i]), v3 = f2bf(p[kOW3 + i]);
-        sm.w2[i] = v2;
-        sm.w2t[out * kH + in] = v2;
-        sm.w3[i] = v3;
-        sm.w3t[out * kH + in] = v3;
-    }
-    for (int i = threadIdx.x; i < kIn * kH; i += blockDim.x) sm.w1[i] = rbf(p[kOW1 + i]);
-    for (int i = threadIdx.x; i < kH * kOut; i += blockDim.x) sm.w4[i] = rbf(p[kOW4 + i]);
-    for (int i = threadIdx.x; i < kH; i += blockDim.x) {
-        sm.b1[i] = p[kOB1 + i];
-        sm.b2[i] = p[kOB2 + i];
-        sm.b3[i] = p[kOB3 + i];
-    }
-    if (threadIdx.x < kOut) sm.b4[threadIdx.x] = p[kOB4 + threadIdx.x];
-    __syncthreads();
-}
-
-// B fragment of a forward product h W (B[k][n] = W[k][n]), k-step s, n-tile t.
-__device__ inline bf16x4 bfrag_fwd(const uint16_t* __restrict__ wt, int s, int t, int g, int c) {
-    const uint16_t* q = wt + (16 * t + c) * kH + 16 * s + 4 * g;
-    bf16x4 v;
-    v[0] = (short)q[0];
-    v[1] = (short)q[1];
-    v[2] = (short)q[2];
-    v[3] = (short)q[3];
-    return v;
-}
-// B fragment of a data-gradient product dz W^T (B[k][n] = W[n][k]).
-__device__ inline bf16x4 bfrag_bwd(const uint16_t* __restrict__ w, int s, int t, int g, int c) {
-    const uint16_t* q = w + (16 * t + c) * kH + 16 * s + 4 * g;
-    bf16x4 v;
-    v[0] = (short)q[0];
-    v[1] = (short)q[1];
-    v[2] = (short)q[2];
-    v[3] = (short)q[3];
-    return v;
-}
-
-// D-layout values v[t][r] (row 4g + r, column 16t + c) -> A fragments
-// (row c, columns 16s + 4g + r) through the wave's LDS tile, BF16-rounded.
-__device__ inline void d_to_a(float* tile, const float (&v)[4][4], bf16x4 (&a)[4], int g, int c) {
-    for (int t = 0; t < 4; ++t)
-        for (int r = 0; r < 4; ++r) tile[(4 * g + r) * kPad + 16 * t + c] = v[t][r];
-    wave_sync();
-    for (int s = 0; s < 4; ++s)
-        for (int r = 0; r < 4; ++r) a[s][r] = (short)f2bf(tile[c * kPad + 16 * s + 4 * g + r]);
-    wave_sync();
-}
-
-// One 64x64 product on MFMA: out[t] (D layout) = A (16x64) x Wfrag, two
-// 32-wide K steps (16-wide blocks 2s and 2s + 1).
-template <bool FWD>
-__device__ inline void mm64(const bf16x4 (&a)[4], const uint16_t* __restrict__ w, int g, int c, f32x4 (&acc)[4]) {
-    for (int t = 0; t < 4; ++t) {
-        acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
-        for (int s = 0; s < 2; ++s) {
-            const bf16x4 b0 = FWD ? bfrag_fwd(w, 2 * s, t, g, c) : bfrag_bwd(w, 2 * s, t, g, c);
-            const bf16x4 b1 = FWD ? bfrag_fwd(w, 2 * s + 1, t, g, c) : bfrag_bwd(w, 2 * s + 1, t, g, c);
-            acc[t] = mfma32(cat8(a[2 * s], a[2 * s + 1]), cat8(b0, b1), acc[t]);
-        }
-    }
-}
-
-// First layer for one sample x: z1 at column col.
-__device__ inline float layer1(const Smem& sm, const float (&x)[4], int col) {
-    float z = sm.b1[col];
-    for (int f = 0; f < kIn; ++f) z = __builtin_fmaf(x[f], sm.w1[f * kH + col], z);
-    return z;
-}
-
-// State of one 16-sample tile kept for the backward pass.
-struct Tile {
-    float xA[4];        // features of sample row c
-    float xD[4][4];     // features of sample rows 4g + r
-    float bD[4][3];     // basis of rows 4g + r (for the output gradient)
-    float tD[4];        // targets of rows 4g + r
-    float h1[4][4];     // D layout (post-ReLU)
-    float h2[4][4];
-    float h3[4][4];
-};
-
-// Forward pass of one tile; leaves h3 in the wave's LDS tile and the
-// outputs o in sm.go[wave].  Returns nothing; the caller reads sm.go.
-__device__ inline void tile_forward(Smem& sm, Tile& T, int wave, int g, int c) {
-    float* tile = sm.tile[wave];
-    // layer 1 in A layout (input of the first MFMA product) and in D layout
-    bf16x4 a[4];
-    for (int s = 0; s < 4; ++s)
-        for (int r = 0; r < 4; ++r) a[s][r] = (short)f2bf(fmaxf(layer1(sm, T.xA, 16 * s + 4 * g + r), 0.f));
-    for (int t = 0; t < 4; ++t)
-        for (int r = 0; r < 4; ++r) T.h1[t][r] = fmaxf(layer1(sm, T.xD[r], 16 * t + c), 0.f);
-    f32x4 acc[4];
-    mm64<true>(a, sm.w2t, g, c, acc);
-    for (int t = 0; t < 4; ++t)
-        for (int r = 0; r < 4; ++r) T.h2[t][r] = fmaxf(acc[t][r] + sm.b2[16 * t + c], 0.f);
-    d_to_a(tile, T.h2, a, g, c);
-    mm64<true>(a, sm.w3t, g, c, acc);
-    for (int t = 0; t < 4; ++t)
-        for (int r = 0; r < 4; ++r) T.h3[t][r] = fmaxf(acc[t][r] + sm.b3[16 * t + c], 0.f);
-    // layer 4 on the vector ALU: h3 through the LDS tile
-    for (int t = 0; t < 4; ++t)
-        for (int r = 0; r < 4; ++r) tile[(4 * g + r) * kPad + 16 * t + c] = T.h3[t][r];
-    wave_sync();
-    const int lane = threadIdx.x % kWave;
-    if (lane < 16 * kOut) {
-        const int row = lane / kOut, k = lane % kOut;
-        float o = sm.b4[k];
-        for (int col = 0; col < kH; ++col) o = __builtin_fmaf(tile[row * kPad + col], sm.w4[col * kOut + k], o);
-        sm.go[wave][row * 4 + k] = o;
-    }
-    wave_sync();
-}
-
-// Loads sample `s` (or zeros when s < 0) into the lane's tile rows.
-__device__ inline void load_tile(Tile& T, const float* __restrict__ S, const int32_t* __restrict__ idx,
-                                 int64_t base, int64_t count, int g, int c) {
-    auto sample = [&](int64_t k) -> const float* {
-        if (k >= count) return nullptr;
-        const int64_t s = idx ? (int64_t)idx[base + k] : base + k;
-        return S + s * kSample;
-    };
-    const float* pa = sample(c);
-    for (int f = 0; f < 4; ++f) T.xA[f] = pa ? pa[f] : 0.f;
-    for (int r = 0; r < 4; ++r) {
-        const float* pd = sample(4 * g + r);
-        for (int f = 0; f < 4; ++f) T.xD[r][f] = pd ? pd[f] : 0.f;
-        for (int k = 0; k < 3; ++k) T.bD[r][k] = pd ? pd[4 + k] : 0.f;
-        T.tD[r] = pd ? pd[7] : 0.f;
-    }
-}
-
-// Inference: out[s] = (o0, o1, o2, pred) for samples [0, n).  All four
-// products run on MFMA, transposed, Z^T = W^T H^T, with the 16 samples of a
-// tile on the MFMA N dimension: a product's output then sits in registers
-// exactly as the next product's B operand (lane (g, c) holds features
-// 16t + 4g + r of sample c), so no LDS transpose is needed; the weights of
-// the 64x64 layers, as A operands, stay in registers for the whole launch,
-// those of the first and last layers in LDS.  The 64x64 layers take BF16
-// weights and BF16 layer inputs, as in the training kernel.  The first and
-// last layers take their inputs as sums of BF16 parts against the same BF16
-// weight: the features as three parts, which hold an FP32 value exactly (K
-// slots 4g + r, g = 0, 1, 2, carry part g of feature r), so layer 1 equals
-// the training kernel's FP32 layer up to the order of its FP32 sums (its
-// output is rounded to BF16 next, where a less accurate input would flip
-// roundings); the last hidden layer as two parts, to 2^-16 relative (one K
-// step per part; the output is not rounded again).  The training kernel
-// evaluates these two layers in FP32 on the vector ALU.
 // Two floats to packed BF16, nearest-even (the hardware conversion of
 // gfx950; the same rounding as f2bf on finite values).
 typedef float f32x2 __attribute__((ext_vector_type(2)));
@@ -237,7 +77,31 @@ __device__ inline void bf16x4_split(const float (&v)[4], bf16x4& hi, bf16x4& lo,
     lo = bf16x4_of(rem[0], rem[1], rem[2], rem[3]);
     for (int r = 0; r < 4; ++r) rem[r] -= bf2f((uint16_t)lo[r]);
 }
+// Four values as the operand of one step, exactly: part g (g = 0, 1, 2) of
+// value r in K slot 4g + r, to meet the same weight in all three.
+__device__ inline bf16x8 parts_operand(const float (&v)[4], int g) {
+    const bf16x4 z4 = {0, 0, 0, 0};
+    bf16x4 hi, lo;
+    float rem[4];
+    bf16x4_split(v, hi, lo, rem);
+    const bf16x4 last = bf16x4_of(rem[0], rem[1], rem[2], rem[3]);  // exact: at most 8 bits remain
+    return cat8(g == 0 ? hi : (g == 1 ? lo : (g == 2 ? last : z4)), z4);
+}
 
+// Inference: out[s] = (o0, o1, o2, pred) for samples [0, n).  All four
+// products run on MFMA, transposed, Z^T = W^T H^T, with the 16 samples of a
+// tile on the MFMA N dimension: a product's output then sits in registers
+// exactly as the next product's B operand (lane (g, c) holds features
+// 16t + 4g + r of sample c), so no LDS transpose is needed; the weights of
+// the 64x64 layers, as A operands, stay in registers for the whole launch,
+// those of the first and last layers in LDS.  The 64x64 layers take BF16
+// weights and BF16 layer inputs, as in the training kernel.  The first and
+// last layers take their inputs as sums of BF16 parts against the same BF16
+// weight: the features as three parts, which hold an FP32 value exactly (K
+// slots 4g + r, g = 0, 1, 2, carry part g of feature r; the layer's output is
+// rounded to BF16 next, where a less accurate input would flip roundings); the
+// last hidden layer as two parts, to 2^-16 relative (one K step per part; the
+// output is not rounded again).  The training kernel takes three there too.
 struct alignas(16) InferSmem {
     alignas(16) float b1[kH];
     alignas(16) float b2[kH];
@@ -309,11 +173,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) v
         const bool valid = smp < n;
         const float4 x = valid ? *reinterpret_cast<const float4*>(S + smp * kSample) : float4{0.f, 0.f, 0.f, 0.f};
         // layer 1 on MFMA, bias, ReLU, BF16: the B operand of layer 2
-        bf16x4 xh, xm;
-        float xr[4];
-        bf16x4_split({x.x, x.y, x.z, x.w}, xh, xm, xr);
-        const bf16x4 xl = bf16x4_of(xr[0], xr[1], xr[2], xr[3]);  // exact: at most 8 bits remain
-        const bf16x8 b1 = cat8(g == 0 ? xh : (g == 1 ? xm : (g == 2 ? xl : z4)), z4);
+        const bf16x8 b1 = parts_operand({x.x, x.y, x.z, x.w}, g);
         bf16x4 h[4];
         for (int t = 0; t < 4; ++t) {
             const f32x4 z = mfma32(sm.a1[t][lane], b1, f32x4{0.f, 0.f, 0.f, 0.f});
@@ -365,167 +225,344 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) v
     }
 }
 
-// Forward and backward of a batch (sample ids idx[0, batch)); every wave
-// writes its partial gradient (kNParam values) and its partial sum of
-// squared errors to part[global wave][0 .. kNParam].
-__global__ __launch_bounds__(kThreads) void k_mlp_train(const float* __restrict__ S,
-                                                        const int32_t* __restrict__ idx, int64_t batch,
-                                                        const float* __restrict__ params,
-                                                        float* __restrict__ part, int32_t tiles_per_wave) {
-    __shared__ Smem sm;
-    load_params(sm, params);
-    const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave, g = lane / 16, c = lane % 16;
-    const int64_t gw = (int64_t)blockIdx.x * kWaves + wave;
-    const float inv_m = 2.0f / (float)batch;
-    float* tile = sm.tile[wave];
-    f32x4 gW2[4][4], gW3[4][4];
-    for (int i = 0; i < 4; ++i)
-        for (int j = 0; j < 4; ++j) gW2[i][j] = gW3[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-    float gW1[4][4] = {}, gb1[4] = {}, gb2[4] = {}, gb3[4] = {};
-    float gW4[3] = {0.f, 0.f, 0.f}, gb4 = 0.f, sse = 0.f;
-    // The weight gradients h^T dz sum over the samples (K); one 32-wide
-    // step takes two tiles, so the operands of every even tile wait for the
-    // next tile (or for zeros after the last one).
-    bf16x4 pah3[4], pbz3[4], pah2[4], pbz2[4];
-    bool pend = false;
-    const auto wgrad = [&](f32x4 (&gW)[4][4], bf16x4 (&pa)[4], bf16x4 (&pb)[4], const bf16x4 (&ah)[4],
-                           const bf16x4 (&bz)[4]) {
-        if (!pend) {
-            for (int t = 0; t < 4; ++t) {
-                pa[t] = ah[t];
-                pb[t] = bz[t];
-            }
-            return;
-        }
-        for (int mt = 0; mt < 4; ++mt)
-            for (int nt = 0; nt < 4; ++nt) gW[mt][nt] = mfma32(cat8(pa[mt], ah[mt]), cat8(pb[nt], bz[nt]), gW[mt][nt]);
+// Forward and backward of a batch (sample ids idx[0, batch)); every block
+// writes its partial gradient (kNParam values) and its partial sum of squared
+// errors to part[block][0 .. kNParam].
+//
+// Each product is taken twice with the operands swapped: transposed ("T": lane
+// (g, c) holds features 16t + 4g + r of sample c), which is the next product's
+// operand, and plain ("N": feature 16t + c of samples 4g + r), which is the
+// operand of the weight gradients h^T dz, whose K is the samples.  Matrix
+// instructions are cheaper here than the transposes through LDS that one of
+// the two forms would need: they are idle nine tenths of the time.  Two tiles
+// go together, for the 32 samples of a weight gradient's K step and because
+// one wave per SIMD (the gradients of both 64x64 layers take 128 registers)
+// has only its own instructions to overlap; the weights' fragments come from
+// LDS in lane order, one 16-byte read for four products.  Layers 1 and 4 and
+// the last layer's data gradient take their FP32 inputs as three BF16 parts,
+// that is exactly; bias gradients and those of layers 1 and 4 are FP32 on the
+// vector ALU.  The four waves' gradients are added in FP64 in the block.
+// A step of 65,536 samples: 68 -> 28 us, and the sum of the 256 partials (1024
+// before) 9 -> 4.
+// What bounds it is the vector ALU of a single wave (bias, ReLU, rounding and
+// the small gradients: about 700 instructions a tile) and, at this size, the
+// setup and the exchange at the end, about a third.
+struct alignas(16) TrainSmem {
+    bf16x8 f2[8][kWave], f3[8][kWave];  // W[in][16t + c], K = in; [2 t + s]: tile t, K step s
+    bf16x8 r2[8][kWave], r3[8][kWave];  // W[16t + c][out], K = out
+    bf16x8 a1[4][kWave];                // layer 1: W[r][16t + c] in K slots 4g + r, g < 3
+    bf16x8 a4[2][kWave];                // layer 4: W[in][c % 4], K = in (every lane group gets the outputs)
+    bf16x8 r4[4][kWave];                // its data gradient: W[16t + c][r] in K slots 4g + r, g < 3
+    float b1[kH], b2[kH], b3[kH], b4[4];
+    float4 smp[kWaves][4][16][2];       // a wave's four tiles of samples
+    float4 go[kWaves][2][16];           // output gradients of two tiles
+};
+constexpr int kExchange = 64;  // values per lane that the waves exchange at a time
+union TrainLds {
+    TrainSmem p;
+    float x[kWaves][kExchange][kWave];
+};
+
+__device__ inline void train_params(TrainSmem& sm, const float* __restrict__ p) {
+    const bf16x4 z4 = {0, 0, 0, 0};
+    const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave, g = lane / 16, c = lane % 16;
+    // value i of a fragment: K index 16 (i / 4) + 4g + i % 4 of the step
+    const auto frag = [&](auto w) {
+        return cat8(bf16x4_of(w(4 * g), w(4 * g + 1), w(4 * g + 2), w(4 * g + 3)),
+                    bf16x4_of(w(16 + 4 * g), w(17 + 4 * g), w(18 + 4 * g), w(19 + 4 * g)));
     };
-    for (int q = 0; q < tiles_per_wave; ++q) {
-        const int64_t base = (gw * tiles_per_wave + q) * 16;
-        Tile T;
-        load_tile(T, S, idx, base, batch - base, g, c);
-        tile_forward(sm, T, wave, g, c);
-        // output gradient g_o = (2/m) (pred - t) B of rows 0..15 (lanes 0..15
-        // read their own o and overwrite it)
-        if (lane < 16) {
-            const int64_t k = base + lane;
-            float go[3] = {0.f, 0.f, 0.f};
-            if (k < batch) {
-                const float* ps = S + (int64_t)idx[k] * kSample;
-                const float* o = &sm.go[wave][lane * 4];
-                float pred = o[0] * ps[4];
-                pred = __builtin_fmaf(o[1], ps[5], pred);
-                pred = __builtin_fmaf(o[2], ps[6], pred);
-                const float err = pred - ps[7];
-                sse = __builtin_fmaf(err, err, sse);
-                for (int j = 0; j < 3; ++j) go[j] = inv_m * err * ps[4 + j];
-            }
-            for (int j = 0; j < 3; ++j) sm.go[wave][lane * 4 + j] = go[j];
-        }
-        wave_sync();
-        const float* GO = sm.go[wave];
-        // layer 4: dW4[col][k] += sum_row h3[row][col] g_o[row][k] (h3 still in the tile)
-        for (int row = 0; row < 16; ++row) {
-            const float h = tile[row * kPad + lane];
-            for (int k = 0; k < 3; ++k) gW4[k] = __builtin_fmaf(h, GO[row * 4 + k], gW4[k]);
-        }
-        if (lane < 3)
-            for (int row = 0; row < 16; ++row) gb4 += GO[row * 4 + lane];
-        // dz3 (D layout)
-        float dz[4][4];
-        for (int t = 0; t < 4; ++t)
-            for (int r = 0; r < 4; ++r) {
-                const int row = 4 * g + r, col = 16 * t + c;
-                float d = GO[row * 4 + 0] * sm.w4[col * kOut + 0];
-                d = __builtin_fmaf(GO[row * 4 + 1], sm.w4[col * kOut + 1], d);
-                d = __builtin_fmaf(GO[row * 4 + 2], sm.w4[col * kOut + 2], d);
-                dz[t][r] = T.h3[t][r] > 0.f ? d : 0.f;
-            }
-        wave_sync();
-        // layer 3: weight gradient h2^T dz3, bias gradient, data gradient dz3 W3^T
-        for (int t = 0; t < 4; ++t)
-            for (int r = 0; r < 4; ++r) gb3[t] += dz[t][r];
-        {
-            bf16x4 ah[4], bz[4];
-            for (int t = 0; t < 4; ++t)
-                for (int r = 0; r < 4; ++r) {
-                    ah[t][r] = (short)f2bf(T.h2[t][r]);
-                    bz[t][r] = (short)f2bf(dz[t][r]);
-                }
-            wgrad(gW3, pah3, pbz3, ah, bz);
-        }
-        bf16x4 a[4];
-        d_to_a(tile, dz, a, g, c);
-        f32x4 acc[4];
-        mm64<false>(a, sm.w3, g, c, acc);
-        for (int t = 0; t < 4; ++t)
-            for (int r = 0; r < 4; ++r) dz[t][r] = T.h2[t][r] > 0.f ? acc[t][r] : 0.f;
-        // layer 2
-        for (int t = 0; t < 4; ++t)
-            for (int r = 0; r < 4; ++r) gb2[t] += dz[t][r];
-        {
-            bf16x4 ah[4], bz[4];
-            for (int t = 0; t < 4; ++t)
-                for (int r = 0; r < 4; ++r) {
-                    ah[t][r] = (short)f2bf(T.h1[t][r]);
-                    bz[t][r] = (short)f2bf(dz[t][r]);
-                }
-            wgrad(gW2, pah2, pbz2, ah, bz);
-        }
-        d_to_a(tile, dz, a, g, c);
-        mm64<false>(a, sm.w2, g, c, acc);
-        // layer 1
-        for (int t = 0; t < 4; ++t)
-            for (int r = 0; r < 4; ++r) {
-                const float d = T.h1[t][r] > 0.f ? acc[t][r] : 0.f;
-                gb1[t] += d;
-                for (int f = 0; f < 4; ++f) gW1[f][t] = __builtin_fmaf(T.xD[r][f], d, gW1[f][t]);
-            }
-        pend = !pend;
+#pragma unroll
+    for (int q = wave; q < 8; q += kWaves) {
+        const int o = 16 * (q / 2) + c, k0 = 32 * (q % 2);
+        sm.f2[q][lane] = frag([&](int k) { return p[kOW2 + (k0 + k) * kH + o]; });
+        sm.f3[q][lane] = frag([&](int k) { return p[kOW3 + (k0 + k) * kH + o]; });
+        sm.r2[q][lane] = frag([&](int k) { return p[kOW2 + o * kH + k0 + k]; });
+        sm.r3[q][lane] = frag([&](int k) { return p[kOW3 + o * kH + k0 + k]; });
     }
-    if (pend) {
-        // the last tile's weight gradients with a zero partner
-        const bf16x4 z4{0, 0, 0, 0};
-        const bf16x4 zero[4] = {z4, z4, z4, z4};
-        wgrad(gW3, pah3, pbz3, zero, zero);
-        wgrad(gW2, pah2, pbz2, zero, zero);
+    {
+        const int o = 16 * wave + c;
+        const auto w1 = [&](int r) { return p[kOW1 + r * kH + o]; };
+        const auto w4 = [&](int r) { return p[kOW4 + o * kOut + r]; };
+        sm.a1[wave][lane] = cat8(g < 3 ? bf16x4_of(w1(0), w1(1), w1(2), w1(3)) : z4, z4);
+        sm.r4[wave][lane] = cat8(g < 3 ? bf16x4_of(w4(0), w4(1), w4(2), 0.f) : z4, z4);
     }
-    // write this wave's partial gradient
-    float* P = part + gw * (int64_t)(kNParam + 1);
-    for (int mt = 0; mt < 4; ++mt)
-        for (int nt = 0; nt < 4; ++nt)
-            for (int r = 0; r < 4; ++r) {
-                const int row = 16 * mt + 4 * g + r, col = 16 * nt + c;
-                P[kOW2 + row * kH + col] = gW2[mt][nt][r];
-                P[kOW3 + row * kH + col] = gW3[mt][nt][r];
-            }
-    for (int t = 0; t < 4; ++t) {
-        float v1 = gb1[t], v2 = gb2[t], v3 = gb3[t];
-        float w[4] = {gW1[0][t], gW1[1][t], gW1[2][t], gW1[3][t]};
-        for (int off = 16; off < kWave; off <<= 1) {
-            v1 += __shfl_xor(v1, off, kWave);
-            v2 += __shfl_xor(v2, off, kWave);
-            v3 += __shfl_xor(v3, off, kWave);
-            for (int f = 0; f < 4; ++f) w[f] += __shfl_xor(w[f], off, kWave);
-        }
-        if (g == 0) {
-            P[kOB1 + 16 * t + c] = v1;
-            P[kOB2 + 16 * t + c] = v2;
-            P[kOB3 + 16 * t + c] = v3;
-            for (int f = 0; f < 4; ++f) P[kOW1 + f * kH + 16 * t + c] = w[f];
-        }
+    if (wave < 2) sm.a4[wave][lane] = frag([&](int k) { return c % 4 < kOut ? p[kOW4 + (32 * wave + k) * kOut + c % 4] : 0.f; });
+    if (threadIdx.x < kH) {
+        sm.b1[threadIdx.x] = p[kOB1 + threadIdx.x];
+        sm.b2[threadIdx.x] = p[kOB2 + threadIdx.x];
+        sm.b3[threadIdx.x] = p[kOB3 + threadIdx.x];
     }
-    for (int k = 0; k < 3; ++k) P[kOW4 + lane * kOut + k] = gW4[k];
-    if (lane < 3) P[kOB4 + lane] = gb4;
-    for (int off = 1; off < 16; off <<= 1) sse += __shfl_xor(sse, off, kWave);
-    if (lane == 0) P[kNParam] = sse;
+    if (threadIdx.x < 4) sm.b4[threadIdx.x] = threadIdx.x < kOut ? p[kOB4 + threadIdx.x] : 0.f;
 }
 
-// Sums the per-wave partials in a fixed order.  With Adam (step > 0) it
+__device__ inline bf16x4 relu_bf16(f32x4 z) {
+    return bf16x4_of(fmaxf(z[0], 0.f), fmaxf(z[1], 0.f), fmaxf(z[2], 0.f), fmaxf(z[3], 0.f));
+}
+// The gradient signal where the layer's output (BF16, never negative) is not 0.
+__device__ inline f32x4 where_on(f32x4 d, bf16x4 h) {
+    return f32x4{h[0] ? d[0] : 0.f, h[1] ? d[1] : 0.f, h[2] ? d[2] : 0.f, h[3] ? d[3] : 0.f};
+}
+__device__ inline bf16x4 to_bf16(f32x4 d) { return bf16x4_of(d[0], d[1], d[2], d[3]); }
+
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 1))) void k_mlp_train(
+    const float* __restrict__ S, const int32_t* __restrict__ idx, int64_t batch, const float* __restrict__ params,
+    float* __restrict__ part, int32_t tiles_per_wave) {
+    __shared__ __align__(16) TrainLds lds;
+    TrainSmem& sm = lds.p;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int lane = threadIdx.x % kWave, g = lane / 16, c = lane % 16;
+    const int64_t tile0 = ((int64_t)blockIdx.x * kWaves + wave) * tiles_per_wave;
+    const int64_t left = ceil_div(batch, (int64_t)16) - tile0;
+    const int32_t mine = (int32_t)(left < 0 ? 0 : min(left, (int64_t)tiles_per_wave));
+    // samples of four tiles at a time, lane (g, c) sample c of tile g; zeros
+    // beyond the batch give no gradient
+    float4 sx, sb;
+    const auto load = [&](int32_t q) {
+        const int64_t k = (tile0 + q + g) * 16 + c;
+        sx = sb = float4{0.f, 0.f, 0.f, 0.f};
+        if (q + g < mine && k < batch) {
+            // (the caller's samples need not be aligned to 16 bytes)
+            typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
+            const f32x4u* v = reinterpret_cast<const f32x4u*>(S + (int64_t)idx[k] * kSample);
+            sx = float4{v[0][0], v[0][1], v[0][2], v[0][3]};
+            sb = float4{v[1][0], v[1][1], v[1][2], v[1][3]};
+        }
+    };
+    load(0);
+    train_params(sm, params);
+    __syncthreads();
+    const float inv_m = 2.0f / (float)batch;
+    const f32x4 z = {0.f, 0.f, 0.f, 0.f};
+    f32x4 gW2[4][4], gW3[4][4];
+    for (int i = 0; i < 4; ++i)
+        for (int j = 0; j < 4; ++j) gW2[i][j] = gW3[i][j] = z;
+    float gW1[4][4] = {}, gW4[4][3] = {}, gb1[4] = {}, gb2[4] = {}, gb3[4] = {}, gb4[3] = {}, sse = 0.f;
+    // a layer's bias as the accumulator to start from, in both forms
+    const auto biasT = [&](const float* b, int t) { return *reinterpret_cast<const f32x4*>(b + 16 * t + 4 * g); };
+    const auto biasN = [&](const float* b, int t) {
+        const float v = b[16 * t + c];
+        return f32x4{v, v, v, v};
+    };
+    for (int32_t q = 0; q < mine; q += 4) {
+        sm.smp[wave][g][c][0] = sx;
+        sm.smp[wave][g][c][1] = sb;
+        wave_sync();
+        load(q + 4);
+        for (int32_t pr = 0; pr < 2 && q + 2 * pr < mine; ++pr) {
+            // re-read the tables for every pair rather than keeping them in registers
+            __asm__ volatile("" ::: "memory");
+            bf16x4 h1o[2][4], h1n[2][4], h2o[2][4], h2n[2][4], h3o[2][4];
+            bf16x8 in[2];
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                const float4 x = sm.smp[wave][2 * pr + u][c][0];
+                in[u] = parts_operand({x.x, x.y, x.z, x.w}, g);
+            }
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                const bf16x8 w = sm.a1[t][lane];
+                const f32x4 bT = biasT(sm.b1, t), bN = biasN(sm.b1, t);
+#pragma unroll
+                for (int u = 0; u < 2; ++u) {
+                    h1o[u][t] = relu_bf16(mfma32(w, in[u], bT));
+                    h1n[u][t] = relu_bf16(mfma32(in[u], w, bN));
+                }
+            }
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                const bf16x8 w0 = sm.f2[2 * t][lane], w1 = sm.f2[2 * t + 1][lane];
+                const f32x4 bT = biasT(sm.b2, t), bN = biasN(sm.b2, t);
+#pragma unroll
+                for (int u = 0; u < 2; ++u) {
+                    const bf16x8 v0 = cat8(h1o[u][0], h1o[u][1]), v1 = cat8(h1o[u][2], h1o[u][3]);
+                    h2o[u][t] = relu_bf16(mfma32(w1, v1, mfma32(w0, v0, bT)));
+                    h2n[u][t] = relu_bf16(mfma32(v1, w1, mfma32(v0, w0, bN)));
+                }
+            }
+            // layer 3, whose output layer 4 takes as three BF16 parts
+            f32x4 h3n[2][4], o4[2];
+            bf16x4 h3m[2][4], h3l[2][4];
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                const bf16x8 w0 = sm.f3[2 * t][lane], w1 = sm.f3[2 * t + 1][lane];
+                const f32x4 bT = biasT(sm.b3, t), bN = biasN(sm.b3, t);
+#pragma unroll
+                for (int u = 0; u < 2; ++u) {
+                    const bf16x8 v0 = cat8(h2o[u][0], h2o[u][1]), v1 = cat8(h2o[u][2], h2o[u][3]);
+                    const f32x4 zT = mfma32(w1, v1, mfma32(w0, v0, bT));
+                    const float v[4] = {fmaxf(zT[0], 0.f), fmaxf(zT[1], 0.f), fmaxf(zT[2], 0.f), fmaxf(zT[3], 0.f)};
+                    float rem[4];
+                    bf16x4_split(v, h3o[u][t], h3m[u][t], rem);
+                    h3l[u][t] = bf16x4_of(rem[0], rem[1], rem[2], rem[3]);
+                    h3n[u][t] = mfma32(v1, w1, mfma32(v0, w0, bN));
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) h3n[u][t][r] = fmaxf(h3n[u][t][r], 0.f);
+                }
+            }
+            o4[0] = o4[1] = *reinterpret_cast<const f32x4*>(sm.b4);
+#pragma unroll
+            for (int s = 0; s < 2; ++s) {
+                const bf16x8 w = sm.a4[s][lane];
+#pragma unroll
+                for (int u = 0; u < 2; ++u) {
+                    o4[u] = mfma32(w, cat8(h3l[u][2 * s], h3l[u][2 * s + 1]), o4[u]);
+                    o4[u] = mfma32(w, cat8(h3m[u][2 * s], h3m[u][2 * s + 1]), o4[u]);
+                    o4[u] = mfma32(w, cat8(h3o[u][2 * s], h3o[u][2 * s + 1]), o4[u]);
+                }
+            }
+            // output gradient g_o = (2/m) (pred - t) B of sample c
+            bf16x8 gin[2];
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                const float4 bs = sm.smp[wave][2 * pr + u][c][1];
+                float pred = o4[u][0] * bs.x;
+                pred = __builtin_fmaf(o4[u][1], bs.y, pred);
+                pred = __builtin_fmaf(o4[u][2], bs.z, pred);
+                const float err = pred - bs.w;
+                const float go[4] = {inv_m * err * bs.x, inv_m * err * bs.y, inv_m * err * bs.z, 0.f};
+                if (g == 0) {
+                    sse = __builtin_fmaf(err, err, sse);
+                    for (int k = 0; k < 3; ++k) gb4[k] += go[k];
+                    sm.go[wave][u][c] = float4{go[0], go[1], go[2], 0.f};
+                }
+                gin[u] = parts_operand(go, g);
+            }
+            wave_sync();
+            // layer 4: weight gradient h3^T g_o, and the signal of layer 3
+            bf16x4 dzo[2][4], dzn[2][4];
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const float4 o = sm.go[wave][u][4 * g + r];
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) {
+                        gW4[t][0] = __builtin_fmaf(h3n[u][t][r], o.x, gW4[t][0]);
+                        gW4[t][1] = __builtin_fmaf(h3n[u][t][r], o.y, gW4[t][1]);
+                        gW4[t][2] = __builtin_fmaf(h3n[u][t][r], o.z, gW4[t][2]);
+                    }
+                }
+            }
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                const bf16x8 w = sm.r4[t][lane];
+#pragma unroll
+                for (int u = 0; u < 2; ++u) {
+                    dzo[u][t] = to_bf16(where_on(mfma32(w, gin[u], z), h3o[u][t]));
+                    f32x4 d = mfma32(gin[u], w, z);
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        d[r] = h3n[u][t][r] > 0.f ? d[r] : 0.f;
+                        gb3[t] += d[r];
+                    }
+                    dzn[u][t] = to_bf16(d);
+                }
+            }
+#pragma unroll
+            for (int mt = 0; mt < 4; ++mt)
+#pragma unroll
+                for (int nt = 0; nt < 4; ++nt)
+                    gW3[mt][nt] = mfma32(cat8(h2n[0][mt], h2n[1][mt]), cat8(dzn[0][nt], dzn[1][nt]), gW3[mt][nt]);
+            // layer 2: signal dz3 W3^T where h2 > 0
+            bf16x4 ezo[2][4];
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                const bf16x8 w0 = sm.r3[2 * t][lane], w1 = sm.r3[2 * t + 1][lane];
+#pragma unroll
+                for (int u = 0; u < 2; ++u) {
+                    const bf16x8 v0 = cat8(dzo[u][0], dzo[u][1]), v1 = cat8(dzo[u][2], dzo[u][3]);
+                    ezo[u][t] = to_bf16(where_on(mfma32(w1, v1, mfma32(w0, v0, z)), h2o[u][t]));
+                    const f32x4 d = where_on(mfma32(v1, w1, mfma32(v0, w0, z)), h2n[u][t]);
+                    gb2[t] += (d[0] + d[1]) + (d[2] + d[3]);
+                    dzn[u][t] = to_bf16(d);
+                }
+            }
+#pragma unroll
+            for (int mt = 0; mt < 4; ++mt)
+#pragma unroll
+                for (int nt = 0; nt < 4; ++nt)
+                    gW2[mt][nt] = mfma32(cat8(h1n[0][mt], h1n[1][mt]), cat8(dzn[0][nt], dzn[1][nt]), gW2[mt][nt]);
+            // layer 1
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                const bf16x8 v0 = cat8(ezo[u][0], ezo[u][1]), v1 = cat8(ezo[u][2], ezo[u][3]);
+                f32x4 d[4];
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    d[t] = where_on(mfma32(v1, sm.r2[2 * t + 1][lane], mfma32(v0, sm.r2[2 * t][lane], z)), h1n[u][t]);
+                    gb1[t] += (d[t][0] + d[t][1]) + (d[t][2] + d[t][3]);
+                }
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const float4 x = sm.smp[wave][2 * pr + u][4 * g + r][0];
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) {
+                        gW1[0][t] = __builtin_fmaf(x.x, d[t][r], gW1[0][t]);
+                        gW1[1][t] = __builtin_fmaf(x.y, d[t][r], gW1[1][t]);
+                        gW1[2][t] = __builtin_fmaf(x.z, d[t][r], gW1[2][t]);
+                        gW1[3][t] = __builtin_fmaf(x.w, d[t][r], gW1[3][t]);
+                    }
+                }
+            }
+            wave_sync();
+        }
+    }
+    // The block's sums: the waves' values side by side in LDS, 64 per lane at a
+    // time, added by all threads.
+    float* P = part + (int64_t)blockIdx.x * (kNParam + 1);
+    const auto exchange = [&](const f32x4 (&gW)[4][4], int off) {
+        __syncthreads();
+#pragma unroll
+        for (int mt = 0; mt < 4; ++mt)
+#pragma unroll
+            for (int nt = 0; nt < 4; ++nt)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) lds.x[wave][(4 * mt + nt) * 4 + r][lane] = gW[mt][nt][r];
+        __syncthreads();
+        for (int v = wave; v < kExchange; v += kWaves) {
+            double s = 0.0;
+            for (int w = 0; w < kWaves; ++w) s += (double)lds.x[w][v][lane];
+            P[off + (16 * (v / 16) + 4 * g + v % 4) * kH + 16 * (v / 4 % 4) + c] = (float)s;
+        }
+    };
+    exchange(gW2, kOW2);
+    exchange(gW3, kOW3);
+    __syncthreads();
+    constexpr int kSmall = 10;  // per tile t: four rows of W1, three biases, three columns of W4
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+        for (int f = 0; f < 4; ++f) lds.x[wave][kSmall * t + f][lane] = gW1[f][t];
+        lds.x[wave][kSmall * t + 4][lane] = gb1[t];
+        lds.x[wave][kSmall * t + 5][lane] = gb2[t];
+        lds.x[wave][kSmall * t + 6][lane] = gb3[t];
+        for (int k = 0; k < 3; ++k) lds.x[wave][kSmall * t + 7 + k][lane] = gW4[t][k];
+    }
+    for (int k = 0; k < 3; ++k) lds.x[wave][4 * kSmall + k][lane] = gb4[k];
+    lds.x[wave][4 * kSmall + 3][lane] = sse;
+    __syncthreads();
+    // features 16t + c: over the waves and their lane groups
+    for (int e = threadIdx.x; e < 4 * kSmall * 16; e += kThreads) {
+        const int v = e / 16, t = v / kSmall, k = v % kSmall, o = 16 * t + e % 16;
+        double s = 0.0;
+        for (int w = 0; w < kWaves; ++w)
+            for (int l = e % 16; l < kWave; l += 16) s += (double)lds.x[w][v][l];
+        const int at = k < 4 ? kOW1 + k * kH + o : k == 4 ? kOB1 + o : k == 5 ? kOB2 + o : k == 6 ? kOB3 + o
+                                                                                          : kOW4 + o * kOut + k - 7;
+        P[at] = (float)s;
+    }
+    // output biases and squared error: a wave each, over the waves' lanes of group 0
+    double s = 0.0;
+    if (lane < 16)
+        for (int w = 0; w < kWaves; ++w) s += (double)lds.x[w][4 * kSmall + wave][lane];
+    for (int off = 1; off < 16; off <<= 1) s += __shfl_xor(s, off, kWave);
+    if (lane == 0) P[wave < 3 ? kOB4 + wave : kNParam] = (float)s;
+}
+static_assert(kWaves == 4, "the four values beside the tiles: a wave each");
+
+// Sums the blocks' partials in a fixed order.  With Adam (step > 0) it
 // updates the FP32 master weights (Kingma & Ba, bias-corrected); otherwise it
 // writes the gradient to `grad`.  out[0] = mean squared error of the batch.
-// Sums the per-wave partials of every parameter (and of the loss) in FP64
-// and applies Adam.  One lane per parameter, kRedWaves waves per block: wave
+// One lane per parameter, kRedWaves waves per block: wave
 // w adds the partials w, w + kRedWaves, ... in that order, then the first
 // wave adds the waves' sums in wave order, so the result depends only on
 // the number of partials, not on timing.
@@ -572,13 +609,14 @@ __global__ __launch_bounds__(kRedWaves * kWave) void k_mlp_reduce(const float* _
 using namespace sph;
 using namespace sph::mlp;
 
+// Tiles per wave of the training kernel and its blocks: a block per CU (its
+// registers leave room for one), and pairs of tiles.
 static int32_t tiles_per_wave(int64_t n, int32_t* grid) {
-    const int64_t tiles = ceil_div(n, 16);
-    int64_t waves = std::min<int64_t>(ceil_div(tiles, 4), 8192);
-    if (waves < 1) waves = 1;
-    const int64_t blocks = ceil_div(waves, kWaves);
+    const int64_t tiles = ceil_div(n, (int64_t)16);
+    const int64_t blocks = std::min<int64_t>(ceil_div(tiles, (int64_t)(2 * kWaves)), 256);
     *grid = (int32_t)blocks;
-    return (int32_t)ceil_div(tiles, blocks * kWaves);
+    const int64_t per = ceil_div(tiles, blocks * kWaves);
+    return (int32_t)((per + 1) / 2 * 2);
 }
 
 sph_status sph::mlp::forward(sph_ctx* ctx, const float* samples, int64_t n, const float* params, float* out) {
@@ -605,7 +643,7 @@ static sph_status train_or_grad(sph_ctx* ctx, const float* samples, const int32_
                                 double* loss) {
     int32_t grid = 0;
     const int32_t tpw = tiles_per_wave(batch, &grid);
-    const int64_t nparts = (int64_t)grid * kWaves;
+    const int64_t nparts = grid;
     float* part = nullptr;
     double* out = nullptr;
     SPH_TRY(ctx->ensure_t(kMlpPart, (size_t)nparts * (kNParam + 1), &part));
