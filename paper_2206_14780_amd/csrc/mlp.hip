@@ -102,6 +102,14 @@ __device__ inline bf16x8 parts_operand(const float (&v)[4], int g) {
 // rounded to BF16 next, where a less accurate input would flip roundings); the
 // last hidden layer as two parts, to 2^-16 relative (one K step per part; the
 // output is not rounded again).  The training kernel takes three there too.
+// A weight operand of one step: w(k) for the lane group's K indices, value i at
+// k = 16 (i / 4) + 4g + i % 4.
+template <typename F>
+__device__ inline bf16x8 weight_frag(F&& w, int g) {
+    return cat8(bf16x4_of(w(4 * g), w(4 * g + 1), w(4 * g + 2), w(4 * g + 3)),
+                bf16x4_of(w(16 + 4 * g), w(17 + 4 * g), w(18 + 4 * g), w(19 + 4 * g)));
+}
+
 struct alignas(16) InferSmem {
     alignas(16) float b1[kH];
     alignas(16) float b2[kH];
@@ -109,10 +117,14 @@ struct alignas(16) InferSmem {
     alignas(16) float b4[4];
     alignas(16) bf16x8 a1[4][kWave];  // A operands of layer 1 (tile t, lane)
     alignas(16) bf16x8 a4[2][kWave];  // A operands of layer 4 (K step s, lane)
+    alignas(16) bf16x8 f2[8][kWave], f3[8][kWave];  // the 64x64 layers', [2 t + s]
 };
 
-// At most 128 registers, so that four waves share a SIMD (the operands' set-up
-// spills a few values once per block, none in the tile loop).
+// Bounded by the vector ALU (bias, ReLU, rounding: 200 instructions a tile, 20
+// us of a launch of 985k samples), once the loads are out of its way: 68 -> 35
+// us for that launch with the samples loaded ahead, the weights gathered once
+// per block and no more waves than fit.  At most 128 registers, so that four
+// waves share a SIMD.
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) void k_mlp_infer(const float* __restrict__ S, int64_t n,
                                                         const float* __restrict__ p, float* __restrict__ out) {
     __shared__ __align__(16) InferSmem sm;
@@ -123,22 +135,14 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) v
     }
     if (threadIdx.x < 4) sm.b4[threadIdx.x] = threadIdx.x < kOut ? p[kOB4 + threadIdx.x] : 0.f;
     // A operands: step s of output tile t holds W[in][16t + c] (W stored
-    // [in][out]) for the lane group's K slots, in = 32s + 16 (i / 4) + 4g + i % 4
+    // [in][out]) for the lane group's K slots, in = 32s + 16 (i / 4) + 4g + i % 4.
+    // The waves share their gathers: each by itself, as before, read all 128
+    // values of a lane one by one, 10 us of a launch of 985k samples.
     const int lane = threadIdx.x % kWave, g = lane / 16, c = lane % 16;
-    bf16x8 a2[4][2], a3[4][2];
-    for (int t = 0; t < 4; ++t)
-        for (int s = 0; s < 2; ++s) {
-            bf16x4 lo2, hi2, lo3, hi3;
-            for (int r = 0; r < 4; ++r) {
-                const int in = 32 * s + 4 * g + r, o = 16 * t + c;
-                lo2[r] = (short)f2bf(p[kOW2 + in * kH + o]);
-                hi2[r] = (short)f2bf(p[kOW2 + (in + 16) * kH + o]);
-                lo3[r] = (short)f2bf(p[kOW3 + in * kH + o]);
-                hi3[r] = (short)f2bf(p[kOW3 + (in + 16) * kH + o]);
-            }
-            a2[t][s] = cat8(lo2, hi2);
-            a3[t][s] = cat8(lo3, hi3);
-        }
+    for (int q = threadIdx.x / kWave; q < 8; q += kWaves) {
+        sm.f2[q][lane] = weight_frag([&](int k) { return p[kOW2 + (32 * (q % 2) + k) * kH + 16 * (q / 2) + c]; }, g);
+        sm.f3[q][lane] = weight_frag([&](int k) { return p[kOW3 + (32 * (q % 2) + k) * kH + 16 * (q / 2) + c]; }, g);
+    }
     // layer 1: K slot 4g + r (g = 0, 1, 2: the three parts) is feature r;
     // the other slots are zero.  Layer 4: output row c (< 3) of
     // W4^T, K = the 64 hidden units.  Both kept in LDS (one copy per lane
@@ -151,29 +155,36 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) v
                 for (int r = 0; r < 4; ++r) w[r] = (short)f2bf(p[kOW1 + r * kH + 16 * t + c]);
             sm.a1[t][lane] = cat8(w, z4);
         }
-        for (int s = 0; s < 2; ++s) {
-            bf16x4 lo4 = z4, hi4 = z4;
-            if (c < kOut)
-                for (int r = 0; r < 4; ++r) {
-                    const int in = 32 * s + 4 * g + r;
-                    lo4[r] = (short)f2bf(p[kOW4 + in * kOut + c]);
-                    hi4[r] = (short)f2bf(p[kOW4 + (in + 16) * kOut + c]);
-                }
-            sm.a4[s][lane] = cat8(lo4, hi4);
-        }
+        for (int s = 0; s < 2; ++s)
+            sm.a4[s][lane] = weight_frag([&](int k) { return c < kOut ? p[kOW4 + (32 * s + k) * kOut + c] : 0.f; }, g);
     }
     __syncthreads();
+    bf16x8 a2[4][2], a3[4][2];
+    for (int t = 0; t < 4; ++t)
+        for (int s = 0; s < 2; ++s) {
+            a2[t][s] = sm.f2[2 * t + s][lane];
+            a3[t][s] = sm.f3[2 * t + s][lane];
+        }
+    // the next tile's features are loaded a tile ahead and the basis at the
+    // tile's start: waiting for them in turn took half of the time
     const int64_t ntiles = ceil_div(n, (int64_t)16);
     const int64_t nw = (int64_t)gridDim.x * kWaves;
-    for (int64_t tile = (int64_t)blockIdx.x * kWaves + threadIdx.x / kWave; tile < ntiles; tile += nw) {
+    const auto features = [&](int64_t tile) {
+        const int64_t smp = tile * 16 + c;
+        return smp < n ? *reinterpret_cast<const float4*>(S + smp * kSample) : float4{0.f, 0.f, 0.f, 0.f};
+    };
+    int64_t tile = (int64_t)blockIdx.x * kWaves + threadIdx.x / kWave;
+    float4 x = features(tile);
+    for (; tile < ntiles; tile += nw) {
         // re-read the small LDS tables every tile rather than keeping them
         // in registers (which would leave room for fewer waves per SIMD)
         __asm__ volatile("" ::: "memory");
         const int64_t smp = tile * 16 + c;
-        const bool valid = smp < n;
-        const float4 x = valid ? *reinterpret_cast<const float4*>(S + smp * kSample) : float4{0.f, 0.f, 0.f, 0.f};
-        // layer 1 on MFMA, bias, ReLU, BF16: the B operand of layer 2
+        const bool last = g == 0 && smp < n;  // the lanes that write
+        float4 bs;
+        if (last) bs = *reinterpret_cast<const float4*>(S + smp * kSample + 4);
         const bf16x8 b1 = parts_operand({x.x, x.y, x.z, x.w}, g);
+        x = features(tile + nw);
         bf16x4 h[4];
         for (int t = 0; t < 4; ++t) {
             const f32x4 z = mfma32(sm.a1[t][lane], b1, f32x4{0.f, 0.f, 0.f, 0.f});
@@ -214,9 +225,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) v
             o4 = mfma32(w4, cat8(hh[2 * s], hh[2 * s + 1]), o4);
             o4 = mfma32(w4, cat8(hl[2 * s], hl[2 * s + 1]), o4);
         }
-        if (g == 0 && valid) {
+        if (last) {
             const float o0 = o4[0] + sm.b4[0], o1 = o4[1] + sm.b4[1], o2 = o4[2] + sm.b4[2];
-            const float4 bs = *reinterpret_cast<const float4*>(S + smp * kSample + 4);
             float pred = o0 * bs.x;
             pred = __builtin_fmaf(o1, bs.y, pred);
             pred = __builtin_fmaf(o2, bs.z, pred);
@@ -266,11 +276,7 @@ union TrainLds {
 __device__ inline void train_params(TrainSmem& sm, const float* __restrict__ p) {
     const bf16x4 z4 = {0, 0, 0, 0};
     const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave, g = lane / 16, c = lane % 16;
-    // value i of a fragment: K index 16 (i / 4) + 4g + i % 4 of the step
-    const auto frag = [&](auto w) {
-        return cat8(bf16x4_of(w(4 * g), w(4 * g + 1), w(4 * g + 2), w(4 * g + 3)),
-                    bf16x4_of(w(16 + 4 * g), w(17 + 4 * g), w(18 + 4 * g), w(19 + 4 * g)));
-    };
+    const auto frag = [&](auto w) { return weight_frag(w, g); };
 #pragma unroll
     for (int q = wave; q < 8; q += kWaves) {
         const int o = 16 * (q / 2) + c, k0 = 32 * (q % 2);
@@ -621,8 +627,9 @@ static int32_t tiles_per_wave(int64_t n, int32_t* grid) {
 
 sph_status sph::mlp::forward(sph_ctx* ctx, const float* samples, int64_t n, const float* params, float* out) {
     if (n == 0) return SPH_OK;
-    // several tiles per wave: each wave loads its 32 weight fragments once
-    const int64_t waves = std::min<int64_t>(ceil_div(ceil_div(n, (int64_t)16), 4), 8192);
+    // several tiles per wave, which loads its 32 weight fragments once, and
+    // no more waves than the chip holds at a time (four per SIMD)
+    const int64_t waves = std::min<int64_t>(ceil_div(ceil_div(n, (int64_t)16), 4), 4096);
     const int32_t grid = (int32_t)std::max<int64_t>(ceil_div(waves, (int64_t)kWaves), 1);
     hipLaunchKernelGGL(k_mlp_infer, dim3(grid), dim3(kThreads), 0, ctx->stream, samples, n, params, out);
     SPH_LAUNCHED("k_mlp_infer");
