@@ -55,7 +55,7 @@ __global__ __launch_bounds__(kBlock) void k_scan_tiles(const I* __restrict__ in,
         if (base + k < n) out[base + k] = off;
         off += v[k];
     }
-    if (threadIdx.x == 0) tile_sum[blockIdx.x] = total;
+    if (threadIdx.x == 0) (gridDim.x == 1 ? out + n : tile_sum + blockIdx.x)[0] = total;
 }
 
 template <typename I>
@@ -75,15 +75,30 @@ __global__ __launch_bounds__(1024) void k_scan_sums(I* __restrict__ tile_sum, in
     if (threadIdx.x == 0) *out_total = carry;
 }
 
-template <typename I>
+// Adds each tile's offset; OWN: the sum of the tiles before it, by the block
+// itself, and the last one's writes the total.
+template <typename I, bool OWN>
 __global__ __launch_bounds__(kBlock) void k_scan_add(I* __restrict__ out, const I* __restrict__ tile_sum,
                                                      int64_t n) {
+    __shared__ I lds[kBlock / kWave];
     const int64_t base = (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * kScanPer;
-    const I add = tile_sum[blockIdx.x];
+    I add = 0;
+    if constexpr (OWN) {
+        I s = 0;
+        for (unsigned i = threadIdx.x; i < blockIdx.x; i += blockDim.x) s += tile_sum[i];
+        (void)block_exclusive_scan<I>(s, lds, &add);
+        if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) out[n] = add + tile_sum[blockIdx.x];
+    } else {
+        add = tile_sum[blockIdx.x];
+    }
 #pragma unroll
     for (int k = 0; k < kScanPer; ++k)
         if (base + k < n) out[base + k] += add;
 }
+
+// Up to this many tiles their offsets are summed by every block, which saves a
+// launch (of three, about 5 us each; one tile takes a single launch).
+constexpr int64_t kScanOwn = 1024;
 
 template <typename I>
 static sph_status scan_impl(sph_ctx* ctx, const I* in, I* out, int64_t n) {
@@ -96,9 +111,12 @@ static sph_status scan_impl(sph_ctx* ctx, const I* in, I* out, int64_t n) {
     SPH_TRY(ctx->ensure_t(kScanTmp, (size_t)ntiles, &tiles));
     hipLaunchKernelGGL(k_scan_tiles<I>, dim3((unsigned)ntiles), dim3(kBlock), 0, ctx->stream, in, out,
                        tiles, n);
-    hipLaunchKernelGGL(k_scan_sums<I>, dim3(1), dim3(1024), 0, ctx->stream, tiles, ntiles, out + n);
-    hipLaunchKernelGGL(k_scan_add<I>, dim3((unsigned)ntiles), dim3(kBlock), 0, ctx->stream, out, tiles,
-                       n);
+    if (ntiles > kScanOwn) {
+        hipLaunchKernelGGL(k_scan_sums<I>, dim3(1), dim3(1024), 0, ctx->stream, tiles, ntiles, out + n);
+        hipLaunchKernelGGL((k_scan_add<I, false>), dim3((unsigned)ntiles), dim3(kBlock), 0, ctx->stream, out, tiles, n);
+    } else if (ntiles > 1) {
+        hipLaunchKernelGGL((k_scan_add<I, true>), dim3((unsigned)ntiles), dim3(kBlock), 0, ctx->stream, out, tiles, n);
+    }
     SPH_LAUNCHED("scan");
     return SPH_OK;
 }
@@ -134,6 +152,7 @@ __global__ __launch_bounds__(kBlock) void k_cell_of(int64_t n, const double* __r
                                                     const double* __restrict__ y,
                                                     const double* __restrict__ z, Grid g,
                                                     int32_t* __restrict__ cell,
+                                                    int32_t* __restrict__ place,
                                                     int32_t* __restrict__ count) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
@@ -142,18 +161,16 @@ __global__ __launch_bounds__(kBlock) void k_cell_of(int64_t n, const double* __r
     const int32_t cz = cell_axis(z[i], g.org[2], g.cs[2], g.nc[2], g.per[2]);
     const int32_t c = (cz * g.nc[1] + cy) * g.nc[0] + cx;
     cell[i] = c;
-    atomicAdd(&count[c], 1);
+    place[i] = atomicAdd(&count[c], 1);  // its place in the cell, in arrival order
 }
 
 __global__ __launch_bounds__(kBlock) void k_scatter(int64_t n, const int32_t* __restrict__ cell,
                                                     const int32_t* __restrict__ cell_start,
-                                                    int32_t* __restrict__ fill,
+                                                    const int32_t* __restrict__ place,
                                                     int32_t* __restrict__ perm) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
-    const int32_t c = cell[i];
-    const int32_t slot = cell_start[c] + atomicAdd(&fill[c], 1);
-    perm[slot] = (int32_t)i;
+    perm[cell_start[cell[i]] + place[i]] = (int32_t)i;
 }
 
 // The scatter above leaves each cell in arrival order; sort every cell by
@@ -347,7 +364,7 @@ extern "C" sph_status sph_build_neighbors(sph_ctx* ctx, const sph_particles* p, 
     nb->g = g;
     // temporaries from the context's workspace; the handle's arrays in one
     // allocation (device allocations and frees cost tens of microseconds each)
-    int32_t *cell = nullptr, *count = nullptr, *fill = nullptr;
+    int32_t *cell = nullptr, *count = nullptr, *place = nullptr;
     auto fail_oom = [&]() {
         sph_neighbors_free(nb);
         return ctx->fail(SPH_E_OOM, "build_neighbors: device allocation failed");
@@ -368,7 +385,7 @@ extern "C" sph_status sph_build_neighbors(sph_ctx* ctx, const sph_particles* p, 
     {
         sph_status st = ctx->ensure_t(kNbrCell, (size_t)n, &cell);
         if (st == SPH_OK) st = ctx->ensure_t(kNbrCount, (size_t)ncell, &count);
-        if (st == SPH_OK) st = ctx->ensure_t(kNbrFill, (size_t)ncell, &fill);
+        if (st == SPH_OK) st = ctx->ensure_t(kNbrPlace, (size_t)n, &place);
         if (st != SPH_OK) {
             sph_neighbors_free(nb);
             return st;
@@ -381,18 +398,18 @@ extern "C" sph_status sph_build_neighbors(sph_ctx* ctx, const sph_particles* p, 
         return ctx->hip_fail(e, what);
     };
     if ((e = hipMemsetAsync(count, 0, sizeof(int32_t) * ncell, ctx->stream)) != hipSuccess) return hip_err("memset");
-    if ((e = hipMemsetAsync(fill, 0, sizeof(int32_t) * ncell, ctx->stream)) != hipSuccess) return hip_err("memset");
     const unsigned gp = (unsigned)ceil_div(n, kBlock);
     const int32_t per = (int32_t)std::min<int64_t>(std::max<int64_t>(16 * ncell / n, 1), kWave);
     const unsigned gc = (unsigned)ceil_div(ncell, (int64_t)per * (kBlock / kWave));
-    hipLaunchKernelGGL(k_cell_of, dim3(gp), dim3(kBlock), 0, ctx->stream, n, p->x, p->y, p->z, g, cell, count);
+    hipLaunchKernelGGL(k_cell_of, dim3(gp), dim3(kBlock), 0, ctx->stream, n, p->x, p->y, p->z, g, cell, place,
+                       count);
     if ((e = hipGetLastError()) != hipSuccess) return hip_err("k_cell_of");
     sph_status st = scan_i32(ctx, count, nb->cell_start, ncell);
     if (st != SPH_OK) {
         sph_neighbors_free(nb);
         return st;
     }
-    hipLaunchKernelGGL(k_scatter, dim3(gp), dim3(kBlock), 0, ctx->stream, n, cell, nb->cell_start, fill, nb->perm);
+    hipLaunchKernelGGL(k_scatter, dim3(gp), dim3(kBlock), 0, ctx->stream, n, cell, nb->cell_start, place, nb->perm);
     hipLaunchKernelGGL(k_sort_cells, dim3(gc), dim3(kBlock), 0, ctx->stream, ncell, per, nb->cell_start,
                        nb->perm);
     hipLaunchKernelGGL(k_gather_pos, dim3(gp), dim3(kBlock), 0, ctx->stream, n, nb->perm, cell, p->x, p->y,

@@ -634,25 +634,24 @@ __global__ __launch_bounds__(kMaxBlock) void k_final_trr(Ctl* __restrict__ ctl, 
         for (int c = 0; c < 3; ++c) ctl->trr[c] = red[c];
 }
 
-__global__ void k_ctl_init(Ctl* ctl) {
-    int32_t* w = reinterpret_cast<int32_t*>(ctl);
-    for (size_t i = threadIdx.x; i < sizeof(Ctl) / sizeof(int32_t); i += blockDim.x) w[i] = 0;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        ctl->host_checked_iter = -1;
-        ctl->dev_checked_iter = -1;
-        ctl->restart_iter = -1;
-    }
-}
-
 // rhs in caller order (precision C) -> b64 = D^-1 B in FP64 and b = rounded
-// copy, cell order.
+// copy, cell order.  The first block also sets up the control block.
 template <typename T, typename C>
 __global__ __launch_bounds__(kBlock) void k_prep_rhs(int64_t n, const int32_t* __restrict__ perm,
                                                      const C* __restrict__ b0, const C* __restrict__ b1,
                                                      const C* __restrict__ b2, const double* __restrict__ diag64,
                                                      int32_t jacobi, double* __restrict__ b64,
-                                                     T* __restrict__ b) {
+                                                     T* __restrict__ b, Ctl* ctl) {
+    if (blockIdx.x == 0) {
+        int32_t* w = reinterpret_cast<int32_t*>(ctl);
+        for (size_t k = threadIdx.x; k < sizeof(Ctl) / sizeof(int32_t); k += blockDim.x) w[k] = 0;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            ctl->host_checked_iter = -1;
+            ctl->dev_checked_iter = -1;
+            ctl->restart_iter = -1;
+        }
+    }
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
     const int32_t o = perm[i];
@@ -906,11 +905,10 @@ sph_status solve_impl(sph_ctx* ctx, const sph_nbr* nb, const sph_particles* part
     S.sc.force_stall_comp = o->force_stall_comp;
     S.sc.hist_cap = hist_rows;
 
-    hipLaunchKernelGGL(k_ctl_init, dim3(1), dim3(64), 0, ctx->stream, S.ctl);
     hipLaunchKernelGGL((k_prep_rhs<T, X>), dim3((unsigned)ceil_div(n, kBlock)), dim3(kBlock), 0, ctx->stream, n,
                        nb->perm, (const X*)rhs[0], (const X*)rhs[1], (const X*)rhs[2], S.diag64, S.op.jacobi,
-                       S.b64, S.b);
-    S.launches += 2;
+                       S.b64, S.b, S.ctl);
+    ++S.launches;
     const T* r0 = nullptr;
     double* winfo = nullptr;
     if (o->warm_params) {
@@ -975,8 +973,7 @@ sph_status solve_impl(sph_ctx* ctx, const sph_nbr* nb, const sph_particles* part
         r0 = S.tmp;
         ++S.launches;
     }
-    SPH_HIP(hipMemsetAsync(S.p, 0, sizeof(T) * v3, ctx->stream));
-    SPH_HIP(hipMemsetAsync(S.ap, 0, sizeof(T) * v3, ctx->stream));
+    // (the first p update writes p and reads neither p nor A p)
     hipLaunchKernelGGL((k_init<T, KH>), S.gs(), S.bs(), 0, ctx->stream, n, S.b, r0, S.r, S.rh0, S.pk3);
     ++S.launches;
     SPH_LAUNCHED("solve setup");
