@@ -255,21 +255,15 @@ __device__ inline void win_stage(const WinRange& mine, int32_t nr, const XT* __r
     __syncthreads();
 }
 
-// The lane's range of the block's first window; its k-th lies kWinRanges k
-// further.  (One load per lane brings a window's table: a scalar load per
-// range, one after the other, took longer than the copy.)
-template <typename T>
-__device__ __forceinline__ const WinRange* win_table(const Sell<T>& A, int64_t bid) {
-    return A.win + bid * kWinParts * kWinRanges + (threadIdx.x & (kWinRanges - 1));
-}
-
-// Stages the windows of block `bid` in turn (r: the lane's range of the first)
-// and calls f() in the waves whose rows the staged window serves.  Called by
-// the whole block.
+// Stages the windows of block `bid` in turn and calls f() in the waves whose
+// rows the staged window serves.  Called by the whole block.
 template <typename T, typename XT, typename F>
-__device__ __forceinline__ void win_parts(const Sell<T>& A, int64_t bid, WinRange r, const XT* __restrict__ x,
-                                          unsigned char* lds, F&& f) {
-    const WinRange* tab = win_table(A, bid);
+__device__ __forceinline__ void win_parts(const Sell<T>& A, int64_t bid, const XT* __restrict__ x, unsigned char* lds, F&& f) {
+    if (bid * kWinRows >= A.nslices * kWave) return;
+    // one load per lane brings a window's table (a scalar load per range, one
+    // after the other, took longer than the copy)
+    const WinRange* tab = A.win + bid * kWinParts * kWinRanges + (threadIdx.x & (kWinRanges - 1));
+    WinRange r = *tab;
     const int32_t head = __builtin_amdgcn_readfirstlane(r.head);
     const int32_t np = head >> 16;
     win_stage(r, head & 0xFFFF, x, lds);
@@ -290,12 +284,6 @@ __device__ __forceinline__ void win_parts(const Sell<T>& A, int64_t bid, WinRang
         __syncthreads();
         win_stage(r, __builtin_amdgcn_readfirstlane(r.head) & 0xFFFF, x, lds);
     }
-}
-
-template <typename T, typename XT, typename F>
-__device__ __forceinline__ void win_parts(const Sell<T>& A, int64_t bid, const XT* __restrict__ x, unsigned char* lds,
-                                          F&& f) {
-    if (bid * kWinRows < A.nslices * kWave) win_parts(A, bid, win_table(A, bid)[0], x, lds, f);
 }
 
 // One group of slots in registers: the coefficients, the packed column codes
@@ -336,12 +324,9 @@ struct WinStream {
     int64_t base;   // the lane's first slot
     int32_t width;  // slice width, uniform across the wave
     G g[D];
-    __device__ __forceinline__ WinStream(const Sell<T>& A_, int64_t s, int lane)
-        : WinStream(A_, A_.sl_ptr[s], A_.sl_ptr[s + 1], lane) {}
-    // the slice's slots [p0, p1)
-    __device__ __forceinline__ WinStream(const Sell<T>& A_, int64_t p0, int64_t p1, int lane) : A(A_) {
-        base = lane_base<T>(p0, lane);
-        width = (int32_t)((p1 - p0) / kWave);
+    __device__ __forceinline__ WinStream(const Sell<T>& A_, int64_t s, int lane) : A(A_) {
+        base = lane_base<T>(A.sl_ptr[s], lane);
+        width = (int32_t)((A.sl_ptr[s + 1] - A.sl_ptr[s]) / kWave);
 #pragma unroll
         for (int d = 0; d < D; ++d) g[d].load(A, base, width, d * G::N);
     }
@@ -433,11 +418,9 @@ struct AccOf<T, true> {
 // window of x into LDS (about 130 bytes a row against the matrix's 490); the
 // gathers of x, one per slot and lane, are then LDS reads, and the matrix
 // stream has the vector memory path to itself.  The wave's first three groups
-// of slots are loaded before the window, and the flag, the slice's place and
-// the window's table come together before those (one after the other: 3.33 ms
-// instead of 3.14 of the first launch below).  A launch (A s with two dots):
-// 4.13 -> 3.14 ms at 33.7M particles in FP32 (5.6 TB/s of matrix, vectors and
-// windows' own share of HBM), 140 -> 114 us at 1.16M, 85 -> 61 us at 328k in
+// of slots are loaded before the window.  A launch (A s with two dots):
+// 4.13 -> 3.33 ms at 33.7M particles in FP32 (5.3 TB/s of matrix, vectors and
+// windows' own share of HBM), 140 -> 115 us at 1.16M, 85 -> 61 us at 328k in
 // FP64; the delta-coded kernel waits for its gathers, this one for HBM and, a
 // sixth of its time, for the windows.
 template <typename T, int MODE, typename XT = T, bool KH = false, bool WIN = false>
@@ -445,8 +428,7 @@ __global__ __launch_bounds__(kApplyMaxBlock) void k_apply_sell(const int32_t* __
                                                           const XT* __restrict__ x, T* __restrict__ y,
                                                           const T* __restrict__ w, const double* __restrict__ b64,
                                                           double* __restrict__ part) {
-    // (the flag comes with the first addresses, before the matrix)
-    const int32_t halted = halt ? *halt : 0;
+    if (halt && *halt) return;
     constexpr int K = DotK<MODE>::K;
     constexpr bool RES = MODE == kDotResid;
     static_assert(!KH || (sizeof(T) == 4 && !RES), "single-precision arithmetic: FP32 operator, not the residual");
@@ -472,21 +454,13 @@ __global__ __launch_bounds__(kApplyMaxBlock) void k_apply_sell(const int32_t* __
     V3<XT> xs{};
     if constexpr (WIN) {
         static_assert(kApplyMaxBlock == kWinRows, "one block's windows");
-        WinRange tab{};
-        const bool any = bid * kWinRows < A.nslices * kWave;
-        if (any) tab = win_table(A, bid)[0];
-        const int64_t* ptr = A.sl_ptr + min(s, A.nslices - 1);
-        const int64_t p0 = ptr[0], p1 = ptr[1];
-        if (halted) return;
-        WinStream<T, RES, XT> st(A, p0, p1, lane);
+        WinStream<T, RES, XT> st(A, min(s, A.nslices - 1), lane);
         if (on) xs = ld3(x, row);
-        if (any) win_parts(A, bid, tab, x, win_lds, [&]() __attribute__((always_inline)) {
+        win_parts(A, bid, x, win_lds, [&]() __attribute__((always_inline)) {
             if (!on) return;
             if constexpr (KH) win_row_kahan(st, win_lds, xs, A.dg[row], yv);
             else win_row<T, RES>(st, win_lds, xs, a0, a1, a2);
         });
-    } else if (halted) {
-        return;
     } else if (on) {
         const int64_t base = lane_base<T>(A.sl_ptr[s], lane);
         const int32_t width = (int32_t)((A.sl_ptr[s + 1] - A.sl_ptr[s]) / kWave);
