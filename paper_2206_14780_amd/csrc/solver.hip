@@ -991,8 +991,8 @@ sph_status solve_impl(sph_ctx* ctx, const sph_nbr* nb, const sph_particles* part
     // 10 us against a round trip of 20).
     constexpr int32_t kAhead = 2;
     constexpr int64_t kEagerRows = 1 << 18;
-    const int32_t most = o->poll_every > 0 ? o->poll_every : kAhead;
-    IssuePlan plan(o->poll_every > 0 ? o->poll_every : 8);
+    int32_t most = o->poll_every > 0 ? std::min(o->poll_every, kAhead) : kAhead;
+    IssuePlan plan(8);
     const int32_t last_it = o->max_iter + 1;  // P of this iteration always halts
     int32_t j = 0;
     int32_t checked_j = -1;  // last iteration whose true residual a host-issued check took
@@ -1013,6 +1013,7 @@ sph_status solve_impl(sph_ctx* ctx, const sph_nbr* nb, const sph_particles* part
             m.iter = j + 1;
             m.halt = 0;
             plan.restart(m);
+            most = 1;  // (a later round is often short)
         }
         S.sc.tag = ++ctx->mail_tag & 0xFFFF;
         int32_t seen = j;  // last iteration whose p update has been seen
