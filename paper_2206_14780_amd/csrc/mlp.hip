@@ -137,7 +137,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) v
     // A operands: step s of output tile t holds W[in][16t + c] (W stored
     // [in][out]) for the lane group's K slots, in = 32s + 16 (i / 4) + 4g + i % 4.
     // The waves share their gathers: each by itself, as before, read all 128
-    // values of a lane one by one, 10 us of a launch of 985k samples.
+    // values of a lane one by one, 19 us of a launch of 985k samples.
     const int lane = threadIdx.x % kWave, g = lane / 16, c = lane % 16;
     for (int q = threadIdx.x / kWave; q < 8; q += kWaves) {
         sm.f2[q][lane] = weight_frag([&](int k) { return p[kOW2 + (32 * (q % 2) + k) * kH + 16 * (q / 2) + c]; }, g);
