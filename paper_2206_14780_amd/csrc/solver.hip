@@ -219,10 +219,16 @@ __global__ __launch_bounds__(kMaxBlock) void k_pupd(Ctl* __restrict__ ctl, int32
                                                     const double* __restrict__ dw, double* __restrict__ part_rho) {
     __shared__ double lds[2 * kKp * kMaxWaves];
     __shared__ CtlCopy copy;
-    const int32_t halt = ctl->halt;
     copy.load(ctl);
+    // This launch's own block 0 may set the halt word while a late block
+    // starts: one thread of a block reads it, and all its waves follow that
+    // copy (waves that each read it could part ways before the block's sum).
+    const auto stop = [&] {
+        __syncthreads();
+        return copy.get()->halt != 0;
+    };
     double red[kKp];
-    if (!reduce_partials_kh<kKp, KH>(part, nblk, red, lds, [&] { return halt != 0; })) return;
+    if (!reduce_partials_kh<kKp, KH>(part, nblk, red, lds, stop)) return;
     rsc_all(sc, red);
     const Ctl* old = copy.get();  // (the block's sum has passed its barriers)
     const int32_t j = it - 1;

@@ -493,8 +493,9 @@ __device__ inline void write_partials_kh(double (&v)[K], float (&cmp)[K], double
 }
 
 // reduce_partials, or (KH) the compensated FP32 sum of the partials.
-// stop(), asked between the thread's loads and the block's sum, ends it early
-// (the same for the whole block): false is then returned.
+// stop(), asked between the thread's loads and the block's sum, ends it early:
+// false is then returned.  It must be the same for the whole block, which a
+// word read by every wave is only where no block of the same launch writes it.
 template <int K, bool KH, typename F>
 __device__ inline bool reduce_partials_kh(const double* __restrict__ part, int nblk, double (&out)[K], double* lds,
                                           F&& stop) {
