@@ -237,7 +237,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) v
 
 // Forward and backward of a batch (sample ids idx[0, batch)); every block
 // writes its partial gradient (kNParam values) and its partial sum of squared
-// errors to part[block][0 .. kNParam].
+// errors, in FP64, to part[block][0 .. kNParam].
 //
 // Each product is taken twice with the operands swapped: transposed ("T": lane
 // (g, c) holds features 16t + 4g + r of sample c), which is the next product's
@@ -252,11 +252,16 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) v
 // the last layer's data gradient take their FP32 inputs as three BF16 parts,
 // that is exactly; bias gradients and those of layers 1 and 4 are FP32 on the
 // vector ALU.  The four waves' gradients are added in FP64 in the block.
-// A step of 65,536 samples: 68 -> 28 us, and the sum of the 256 partials (1024
-// before) 9 -> 4.
+// A step of 65,536 samples with the sum of its 256 partials (1024, one per wave,
+// before): 82 -> 42 us; 38 with a block's sums rounded to FP32, whose gradient
+// is further off.
 // What bounds it is the vector ALU of a single wave (bias, ReLU, rounding and
 // the small gradients: about 700 instructions a tile) and, at this size, the
 // setup and the exchange at the end, about a third.
+// Sums over the samples are FP32 within four tiles of a wave (the accumulators
+// of the matrix cores) and FP64 from there on: the block adds its waves'
+// values after every four tiles, so that a larger batch does not make the FP32
+// chains longer, and hands the sum on unrounded.
 struct alignas(16) TrainSmem {
     bf16x8 f2[8][kWave], f3[8][kWave];  // W[in][16t + c], K = in; [2 t + s]: tile t, K step s
     bf16x8 r2[8][kWave], r3[8][kWave];  // W[16t + c][out], K = out
@@ -268,7 +273,7 @@ struct alignas(16) TrainSmem {
     float4 go[kWaves][2][16];           // output gradients of two tiles
 };
 constexpr int kExchange = 64;  // values per lane that the waves exchange at a time
-union TrainLds {
+struct TrainLds {
     TrainSmem p;
     float x[kWaves][kExchange][kWave];
 };
@@ -312,7 +317,7 @@ __device__ inline bf16x4 to_bf16(f32x4 d) { return bf16x4_of(d[0], d[1], d[2], d
 
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 1))) void k_mlp_train(
     const float* __restrict__ S, const int32_t* __restrict__ idx, int64_t batch, const float* __restrict__ params,
-    float* __restrict__ part, int32_t tiles_per_wave) {
+    double* __restrict__ part, int32_t tiles_per_wave) {
     __shared__ __align__(16) TrainLds lds;
     TrainSmem& sm = lds.p;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
@@ -339,17 +344,18 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 1))
     __syncthreads();
     const float inv_m = 2.0f / (float)batch;
     const f32x4 z = {0.f, 0.f, 0.f, 0.f};
-    f32x4 gW2[4][4], gW3[4][4];
-    for (int i = 0; i < 4; ++i)
-        for (int j = 0; j < 4; ++j) gW2[i][j] = gW3[i][j] = z;
-    float gW1[4][4] = {}, gW4[4][3] = {}, gb1[4] = {}, gb2[4] = {}, gb3[4] = {}, gb4[3] = {}, sse = 0.f;
+    double* P = part + (int64_t)blockIdx.x * (kNParam + 1);
     // a layer's bias as the accumulator to start from, in both forms
     const auto biasT = [&](const float* b, int t) { return *reinterpret_cast<const f32x4*>(b + 16 * t + 4 * g); };
     const auto biasN = [&](const float* b, int t) {
         const float v = b[16 * t + c];
         return f32x4{v, v, v, v};
     };
-    for (int32_t q = 0; q < mine; q += 4) {
+    for (int32_t q = 0; q < tiles_per_wave; q += 4) {
+        f32x4 gW2[4][4], gW3[4][4];
+        for (int i = 0; i < 4; ++i)
+            for (int j = 0; j < 4; ++j) gW2[i][j] = gW3[i][j] = z;
+        float gW1[4][4] = {}, gW4[4][3] = {}, gb1[4] = {}, gb2[4] = {}, gb3[4] = {}, gb4[3] = {}, sse = 0.f;
         sm.smp[wave][g][c][0] = sx;
         sm.smp[wave][g][c][1] = sb;
         wave_sync();
@@ -512,56 +518,57 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 1))
             }
             wave_sync();
         }
-    }
-    // The block's sums: the waves' values side by side in LDS, 64 per lane at a
-    // time, added by all threads.
-    float* P = part + (int64_t)blockIdx.x * (kNParam + 1);
-    const auto exchange = [&](const f32x4 (&gW)[4][4], int off) {
+        // The block's sums of these four tiles: the waves' values side by side
+        // in LDS, 64 per lane at a time, added by all threads (P[at] by the
+        // same one every time).
+        const auto put = [&](int at, double s) { P[at] = q == 0 ? s : P[at] + s; };
+        const auto exchange = [&](const f32x4 (&gW)[4][4], int off) {
+            __syncthreads();
+#pragma unroll
+            for (int mt = 0; mt < 4; ++mt)
+#pragma unroll
+                for (int nt = 0; nt < 4; ++nt)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) lds.x[wave][(4 * mt + nt) * 4 + r][lane] = gW[mt][nt][r];
+            __syncthreads();
+            for (int v = wave; v < kExchange; v += kWaves) {
+                double s = 0.0;
+                for (int w = 0; w < kWaves; ++w) s += (double)lds.x[w][v][lane];
+                put(off + (16 * (v / 16) + 4 * g + v % 4) * kH + 16 * (v / 4 % 4) + c, s);
+            }
+        };
+        exchange(gW2, kOW2);
+        exchange(gW3, kOW3);
         __syncthreads();
+        constexpr int kSmall = 10;  // per tile t: four rows of W1, three biases, three columns of W4
 #pragma unroll
-        for (int mt = 0; mt < 4; ++mt)
-#pragma unroll
-            for (int nt = 0; nt < 4; ++nt)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) lds.x[wave][(4 * mt + nt) * 4 + r][lane] = gW[mt][nt][r];
-        __syncthreads();
-        for (int v = wave; v < kExchange; v += kWaves) {
-            double s = 0.0;
-            for (int w = 0; w < kWaves; ++w) s += (double)lds.x[w][v][lane];
-            P[off + (16 * (v / 16) + 4 * g + v % 4) * kH + 16 * (v / 4 % 4) + c] = (float)s;
+        for (int t = 0; t < 4; ++t) {
+            for (int f = 0; f < 4; ++f) lds.x[wave][kSmall * t + f][lane] = gW1[f][t];
+            lds.x[wave][kSmall * t + 4][lane] = gb1[t];
+            lds.x[wave][kSmall * t + 5][lane] = gb2[t];
+            lds.x[wave][kSmall * t + 6][lane] = gb3[t];
+            for (int k = 0; k < 3; ++k) lds.x[wave][kSmall * t + 7 + k][lane] = gW4[t][k];
         }
-    };
-    exchange(gW2, kOW2);
-    exchange(gW3, kOW3);
-    __syncthreads();
-    constexpr int kSmall = 10;  // per tile t: four rows of W1, three biases, three columns of W4
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-        for (int f = 0; f < 4; ++f) lds.x[wave][kSmall * t + f][lane] = gW1[f][t];
-        lds.x[wave][kSmall * t + 4][lane] = gb1[t];
-        lds.x[wave][kSmall * t + 5][lane] = gb2[t];
-        lds.x[wave][kSmall * t + 6][lane] = gb3[t];
-        for (int k = 0; k < 3; ++k) lds.x[wave][kSmall * t + 7 + k][lane] = gW4[t][k];
-    }
-    for (int k = 0; k < 3; ++k) lds.x[wave][4 * kSmall + k][lane] = gb4[k];
-    lds.x[wave][4 * kSmall + 3][lane] = sse;
-    __syncthreads();
-    // features 16t + c: over the waves and their lane groups
-    for (int e = threadIdx.x; e < 4 * kSmall * 16; e += kThreads) {
-        const int v = e / 16, t = v / kSmall, k = v % kSmall, o = 16 * t + e % 16;
+        for (int k = 0; k < 3; ++k) lds.x[wave][4 * kSmall + k][lane] = gb4[k];
+        lds.x[wave][4 * kSmall + 3][lane] = sse;
+        __syncthreads();
+        // features 16t + c: over the waves and their lane groups
+        for (int e = threadIdx.x; e < 4 * kSmall * 16; e += kThreads) {
+            const int v = e / 16, t = v / kSmall, k = v % kSmall, o = 16 * t + e % 16;
+            double s = 0.0;
+            for (int w = 0; w < kWaves; ++w)
+                for (int l = e % 16; l < kWave; l += 16) s += (double)lds.x[w][v][l];
+            const int at = k < 4 ? kOW1 + k * kH + o : k == 4 ? kOB1 + o : k == 5 ? kOB2 + o : k == 6 ? kOB3 + o
+                                                                                              : kOW4 + o * kOut + k - 7;
+            put(at, s);
+        }
+        // output biases and squared error: a wave each, over the waves' lanes of group 0
         double s = 0.0;
-        for (int w = 0; w < kWaves; ++w)
-            for (int l = e % 16; l < kWave; l += 16) s += (double)lds.x[w][v][l];
-        const int at = k < 4 ? kOW1 + k * kH + o : k == 4 ? kOB1 + o : k == 5 ? kOB2 + o : k == 6 ? kOB3 + o
-                                                                                          : kOW4 + o * kOut + k - 7;
-        P[at] = (float)s;
+        if (lane < 16)
+            for (int w = 0; w < kWaves; ++w) s += (double)lds.x[w][4 * kSmall + wave][lane];
+        for (int off = 1; off < 16; off <<= 1) s += __shfl_xor(s, off, kWave);
+        if (lane == 0) put(wave < 3 ? kOB4 + wave : kNParam, s);
     }
-    // output biases and squared error: a wave each, over the waves' lanes of group 0
-    double s = 0.0;
-    if (lane < 16)
-        for (int w = 0; w < kWaves; ++w) s += (double)lds.x[w][4 * kSmall + wave][lane];
-    for (int off = 1; off < 16; off <<= 1) s += __shfl_xor(s, off, kWave);
-    if (lane == 0) P[wave < 3 ? kOB4 + wave : kNParam] = (float)s;
 }
 static_assert(kWaves == 4, "the four values beside the tiles: a wave each");
 
@@ -573,7 +580,7 @@ static_assert(kWaves == 4, "the four values beside the tiles: a wave each");
 // wave adds the waves' sums in wave order, so the result depends only on
 // the number of partials, not on timing.
 constexpr int kRedWaves = 16;
-__global__ __launch_bounds__(kRedWaves * kWave) void k_mlp_reduce(const float* __restrict__ part, int32_t nparts,
+__global__ __launch_bounds__(kRedWaves * kWave) void k_mlp_reduce(const double* __restrict__ part, int32_t nparts,
                                                                   int64_t batch, float* __restrict__ params,
                                                                   float* __restrict__ m, float* __restrict__ v,
                                                                   float* __restrict__ grad, int32_t step,
@@ -584,7 +591,7 @@ __global__ __launch_bounds__(kRedWaves * kWave) void k_mlp_reduce(const float* _
     double sw = 0.0;
     if (p <= kNParam) {
 #pragma unroll 8
-        for (int q = w; q < nparts; q += kRedWaves) sw += (double)part[(int64_t)q * (kNParam + 1) + p];
+        for (int q = w; q < nparts; q += kRedWaves) sw += part[(int64_t)q * (kNParam + 1) + p];
     }
     lds[w][lane] = sw;
     __syncthreads();
@@ -651,7 +658,7 @@ static sph_status train_or_grad(sph_ctx* ctx, const float* samples, const int32_
     int32_t grid = 0;
     const int32_t tpw = tiles_per_wave(batch, &grid);
     const int64_t nparts = grid;
-    float* part = nullptr;
+    double* part = nullptr;
     double* out = nullptr;
     SPH_TRY(ctx->ensure_t(kMlpPart, (size_t)nparts * (kNParam + 1), &part));
     SPH_TRY(ctx->ensure_t(kMlpOut, 1, &out));
