@@ -185,7 +185,9 @@ struct RowWriter {
 
 // RowWriter's counterpart for the windowed code: the window index of a column
 // comes from the block's ranges, which ascend with the columns of a row, so a
-// lane walks them once.
+// lane walks them once.  A coefficient that is 0 codes the row itself (as the
+// delta-coded row gathers it), so that an Inf or NaN of x which the matrix does
+// not see stays out of the sum.
 template <typename T>
 struct WinWriter {
     T* coef;
@@ -193,7 +195,7 @@ struct WinWriter {
     float* lo;
     int64_t base;
     const WinRange* tab;  // the block's ranges
-    int32_t own;          // column code of the row itself (padding)
+    int32_t own;          // column code of the row itself (padding, zeros)
     int32_t j = 0;
     int32_t q = 0;
     __device__ int32_t code(int32_t col) {
@@ -201,7 +203,7 @@ struct WinWriter {
         return (col - tab[q].beg + tab[q].base) * kWinStep;
     }
     __device__ void put(int32_t col, double c) {
-        sell_put(coef, dcol, lo, slot_of<T>(base, j), code(col), c);
+        sell_put(coef, dcol, lo, slot_of<T>(base, j), (T)c == T(0) ? own : code(col), c);
         ++j;
     }
     __device__ void pad(int32_t width) {
@@ -991,7 +993,7 @@ __global__ __launch_bounds__(W* kWave) __attribute__((amdgpu_waves_per_eu(2))) v
                     }
                 }
                 cv[u] = (T)v;
-                dv[u] = on ? code(a[t][e * P + u]) : own;
+                dv[u] = cv[u] != T(0) ? code(a[t][e * P + u]) : own;  // (zeros and padding: see WinWriter)
                 if constexpr (sizeof(T) == 4) lv[u] = (float)(v - (double)cv[u]);
             }
             const int64_t i = slot_of<T>(base, k0 + e * P);

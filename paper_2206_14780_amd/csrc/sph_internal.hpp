@@ -92,7 +92,7 @@ struct OpParams {
 //     takes; dcol holds kWinStep times the window index of the
 //     column (a byte offset into the window of FP32 3-vectors that the
 //     operator stages in LDS).  Rows shorter than their slice are padded with
-//     (own row, coef 0).
+//     (own row, coef 0); an entry whose coefficient is 0 codes its own row too.
 //   delta coded (wmax = 0; a system with a window too large to stage): the row
 //     starts at column c0[r] and each slot adds its 16-bit step dcol (the
 //     first entry steps by 0).  A step that does not fit takes an escape slot
