@@ -82,38 +82,12 @@ constexpr int kCellRows = 4;      // rows of a wave at a time, 16 lanes each
 constexpr int kCellList = 192;    // listed neighbours of a row before they are summed
 enum { kTakeNone = 0, kTakeAll = 1, kTakeFluid = 2 };  // neighbours of a row
 
-// Candidates that a block stages: the mean of the 27 cells around a particle
-// and a seventh more (the blocks of cells of a lattice hold up to 8^3 where
-// the mean is 7.95^3), within the LDS; a cell with more is done in batches.
-inline int32_t cell_cap(const sph_nbr* nb) {
-    const double want = 27.0 * (double)nb->n / (double)nb->ncell * 1.07;
-    const int32_t most = nb->g.kernel == SPH_KERNEL_GAUSSIAN ? 1900 : 1024;
-    return (int32_t)(want < most ? want : most) / kWave * kWave + kWave;
-}
 template <class B, int W>
 constexpr size_t cell_bytes(int32_t cap) {
     // positions and extras, fluid masks, and the rows' lists, which share their
     // place with the candidates' indices
     return W == 0 ? 0 : (size_t)cap * (24 + sizeof(typename B::X) * B::NX) + 8 * (cap / kWave) +
            (W * kCellRows * kCellList * 2 > cap * 4 ? W * kCellRows * kCellList * 2 : cap * 4);
-}
-
-// Whether the sums are taken a cell at a time, or by one thread per row
-// (cell_rows<0>).  Blocks pay for cells that are empty or hold a row or two,
-// as in a box that the particles fill in part: the operator (FP64) by cells /
-// by rows at 1M scattered particles with 4, 8, 21 in the mean cell: 2.57 /
-// 0.82, 1.77 / 1.23, 1.82 / 2.54 ms; at 65k with 4, 7, 16: 198 / 161, 154 / 226,
-// 152 / 400 us; Gaussian, 1M, 21, 64: 3.65 / 2.80, 4.72 / 6.49 ms; 65k, 7, 16:
-// 446 / 246, 317 / 441 us.  Cells with more candidates than a block stages at
-// once still gain while the rows alone are too few for the chip: 65k, 65 in a
-// cell, 0.62 / 1.30 ms, but 1M, 64: 7.2 / 5.9; and a few blocks do not fill it
-// either (4096 particles in 8 cells: 4.1 / 1.8 ms).
-inline bool by_cells(const sph_nbr* nb) {
-    const bool gauss = nb->g.kernel == SPH_KERNEL_GAUSSIAN, small = nb->n < (1 << 18);
-    const double mean = (double)nb->n / (double)nb->ncell;
-    if (mean < (gauss ? (small ? 12.0 : 32.0) : (small ? 5.0 : 12.0))) return false;
-    const double most = (gauss ? 1900.0 : 1024.0) / (27.0 * 1.07);
-    return mean <= most || (small && nb->ncell >= 64);
 }
 
 // cell_rows by one thread per row.

@@ -220,9 +220,11 @@ __device__ inline void sort_cell(int32_t* __restrict__ perm, int32_t b, int32_t 
     }
 }
 
+// crowd[k] becomes 1 where a cell of kCrowdLeast particles or more has k
+// kCrowdStep of them (k_gather_pos takes it to the host).
 __global__ __launch_bounds__(kBlock) void k_sort_cells(int64_t ncell, int32_t per,
                                                        const int32_t* __restrict__ cell_start,
-                                                       int32_t* __restrict__ perm) {
+                                                       int32_t* __restrict__ perm, int32_t* __restrict__ crowd) {
     const int lane = threadIdx.x & (kWave - 1);
     const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const int64_t c = ((int64_t)blockIdx.x * (kBlock / kWave) + wid) * per + lane;
@@ -231,6 +233,7 @@ __global__ __launch_bounds__(kBlock) void k_sort_cells(int64_t ncell, int32_t pe
         beg = cell_start[c];
         len = cell_start[c + 1] - beg;
     }
+    if (len >= kCrowdLeast) crowd[min(len / kCrowdStep, kCrowdLevels - 1)] = 1;
     for (uint64_t todo = __ballot(len > 1); todo; todo &= todo - 1) {
         const int l = __builtin_ctzll(todo);
         sort_cell(perm, __builtin_amdgcn_readlane(beg, l), __builtin_amdgcn_readlane(len, l), lane);
@@ -244,8 +247,10 @@ __global__ __launch_bounds__(kBlock) void k_gather_pos(int64_t n, const int32_t*
                                                        const double* __restrict__ z,
                                                        Pos4* __restrict__ pos,
                                                        int32_t* __restrict__ scell,
-                                                       int32_t* __restrict__ iperm) {
+                                                       int32_t* __restrict__ iperm,
+                                                       const int32_t* __restrict__ crowd, int32_t* host_crowd) {
     const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (s < kCrowdLevels) __hip_atomic_store(&host_crowd[s], crowd[s], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     if (s >= n) return;
     const int32_t o = perm[s];
     pos[s] = Pos4{x[o], y[o], z[o], 0.0};
@@ -384,7 +389,7 @@ extern "C" sph_status sph_build_neighbors(sph_ctx* ctx, const sph_particles* p, 
     }
     {
         sph_status st = ctx->ensure_t(kNbrCell, (size_t)n, &cell);
-        if (st == SPH_OK) st = ctx->ensure_t(kNbrCount, (size_t)ncell, &count);
+        if (st == SPH_OK) st = ctx->ensure_t(kNbrCount, (size_t)ncell + kCrowdLevels, &count);
         if (st == SPH_OK) st = ctx->ensure_t(kNbrPlace, (size_t)n, &place);
         if (st != SPH_OK) {
             sph_neighbors_free(nb);
@@ -397,7 +402,7 @@ extern "C" sph_status sph_build_neighbors(sph_ctx* ctx, const sph_particles* p, 
         sph_neighbors_free(nb);
         return ctx->hip_fail(e, what);
     };
-    if ((e = hipMemsetAsync(count, 0, sizeof(int32_t) * ncell, ctx->stream)) != hipSuccess) return hip_err("memset");
+    if ((e = hipMemsetAsync(count, 0, sizeof(int32_t) * (ncell + kCrowdLevels), ctx->stream)) != hipSuccess) return hip_err("memset");
     const unsigned gp = (unsigned)ceil_div(n, kBlock);
     const int32_t per = (int32_t)std::min<int64_t>(std::max<int64_t>(16 * ncell / n, 1), kWave);
     const unsigned gc = (unsigned)ceil_div(ncell, (int64_t)per * (kBlock / kWave));
@@ -411,11 +416,13 @@ extern "C" sph_status sph_build_neighbors(sph_ctx* ctx, const sph_particles* p, 
     }
     hipLaunchKernelGGL(k_scatter, dim3(gp), dim3(kBlock), 0, ctx->stream, n, cell, nb->cell_start, place, nb->perm);
     hipLaunchKernelGGL(k_sort_cells, dim3(gc), dim3(kBlock), 0, ctx->stream, ncell, per, nb->cell_start,
-                       nb->perm);
+                       nb->perm, count + ncell);
     hipLaunchKernelGGL(k_gather_pos, dim3(gp), dim3(kBlock), 0, ctx->stream, n, nb->perm, cell, p->x, p->y,
-                       p->z, nb->pos, nb->scell, nb->iperm);
+                       p->z, nb->pos, nb->scell, nb->iperm, (const int32_t*)(count + ncell), ctx->mail_dev->crowd);
     if ((e = hipGetLastError()) != hipSuccess) return hip_err("neighbour build kernels");
     if ((e = hipStreamSynchronize(ctx->stream)) != hipSuccess) return hip_err("hipStreamSynchronize");
+    for (int32_t k = 0; k < kCrowdLevels; ++k)
+        if (__atomic_load_n(&ctx->host_mail->crowd[k], __ATOMIC_RELAXED)) nb->fullest = k * kCrowdStep;
     *out = nb;
     return SPH_OK;
 }

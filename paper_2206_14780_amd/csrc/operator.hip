@@ -664,7 +664,7 @@ __global__ __launch_bounds__(kBlock) void k_row_scan(NbrView nv, PartView pv, Op
 }
 
 // The scan by one thread per row, for cells that are mostly empty or too full
-// (see launch_row_scan).  The lanes of a wave reach their k-th neighbour at
+// (see scan_by_rows).  The lanes of a wave reach their k-th neighbour at
 // different points, so each collects kChunk indices in LDS and writes them as
 // one segment.
 __global__ __launch_bounds__(kBlock) void k_row_scan_rows(NbrView nv, PartView pv, OpParams op, bool all,
@@ -1024,34 +1024,22 @@ sph_status row_diag64(sph_ctx* ctx, const sph_nbr* nb, const PartView& pv, const
     return SPH_OK;
 }
 
-// Whether k_row_scan_rows scans, and the matrix keeps the delta code.  A wave
-// per cell pays for empty cells too (30M cells around 1000 particles: 4.6 ms),
-// the windows of scattered rows are many short ranges, and of rows that are
-// mostly longer than their list (the mean over the support's sphere) the
-// counts of slots are wanted.  Matrix and one product, FP64, by cells and
-// windows / by rows and delta code: 1M scattered particles with 2, 4, 8, 21 in
-// the mean cell 1.48 / 0.75, 1.27 / 1.05, 1.44 / 1.57, 10.4 / 10.6 ms, with 64
-// 29.4 / 27.3; 65k with 2, 4, 7: 196 / 180, 188 / 233, 199 / 301 us; Gaussian, 1M
-// with 8, 21: 1.73 / 1.61, 2.93 / 3.38 ms.
-static bool scan_by_rows(const sph_nbr* nb, int32_t cap) {
-    const double mean = (double)nb->n / (double)nb->ncell;
-    const double least = nb->n < (1 << 18) ? 3.0 : nb->g.kernel == SPH_KERNEL_GAUSSIAN ? 12.0 : 6.0;
-    const double row = mean * 4.19 * nb->g.cut2 * std::sqrt(nb->g.cut2) / (nb->g.cs[0] * nb->g.cs[1] * nb->g.cs[2]);
-    return mean < least || row > (cap > 0 ? cap : kListCapGauss);
-}
-
+// The scan, and with win the operator's windows (by cells in the same launch);
 // cnt: slots of the delta code per row (by rows only, may be null).
 static void launch_row_scan(sph_ctx* ctx, const sph_nbr* nb, const PartView& pv, const OpParams& op, bool all,
                             bool by_rows, int32_t* cnt, int32_t* creal, int32_t* list, int32_t cap, WinRange* win,
                             int32_t* wmax) {
     constexpr int64_t kW = kBlock / kWave;
+    const int64_t wblk = win ? ceil_div(ceil_div(nb->n, (int64_t)kWinRows), kW) : 0;
     if (by_rows) {
+        if (win)
+            hipLaunchKernelGGL(k_row_scan, dim3((unsigned)wblk), dim3(kBlock), 0, ctx->stream, nb->view(), pv, op,
+                               nb->ncell, 1, all, creal, list, cap, (int32_t)wblk, win, wmax);
         const int64_t blocks = ceil_div(ceil_div(nb->n, (int64_t)kBlock), (int64_t)kNumXcd) * kNumXcd;
         hipLaunchKernelGGL(k_row_scan_rows, dim3((unsigned)blocks), dim3(kBlock), 0, ctx->stream, nb->view(), pv, op,
                            all, cnt, creal, list, cap);
         return;
     }
-    const int64_t wblk = win ? ceil_div(ceil_div(nb->n, (int64_t)kWinRows), kW) : 0;
     // four waves per SIMD (what the scan's registers allow) on every CU
     int32_t split = 1;
     while (split < 8 && nb->ncell * split < 4096) split *= 2;
@@ -1106,8 +1094,8 @@ int32_t export_cap(const sph_nbr* nb) {
 sph_status neighbour_scan(sph_ctx* ctx, const sph_nbr* nb, int32_t cap, int32_t* count, int32_t** list) {
     int32_t* l = nullptr;
     if (cap > 0) SPH_TRY(ctx->ensure_t(kList, (size_t)ceil_div(nb->n, (int64_t)kWave) * kWave * cap, &l));
-    launch_row_scan(ctx, nb, PartView{}, OpParams{}, true, scan_by_rows(nb, cap), nullptr, count, l, cap, nullptr,
-                    nullptr);
+    launch_row_scan(ctx, nb, PartView{}, OpParams{}, true, scan_by_rows(nb->occupancy(), cap > 0 ? cap : kListCapGauss),
+                    nullptr, count, l, cap, nullptr, nullptr);
     SPH_LAUNCHED("k_row_scan");
     if (list) *list = l;
     return SPH_OK;
@@ -1128,7 +1116,7 @@ sph_status export_rows(sph_ctx* ctx, const sph_nbr* nb, int32_t cap, const int32
 
 template <typename T>
 sph_status build_sell(sph_ctx* ctx, const sph_nbr* nb, const PartView& pv, const OpParams& op, Sell<T>* out,
-                      const double** diag64, int64_t* nnz_out, int64_t* slots_out) {
+                      const double** diag64, int64_t* nnz_out, int64_t* slots_out, bool once) {
     const int64_t n = nb->n;
     const int64_t nslices = ceil_div(n, kWave);
     // Test hook: the environment variable SPH_BUILD_LEGACY=1 selects the
@@ -1143,8 +1131,9 @@ sph_status build_sell(sph_ctx* ctx, const sph_nbr* nb, const PartView& pv, const
                                 (size_t)nslices * kWave * kListCapGauss * 12 <= kListBudget
                             ? kListCapGauss
                             : kListCap;
-    const bool by_rows = scan_by_rows(nb, cap);
-    const bool windows = !legacy && !by_rows;
+    const Occupancy occ = nb->occupancy();
+    const bool by_rows = scan_by_rows(occ, cap);
+    const bool windows = !legacy && !delta_coded(occ, cap) && !(once && crowded_scan(occ));
     int32_t *cnt = nullptr, *creal = nullptr, *list = nullptr;
     double *d = nullptr, *ws = nullptr, *wlist = nullptr;
     int64_t *size = nullptr, *ptr = nullptr;
@@ -1245,9 +1234,9 @@ sph_status build_sell(sph_ctx* ctx, const sph_nbr* nb, const PartView& pv, const
 }
 
 template sph_status build_sell<float>(sph_ctx*, const sph_nbr*, const PartView&, const OpParams&, Sell<float>*,
-                                      const double**, int64_t*, int64_t*);
+                                      const double**, int64_t*, int64_t*, bool);
 template sph_status build_sell<double>(sph_ctx*, const sph_nbr*, const PartView&, const OpParams&,
-                                       Sell<double>*, const double**, int64_t*, int64_t*);
+                                       Sell<double>*, const double**, int64_t*, int64_t*, bool);
 
 
 // Launch geometry of the row kernels.
@@ -1345,7 +1334,7 @@ static sph_status apply_entry(sph_ctx* ctx, const sph_nbr* nb, const sph_particl
     SPH_TRY(gather_vec3<T>(ctx, nb, x, xin));
     Sell<T> sell{};
     if (v->op_mode == SPH_OP_PAPER32) op.f32cell = 1;
-    if (v->op_mode != SPH_OP_ONTHEFLY) SPH_TRY(build_sell<T>(ctx, nb, pv, op, &sell, nullptr));
+    if (v->op_mode != SPH_OP_ONTHEFLY) SPH_TRY(build_sell<T>(ctx, nb, pv, op, &sell, nullptr, nullptr, nullptr, true));
     SPH_TRY(apply_plain<T>(ctx, nb, pv, op, v->op_mode, &sell, xin, yout));
     SPH_TRY(scatter_vec3<T>(ctx, nb, yout, y));
     return SPH_OK;

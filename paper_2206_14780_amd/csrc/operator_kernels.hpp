@@ -618,7 +618,8 @@ template <typename T, int MODE, typename XT = T>
 inline void launch_apply_otf(hipStream_t stream, const Launch& L, const int32_t* halt, const sph_nbr* nb,
                              const PartView& pv, const OpParams& op, const XT* x, T* y, const T* w, const double* b64,
                              double* part) {
-    const int32_t cap = cell_cap(nb);
+    const Occupancy occ = nb->occupancy();
+    const int32_t cap = cell_cap(occ);
     const int64_t cells = ceil_div(nb->ncell, (int64_t)kNumXcd) * kNumXcd;
     const auto go = [&](auto waves) {
         constexpr int W = decltype(waves)::value;
@@ -627,7 +628,7 @@ inline void launch_apply_otf(hipStream_t stream, const Launch& L, const int32_t*
                            (cell_bytes<OtfBody<XT, int>, W>(cap)), stream, halt, nb->view(), pv, op, nb->ncell, cap, x,
                            y, w, b64, part);
     };
-    if (!by_cells(nb)) go(std::integral_constant<int, 0>{});
+    if (!sums_by_cells(occ)) go(std::integral_constant<int, 0>{});
     else if (nb->g.kernel == SPH_KERNEL_GAUSSIAN) go(std::integral_constant<int, kCellWavesGauss>{});
     else go(std::integral_constant<int, kCellWaves>{});
 }

@@ -849,7 +849,7 @@ sph_status solve_impl(sph_ctx* ctx, const sph_nbr* nb, const sph_particles* part
     S.L = make_launch(n, sizeof(T) == 8);
     // the on-the-fly operator by cells: enough blocks for the chip's places
     // (a solve's products at 65k particles, 7 in a cell: 340 us each with 256)
-    if (S.mode == SPH_OP_ONTHEFLY && by_cells(nb))
+    if (S.mode == SPH_OP_ONTHEFLY && sums_by_cells(nb->occupancy()))
         S.L.grid_apply = (int32_t)std::max<int64_t>(
             S.L.grid_apply, std::min<int64_t>(ceil_div(nb->ncell, (int64_t)kNumXcd) * kNumXcd, 2048));
     const Launch& L = S.L;

@@ -3,6 +3,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <cmath>
 #include <cstddef>
 #include <cstdint>
 #include <cstring>
@@ -11,6 +12,7 @@
 
 #include "sph.h"
 #include "issue_plan.hpp"
+#include "occupancy.hpp"
 
 namespace sph {
 
@@ -93,7 +95,7 @@ struct OpParams {
 //     column (a byte offset into the window of FP32 3-vectors that the
 //     operator stages in LDS).  Rows shorter than their slice are padded with
 //     (own row, coef 0); an entry whose coefficient is 0 codes its own row too.
-//   delta coded (wmax = 0; a system with a window too large to stage): the row
+//   delta coded (wmax = 0; a window too large to stage, or see delta_coded): the row
 //     starts at column c0[r] and each slot adds its 16-bit step dcol (the
 //     first entry steps by 0).  A step that does not fit takes an escape slot
 //     (dcol = kEscape) whose coefficient bits hold the whole jump and which
@@ -219,6 +221,7 @@ struct HostMail {
     SolveMail mail;
     alignas(64) Ctl ctl;
     int32_t stall[3 * kMailStallRows];
+    int32_t crowd[kCrowdLevels];  // neighbour build: a cell of level k (k kCrowdStep particles) was seen
 };
 
 // Constants of one solve, passed by value to the iteration kernels.
@@ -300,7 +303,12 @@ struct sph_nbr {
     sph::Pos4* pos = nullptr;
     void* blob = nullptr;       // the one device allocation holding the arrays above
     int64_t nnz = -1;           // pair count, computed on demand
+    int32_t fullest = 0;        // see Occupancy
 
+    sph::Occupancy occupancy() const {
+        const double cell = g.cs[0] * g.cs[1] * g.cs[2];
+        return {n, ncell, g.kernel == SPH_KERNEL_GAUSSIAN, fullest, 4.19 * g.cut2 * std::sqrt(g.cut2) / cell};
+    }
     sph::NbrView view() const {
         sph::NbrView v;
         v.n = n;
@@ -356,11 +364,12 @@ sph_status gather_vec3_cvt(sph_ctx* ctx, const sph_nbr* nb, const void* const sr
 template <typename T>
 sph_status scatter_vec3(sph_ctx* ctx, const sph_nbr* nb, const T* src, void* const dst[3]);
 // Builds the cached matrix, windowed where the windows fit; *nnz / *slots (host, optional) receive the
-// off-diagonal entry count and the stored slot count.
+// off-diagonal entry count and the stored slot count; once: the matrix is for
+// a single product.
 template <typename T>
 sph_status build_sell(sph_ctx* ctx, const sph_nbr* nb, const PartView& pv, const OpParams& op,
                       Sell<T>* out, const double** diag64, int64_t* nnz = nullptr,
-                      int64_t* slots = nullptr);
+                      int64_t* slots = nullptr, bool once = false);
 template <typename T>
 sph_status apply_plain(sph_ctx* ctx, const sph_nbr* nb, const PartView& pv, const OpParams& op,
                        int mode, const Sell<T>* sell, const T* x, T* y);

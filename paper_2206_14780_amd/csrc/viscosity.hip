@@ -104,7 +104,8 @@ static sph_status papa_entry(sph_ctx* ctx, const sph_nbr* nb, const sph_particle
     SPH_TRY(ctx->ensure_t(kViscU, (size_t)nb->n * 3, &ucell));
     SPH_TRY(gather_vec3<T>(ctx, nb, u, ucell));
     const double x0 = std::pow(362880.0 * std::ldexp(1.0, -23), 0.125);
-    const int32_t cap = cell_cap(nb);
+    const Occupancy occ = nb->occupancy();
+    const int32_t cap = cell_cap(occ);
     const auto go = [&](auto waves) {
         constexpr int W = decltype(waves)::value;
         const int64_t blocks = W ? nb->ncell : ceil_div(nb->n, (int64_t)kBlock);
@@ -113,7 +114,7 @@ static sph_status papa_entry(sph_ctx* ctx, const sph_nbr* nb, const sph_particle
                            nb->view(), nb->ncell, cap,
                            (PapaBody<T>{pv, ucell, nb->perm, tau0, m, mu0, x0, mu_out, d_out}));
     };
-    if (!by_cells(nb)) go(std::integral_constant<int, 0>{});
+    if (!sums_by_cells(occ)) go(std::integral_constant<int, 0>{});
     else if (nb->g.kernel == SPH_KERNEL_GAUSSIAN) go(std::integral_constant<int, kCellWavesGauss>{});
     else go(std::integral_constant<int, kCellWaves>{});
     SPH_LAUNCHED("k_papa_visc");
