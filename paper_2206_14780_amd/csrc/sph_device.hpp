@@ -94,6 +94,19 @@ __device__ inline int axis_cells(int32_t c, int32_t n, int32_t per, int32_t (&ou
     return m;
 }
 
+// Particles from the first to the last cell around cell c, by index.
+__device__ inline int32_t candidate_span(const NbrView& nv, int32_t c) {
+    const Grid& g = nv.g;
+    const int32_t nx = g.nc[0], ny = g.nc[1];
+    int32_t xs[3], ys[3], zs[3];
+    const int nxs = axis_cells(c % nx, nx, g.per[0], xs);
+    const int nys = axis_cells((c / nx) % ny, ny, g.per[1], ys);
+    const int nzs = axis_cells(c / (nx * ny), g.nc[2], g.per[2], zs);
+    const int32_t first = (zs[0] * ny + ys[0]) * nx + xs[0];
+    const int32_t last = (zs[nzs - 1] * ny + ys[nys - 1]) * nx + xs[nxs - 1];
+    return nv.cell_start[last + 1] - nv.cell_start[first];
+}
+
 // Calls f(a, r2) for every neighbour a of sorted particle `row` (a != row,
 // r2 = |r_row - r_a|^2 < (2h)^2), visiting the 3x3x3 cell block around the
 // particle's cell as at most 9 runs of consecutive cells along x (a wrapped
