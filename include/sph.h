@@ -152,9 +152,11 @@ typedef struct {
  *          restarted from that residual.  0 = only when no component progresses.
  *   x0_given: 1 = x holds the initial guess on entry, 0 = start from zero.
  *   poll_every: most iterations queued beyond the last one whose outcome the
- *          host has read (0 = library default, 2; more count as 2).  Fewer
- *          where the residual history predicts the halt, so that few
- *          iterations are issued past it.  Does not change the result.
+ *          host has read (0 = library default, 2).  More than 2 are queued
+ *          while the residual history, of at least twice as many iterations,
+ *          predicts the halt at least four times as far away; fewer where it is
+ *          near, so that few iterations are issued past it.  Does not change
+ *          the result.
  *   force_stall_iter / force_stall_comp: test hook; at that iteration that
  *          component's delta is treated as zero.  -1 = off.
  *   profile: k > 0 = bracket the second operator launch (A r_star and its

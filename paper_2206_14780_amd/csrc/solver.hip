@@ -985,20 +985,16 @@ sph_status solve_impl(sph_ctx* ctx, const sph_nbr* nb, const sph_particles* part
     SPH_LAUNCHED("solve setup");
     SPH_HIP(hipEventRecord(e1, ctx->stream));
 
-    // Iterate.  Each p update mails its outcome (SolveMail); the host keeps at
-    // most kAhead iterations queued beyond the one whose p update it has seen
-    // and, near the halt that IssuePlan forecasts, none, which leaves no gap:
-    // the p update is the first kernel of its iteration, and the others run
-    // while the host queues the next.  Kernels issued after a halt return at
+    // Iterate.  Each p update mails its outcome (SolveMail); the host keeps few
+    // iterations queued beyond the one whose p update it has seen and, near the
+    // forecast halt, none (IssueLoop).  Kernels issued after a halt return at
     // once, but cost a launch each: with polls by copy and event, one batch
-    // behind, a solve of 8 iterations at 1.5k particles issued 20.  Round
+    // behind, a solve of 8 iterations at 5,632 particles issued 20.  Round
     // trips at the end: with at most kEagerRows rows the solution is written
     // before the host knows that no further round follows (a scatter of some
     // 10 us against a round trip of 20).
-    constexpr int32_t kAhead = 2;
     constexpr int64_t kEagerRows = 1 << 18;
-    int32_t most = o->poll_every > 0 ? std::min(o->poll_every, kAhead) : kAhead;
-    IssuePlan plan(8);
+    IssueLoop loop(o->poll_every);
     const int32_t last_it = o->max_iter + 1;  // P of this iteration always halts
     int32_t j = 0;
     int32_t checked_j = -1;  // last iteration whose true residual a host-issued check took
@@ -1018,19 +1014,17 @@ sph_status solve_impl(sph_ctx* ctx, const sph_nbr* nb, const sph_particles* part
             std::memcpy(m.state, hctl.state, sizeof(m.state));
             m.iter = j + 1;
             m.halt = 0;
-            plan.restart(m);
-            most = 1;  // (a later round is often short)
+            loop.later_round(m);
         }
         S.sc.tag = ++ctx->mail_tag & 0xFFFF;
         int32_t seen = j;  // last iteration whose p update has been seen
         uint64_t word = 0;
         int32_t reason = 0;
         while (!reason) {
-            const int32_t ahead = it - 1 - seen;
-            const int32_t k = it <= last_it && ahead < most ? std::min(plan.batch(it, ahead > 0), most - ahead) : 0;
+            const int32_t k = it <= last_it ? loop.queue(it, seen) : 0;
             for (int32_t q = 0; q < k && it <= last_it; ++q) SPH_TRY(S.iteration(it++));
             if (k > 0) SPH_LAUNCHED("iteration kernels");
-            else if (ahead == 0) return ctx->fail(SPH_E_HIP, "visc_solve: iteration issue ended without a halt");
+            else if (it - 1 == seen) return ctx->fail(SPH_E_HIP, "visc_solve: iteration issue ended without a halt");
             const uint64_t now = __atomic_load_n(&host.mail.word, __ATOMIC_ACQUIRE);
             if (k > 0 && (now == word || (uint32_t)(now >> kMailTag) != S.sc.tag)) continue;
             SPH_TRY(wait_mail(ctx, S.sc.tag, &word));
@@ -1044,7 +1038,7 @@ sph_status solve_impl(sph_ctx* ctx, const sph_nbr* nb, const sph_particles* part
                 m.state[c] = (int32_t)(word >> (kMailState + 2 * c) & 3);
             }
             seen = m.iter;
-            plan.observe(m);
+            loop.observe(m);
         }
         S.issued_iters += (it - 1) - j0;
         j = seen;  // (of a halt: the iteration before the p update's)
