@@ -38,6 +38,14 @@ sph_status sph_ctx::ensure(int slot, size_t bytes, void** out) {
     return SPH_OK;
 }
 
+void sph_ctx::release(int slot) {
+    if (!ws[slot]) return;
+    (void)hipStreamSynchronize(stream);
+    (void)hipFree(ws[slot]);
+    ws[slot] = nullptr;
+    ws_bytes[slot] = 0;
+}
+
 extern "C" sph_status sph_create(sph_ctx** out, int32_t device, void* hip_stream) {
     if (!out) return SPH_E_ARG;
     *out = nullptr;

@@ -282,6 +282,8 @@ struct sph_ctx {
     // Ensure workspace slot `slot` holds at least `bytes`; on success *out
     // receives the device pointer.
     sph_status ensure(int slot, size_t bytes, void** out);
+    // Frees the slot once the stream is done with it.
+    void release(int slot);
     template <typename P>
     sph_status ensure_t(int slot, size_t count, P** out) {
         void* v = nullptr;
