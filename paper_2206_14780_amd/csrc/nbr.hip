@@ -262,6 +262,17 @@ __global__ __launch_bounds__(kBlock) void k_gather_pos(int64_t n, const int32_t*
 // ---------------------------------------------------------------------------
 // Canonical export: CSR over original indices, columns ascending.
 // ---------------------------------------------------------------------------
+// Neighbours of every particle, in the caller's order.
+__global__ __launch_bounds__(kBlock) void k_count_rows(NbrView nv, const int32_t* __restrict__ iperm,
+                                                       int64_t* __restrict__ cnt) {
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= nv.n) return;
+    int32_t c = 0;
+    for_each_neighbor(nv, iperm[i], [&](int32_t, double) { ++c; });
+    cnt[i] = c;
+}
+
+// The same from the counts of the scan, and (longest not null) the largest.
 __global__ __launch_bounds__(kBlock) void k_count_orig(int64_t n, const int32_t* __restrict__ iperm,
                                                        const int32_t* __restrict__ count, int64_t* __restrict__ cnt,
                                                        int32_t* __restrict__ longest) {
@@ -271,6 +282,7 @@ __global__ __launch_bounds__(kBlock) void k_count_orig(int64_t n, const int32_t*
         c = count[iperm[i]];
         cnt[i] = c;
     }
+    if (!longest) return;
     __shared__ int32_t most[kBlock / kWave];
     for (int o = kWave / 2; o > 0; o >>= 1) c = max(c, __shfl_xor(c, o, kWave));
     if (threadIdx.x % kWave == 0) most[threadIdx.x / kWave] = c;
@@ -429,19 +441,28 @@ extern "C" sph_status sph_build_neighbors(sph_ctx* ctx, const sph_particles* p, 
 }
 
 // Pairs per particle (caller order) into cnt and the lists behind them (cap
-// entries per row, 0: none); *longest: device, the longest row.
+// entries per row, 0: none); *longest: device, the longest row (null without lists).
 static sph_status count_pairs(sph_ctx* ctx, const sph_nbr* nb, int32_t cap, int64_t** cnt_out, int32_t** count,
                               int32_t** list, int32_t** longest) {
     int64_t* cnt = nullptr;
     SPH_TRY(ctx->ensure_t(kExportCnt, (size_t)(nb->n + 1), &cnt));
-    SPH_TRY(ctx->ensure_t(kCntReal, (size_t)nb->n + 1, count));
-    *longest = *count + nb->n;
-    SPH_HIP(hipMemsetAsync(*longest, 0, sizeof(int32_t), ctx->stream));
-    SPH_TRY(neighbour_scan(ctx, nb, cap, *count, list));
-    hipLaunchKernelGGL(k_count_orig, dim3((unsigned)ceil_div(nb->n, kBlock)), dim3(kBlock), 0, ctx->stream, nb->n,
-                       nb->iperm, (const int32_t*)*count, cnt, *longest);
-    SPH_LAUNCHED("k_count_orig");
     *cnt_out = cnt;
+    *longest = nullptr;
+    const dim3 grid((unsigned)ceil_div(nb->n, kBlock));
+    if (cap == 0 && count_in_caller_order(nb->occupancy())) {
+        hipLaunchKernelGGL(k_count_rows, grid, dim3(kBlock), 0, ctx->stream, nb->view(), nb->iperm, cnt);
+        SPH_LAUNCHED("k_count_rows");
+        return SPH_OK;
+    }
+    SPH_TRY(ctx->ensure_t(kCntReal, (size_t)nb->n + 1, count));
+    if (cap > 0) {
+        *longest = *count + nb->n;
+        SPH_HIP(hipMemsetAsync(*longest, 0, sizeof(int32_t), ctx->stream));
+    }
+    SPH_TRY(neighbour_scan(ctx, nb, cap, *count, list));
+    hipLaunchKernelGGL(k_count_orig, grid, dim3(kBlock), 0, ctx->stream, nb->n, nb->iperm, (const int32_t*)*count, cnt,
+                       *longest);
+    SPH_LAUNCHED("k_count_orig");
     return SPH_OK;
 }
 
@@ -500,15 +521,15 @@ extern "C" sph_status sph_neighbors_export(sph_ctx* ctx, const sph_nbr* nb, int6
     SPH_TRY(st);
     SPH_TRY(scan_i64(ctx, cnt, row_ptr, nb->n));
     int64_t total = 0;
-    int32_t most = 0;
+    int32_t most = INT32_MAX;
     SPH_HIP(hipMemcpyAsync(&total, row_ptr + nb->n, sizeof(int64_t), hipMemcpyDeviceToHost, ctx->stream));
-    SPH_HIP(hipMemcpyAsync(&most, longest, sizeof(int32_t), hipMemcpyDeviceToHost, ctx->stream));
+    if (lcap > 0) SPH_HIP(hipMemcpyAsync(&most, longest, sizeof(int32_t), hipMemcpyDeviceToHost, ctx->stream));
     SPH_HIP(hipStreamSynchronize(ctx->stream));
     const_cast<sph_nbr*>(nb)->nnz = total;
     *nnz = total;
     if (total > cap || (!cols && total > 0)) return ctx->fail(SPH_E_OVERFLOW, "neighbors_export: cols too small");
     if (lcap > 0) SPH_TRY(export_rows(ctx, nb, lcap, count, list, row_ptr, cols));
-    if (most > lcap) {
+    if (most > lcap && total > 0) {
         hipLaunchKernelGGL(k_fill_orig, dim3((unsigned)ceil_div(nb->n, kBlock)), dim3(kBlock), 0, ctx->stream,
                            nb->view(), nb->iperm, nb->perm, row_ptr, lcap, cols);
         SPH_LAUNCHED("k_fill_orig");

@@ -1096,6 +1096,7 @@ __global__ __launch_bounds__(kBlock) void k_export_rows(int64_t n, const int32_t
 
 int32_t export_cap(const sph_nbr* nb) {
     const int32_t cap = nb->g.kernel == SPH_KERNEL_GAUSSIAN ? kListCapGauss : kListCap;
+    if (export_without_lists(nb->occupancy())) return 0;
     return (size_t)ceil_div(nb->n, (int64_t)kWave) * kWave * cap * 4 <= kListBudget ? cap : 0;
 }
 

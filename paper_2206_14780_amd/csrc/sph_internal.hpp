@@ -380,7 +380,7 @@ sph_status row_diag64(sph_ctx* ctx, const sph_nbr* nb, const PartView& pv, const
 
 // Neighbour counts (cell order) of every particle and, with cap > 0, their
 // lists of at most cap entries; export_cap: the entries that an export lists
-// per row (0: none, beyond the lists' budget).  export_rows writes the listed
+// per row (0: none, beyond the lists' budget or not worth it).  export_rows writes the listed
 // rows of the canonical lists; rows beyond cap are left out.
 int32_t export_cap(const sph_nbr* nb);
 sph_status neighbour_scan(sph_ctx* ctx, const sph_nbr* nb, int32_t cap, int32_t* count, int32_t** list);

@@ -15,7 +15,7 @@ from paper_2206_14780_amd import workloads as W
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 LIST_CAP = {W.KERNEL_WENDLAND: 96, W.KERNEL_GAUSSIAN: 288}
-Rules = namedtuple("Rules", "cap sums_by_cells delta scan_by_rows")
+Rules = namedtuple("Rules", "cap sums_by_cells delta scan_by_rows no_lists caller_order")
 
 
 @functools.lru_cache(maxsize=None)
