@@ -88,6 +88,14 @@ __device__ inline bf16x8 parts_operand(const float (&v)[4], int g) {
     return cat8(g == 0 ? hi : (g == 1 ? lo : (g == 2 ? last : z4)), z4);
 }
 
+// A weight operand of one step: w(k) for the lane group's K indices, value i at
+// k = 16 (i / 4) + 4g + i % 4.
+template <typename F>
+__device__ inline bf16x8 weight_frag(F&& w, int g) {
+    return cat8(bf16x4_of(w(4 * g), w(4 * g + 1), w(4 * g + 2), w(4 * g + 3)),
+                bf16x4_of(w(16 + 4 * g), w(17 + 4 * g), w(18 + 4 * g), w(19 + 4 * g)));
+}
+
 // Inference: out[s] = (o0, o1, o2, pred) for samples [0, n).  All four
 // products run on MFMA, transposed, Z^T = W^T H^T, with the 16 samples of a
 // tile on the MFMA N dimension: a product's output then sits in registers
@@ -102,14 +110,6 @@ __device__ inline bf16x8 parts_operand(const float (&v)[4], int g) {
 // rounded to BF16 next, where a less accurate input would flip roundings); the
 // last hidden layer as two parts, to 2^-16 relative (one K step per part; the
 // output is not rounded again).  The training kernel takes three there too.
-// A weight operand of one step: w(k) for the lane group's K indices, value i at
-// k = 16 (i / 4) + 4g + i % 4.
-template <typename F>
-__device__ inline bf16x8 weight_frag(F&& w, int g) {
-    return cat8(bf16x4_of(w(4 * g), w(4 * g + 1), w(4 * g + 2), w(4 * g + 3)),
-                bf16x4_of(w(16 + 4 * g), w(17 + 4 * g), w(18 + 4 * g), w(19 + 4 * g)));
-}
-
 struct alignas(16) InferSmem {
     alignas(16) float b1[kH];
     alignas(16) float b2[kH];

@@ -257,7 +257,6 @@ __global__ __launch_bounds__(kBlock) void k_row_count(NbrView nv, PartView pv, O
     if (wsum) wsum[row] = sW;
 }
 
-// Slice size = 64 x (most slots of a row of the slice); nnz += entries.
 constexpr int kChunk = 16;                    // indices per segment
 constexpr int kListCap = 96;                  // listed neighbours per row, Wendland kernel
 constexpr int kListCapGauss = 288;            // the same, truncated Gaussian
@@ -305,8 +304,9 @@ __device__ inline int32_t row_slots(const NbrView& nv, const PartView& pv, const
     return sc.slots;
 }
 
-// Slots per row: cnt, or (null) the entries of windowed columns, which need
-// no escapes (*wmax <= wlim), or those of the delta code, counted here.
+// Slice size = 64 x (most slots of a row of the slice); nnz += entries.  Slots
+// per row: the entries of windowed columns, which need no escapes (*wmax <=
+// wlim), else cnt or (null) those of the delta code, counted here.
 __global__ __launch_bounds__(kBlock) void k_slice_size(int64_t n, int64_t nslices, int32_t pack,
                                                        NbrView nv, PartView pv, OpParams op,
                                                        const int32_t* __restrict__ list, int32_t cap,
